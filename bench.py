@@ -98,7 +98,7 @@ def describe(w):
         what = f"alpha={list(w['alphas'])}, beta=1, k={w['k']}"
     return (f"{d}D {grid} {op} operator scaled to (0,1], {what}, "
             f"{w['nrhs']} rhs ({w['rhs']}), {w['precision']} {sched} "
-            f"GMG V(2,2)-PCG to rel residual {w['tol']:g}")
+            f"{'' if w['var'] else 'direct sine-basis start, then '}GMG V(2,2)-PCG to rel residual {w['tol']:g}")
 
 
 def make_rhs(w):
@@ -118,7 +118,7 @@ def make_rhs(w):
 # roofline kernel: each covers launches of one kernel on the finest level with
 # one per-point byte count (restriction and prolongation mix levels in 3D)
 PROFILE_CLASSES = ("smooth_fine", "smooth_fine_rup", "down_fine", "down_fine_plain", "up_fine", "spmv",
-                   "update_xr", "restrict", "prolong", "residual64", "combine")
+                   "update_xr", "restrict", "prolong", "residual64", "combine", "direct")
 ROOF_CLASSES = ("smooth_fine", "smooth_fine_rup", "down_fine", "down_fine_plain", "up_fine", "spmv", "update_xr",
                 "residual64", "combine")
 DEFAULT_WORKLOAD = "2d511-var-k7-256rhs-mixed"

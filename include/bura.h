@@ -11,8 +11,18 @@
  * where r(t)/t = sum_j c_j/(t - d_j) (eq. (15)), r the best uniform rational
  * approximation of t^(1-alpha) on [0,1] (Definition 2.1, eq. (11)), d_0 = 0 >
  * d_1 > ... > d_k and c_j > 0 (Lemma 2.5, Remark 2.6).  Each of the k+1 shifted
- * SPD systems is solved on the GPU by geometric-multigrid preconditioned CG;
- * the k+1 solutions are combined in FP64.
+ * SPD systems is solved on the GPU: with constant coefficients by a direct
+ * solution in the sine basis, whose FP64 residual is tested, and by
+ * geometric-multigrid preconditioned CG from there (from zero with variable
+ * coefficients) until every system meets its tolerance; the k+1 solutions are
+ * combined in FP64.
+ *
+ * The direct solution starts every solve of a constant-coefficient plan whose
+ * tolerance is at most 1e-6, up to 2047 points per axis in 2D and 1023 in 3D,
+ * unless the caller has set the damping (bura_opts_t.omega) or the launch
+ * shapes (bura_plan_set_tiles) of the multigrid kernels, or its tables (four
+ * matrices of about n/2 x n/2 doubles) do not fit the plan's budget.  A system
+ * that it solves reports 0 iterations.
  *
  * Grids: the unit square / cube, n interior points per axis, h = 1/(n+1),
  * homogeneous Dirichlet boundary.  Vectors are FP64, interior points only, in
@@ -123,7 +133,8 @@ typedef struct {
   double omega;        /* Jacobi damping of every sweep; 0 = library default: 4/5 (2D)
                           or 6/7 (3D), and for the FP32 inner solves of BURA_MIXED
                           per-sweep Chebyshev weights on [0.4, 2] (2D) or [0.5, 2]
-                          (3D) for nu <= 2, on [0.3, 2] for nu = 3                     */
+                          (3D) for nu <= 2, on [0.3, 2] for nu = 3.  > 0 also keeps a
+                          constant-coefficient plan to the multigrid iteration         */
   void* stream;        /* hipStream_t used for every launch and copy; NULL = null stream */
   size_t hbm_budget;   /* 0 = unlimited; else plan creation fails with BURA_ENOMEM if its
                           device footprint would exceed this many bytes                 */
@@ -131,7 +142,8 @@ typedef struct {
                           times every tile-shape variant of the stencil product and of
                           each level's fused kernels on the plan's buffers (whole solves
                           in the plan's schedule) and keeps the fastest (cached per shape
-                          in the process; see bura_plan_tiles)                           */
+                          in the process; see bura_plan_tiles).  Plans whose solves the
+                          direct solution starts (tol <= 1e-6) have nothing to time      */
   double err_tol;      /* 0: stop on the residual test (tol) alone.  > 0 (BURA_MIXED, plans
                           without stages; else BURA_EUNSUPPORTED): also require the certified
                           bound of the report (err_bound) to be <= err_tol; the refinement
@@ -144,7 +156,8 @@ typedef struct {
                           them; any other bit: BURA_EINVAL                               */
 } bura_opts_t;
 
-/* Alternative code paths (bura_opts_t.variant). */
+/* Alternative code paths (bura_opts_t.variant) of the multigrid iteration (a
+ * solve that the direct solution starts runs them only where it iterates). */
 enum bura_variant {
   BURA_VARIANT_UNFUSED = 1,      /* 2D multigrid: one kernel per V-cycle step (sweep, residual
                                     and restriction, prolongation) instead of the two fused
@@ -381,7 +394,8 @@ int bura_plan_apply(bura_plan_t plan, double shift, const double* x_dev, double*
 int bura_plan_tiles(bura_plan_t plan, int* out, int max_len, int* len);
 
 /* Set the variants (layout as bura_plan_tiles, len must equal its *len, each
- * value in [0, BURA_TILE_VARIANTS)).  Synchronises the plan's stream and
+ * value in [0, BURA_TILE_VARIANTS)); the plan's solves then run these kernels
+ * from zero, without the direct solution.  Synchronises the plan's stream and
  * drops its captured graphs; BURA_EBUSY while asynchronous solves are queued
  * or running. */
 int bura_plan_set_tiles(bura_plan_t plan, const int* v, int len);
@@ -405,7 +419,8 @@ enum bura_kernel_class {
   BURA_K_DOWN_FINE_PLAIN = 13, /* finest level, fused, without the residual update (the first
                                 preconditioner application of each PCG solve)                    */
   BURA_K_SMOOTH_FINE_RUP = 14, /* first fine-level sweep with the PCG residual update (3D)         */
-  BURA_K_COUNT = 15
+  BURA_K_DIRECT = 15,          /* direct solution of constant-coefficient systems in the sine basis */
+  BURA_K_COUNT = 16
 };
 
 /* Profiling of the plan's launches (for measurement, not for production use).

@@ -497,7 +497,7 @@ def bura_plan_apply(plan, shift: float, x: torch.Tensor, y: torch.Tensor, nvec: 
 
 KERNEL_CLASSES = ["smooth_fine", "smooth_coarse", "restrict", "prolong", "coarse_lds", "spmv", "update_xr",
                   "update_p", "residual64", "combine", "other", "down_fine", "up_fine", "down_fine_plain",
-                  "smooth_fine_rup"]
+                  "smooth_fine_rup", "direct"]
 
 
 def bura_plan_profile(plan, enable):

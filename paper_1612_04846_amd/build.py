@@ -8,11 +8,12 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbura.so")
-HIP_SOURCES = ["bura_kernels.hip", "bura_engine.cpp", "bura_server.cpp"]
+HIP_SOURCES = ["bura_kernels.hip", "bura_direct.hip", "bura_engine.cpp", "bura_server.cpp"]
 HOST_SOURCES = ["bura_remez.cpp", "bura_sinc.cpp"]   # plain C++ (Remez in __float128; quadrature), built by g++
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -21,7 +22,6 @@ FLAGS = [
     "-O3",
     "-std=c++17",
     "-fPIC",
-    "-shared",
     # keep the compiler from emitting packed FP32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-result",
@@ -40,14 +40,21 @@ def _run(cmd, verbose):
 def build(verbose: bool = False) -> str:
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    objs = []
-    for s in HOST_SOURCES:
-        obj = os.path.join(objdir, os.path.splitext(s)[0] + ".o")
-        _run(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-c", os.path.join(CSRC, s), "-o", obj], verbose)
-        objs.append(obj)
-    srcs = [os.path.join(CSRC, s) for s in HIP_SOURCES]
+
+    def compile_one(src):
+        obj = os.path.join(objdir, src + ".o")
+        path = os.path.join(CSRC, src)
+        if src in HOST_SOURCES:
+            _run(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-c", path, "-o", obj], verbose)
+        else:
+            _run([HIPCC] + FLAGS + ["-x", "hip", "-c", path, "-o", obj], verbose)
+        return obj
+
+    sources = HIP_SOURCES + HOST_SOURCES
+    with ThreadPoolExecutor(max_workers=4) as pool:
+        objs = list(pool.map(compile_one, sources))
     tmp = LIB + ".tmp"
-    _run([HIPCC] + FLAGS + ["-o", tmp, "-x", "hip"] + srcs + ["-x", "none"] + objs + ["-lquadmath"], verbose)
+    _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs + ["-lquadmath"], verbose)
     os.replace(tmp, LIB)
     return LIB
 

@@ -187,6 +187,14 @@ struct bura_plan_s {
   double* d_upart = nullptr;   // rows x ceil(N/256) partial sums
   double* d_unorm = nullptr;   // rows = nout x nrhs_max
   double* d_tol_err = nullptr; // MIXED: per-system refinement tolerances set by opts.err_tol
+  // direct solution in the sine basis (constant coefficients, bura_direct.hip):
+  // its tables, the partials of |f|^2 and the systems' gates; off for a plan
+  // whose launch shapes or damping the caller has chosen (direct_allowed)
+  bool direct = false;
+  double* d_sine = nullptr;
+  double* d_fpart = nullptr;
+  int* d_gate = nullptr;
+  int run_nrhs = 0;            // right-hand sides of the solve in progress
   // continuous batching (bura::serve_*): the slots' right-hand sides, the
   // systems being initialised, and the host copy of each slot's terms
   double* d_fserve = nullptr;  // [nrhs_max][N]
@@ -589,6 +597,22 @@ LdsHierarchy<T> lds_view(const bura_plan_t P) {
 
 bool fused_ok(const bura_plan_t P);
 
+// Plans whose solves may start from the direct solution: constant
+// coefficients, and the smoother's damping left to the library (a caller who
+// sets it wants the multigrid iteration).  Largest grids: per system the
+// direct solution costs n^3 (2D) or 3 n^4 / 2 (3D) multiply-adds back and as
+// much forward once per right-hand side, against about 9 iterations of 60-115
+// bytes per point.
+constexpr int kDirectMaxN2 = 2047, kDirectMaxN3 = 1023;
+bool direct_allowed(const bura_plan_t P) {
+  return !P->var && !(P->opts.omega > 0.0) && P->n <= (P->dim == 2 ? kDirectMaxN2 : kDirectMaxN3);
+}
+
+size_t direct_bytes(const bura_plan_t P) {
+  const size_t rows = P->dim == 3 ? (size_t)P->n * P->n : (size_t)P->n;
+  return sine_table_doubles(P->n) * 8 + (size_t)P->opts.nrhs_max * ((rows + 31) / 32) * 8 + (size_t)P->S * 4;
+}
+
 // q = (A + s) p needs a buffer unless the kernel that takes the PCG residual
 // update forms it from p: the fused 2D down kernel, the 3D first fine sweep
 // (the PCG updates folded into the level kernels)
@@ -601,8 +625,15 @@ int alloc_work(bura_plan_t P, Work<T>& W) {
   int rc;
   if ((rc = dev_alloc(P, (void**)&W.x, vb))) return rc;
   if ((rc = dev_alloc(P, (void**)&W.r, vb))) return rc;
-  if ((rc = dev_alloc(P, (void**)&W.z, vb))) return rc;
-  if ((rc = dev_alloc(P, (void**)&W.zt, vb))) return rc;
+  if (sizeof(T) == 4 && direct_allowed(P)) {
+    // z and zt side by side: together an FP64 vector per system, the second
+    // buffer of the direct solution (which runs before either is used)
+    if ((rc = dev_alloc(P, (void**)&W.z, 2 * vb))) return rc;
+    W.zt = W.z + S * (size_t)P->N;
+  } else {
+    if ((rc = dev_alloc(P, (void**)&W.z, vb))) return rc;
+    if ((rc = dev_alloc(P, (void**)&W.zt, vb))) return rc;
+  }
   if ((rc = dev_alloc(P, (void**)&W.p, vb))) return rc;
   if ((rc = dev_alloc(P, (void**)&W.p2, vb))) return rc;
   if (q_stored(P) && (rc = dev_alloc(P, (void**)&W.q, vb))) return rc;
@@ -989,6 +1020,35 @@ bool combine_finishes_x(const bura_plan_t P) {
   return P->foldxr && P->opts.precision == BURA_FP64 && P->stages.empty();
 }
 
+// whether the solve in progress starts from the direct solution (slot plans
+// decide per right-hand side, on the device: launch_start)
+bool starts_direct(const bura_plan_t P) { return P->direct && (P->slots || P->run_tol <= kDirectTol); }
+
+// The direct solution of the active systems [sys0, sys0 + nsys) into x (0
+// where it does not apply), with ||f||^2 through op.  R: right-hand sides per
+// term in the system order.
+void direct_start(bura_plan_t P, int op, const double* f, int R, size_t sys0, int nsys, double* x, double* work) {
+  hipStream_t st = P->stream;
+  SineSolve s{};
+  s.dim = P->dim;
+  s.n = P->n;
+  s.nrhs = std::min(P->run_nrhs, R);
+  s.nsys = nsys;
+  s.stride = R;
+  s.f = f;
+  s.x = x;
+  s.work = work;
+  s.tab = P->d_sine;
+  s.wc = P->lev[0].wc;
+  s.shift = P->d_shift64 + sys0;
+  s.gate = P->d_gate + sys0;
+  ProfScope ps(P, BURA_K_DIRECT);
+  launch_sine_forward(s, st, ps.ctr, P->d_fpart);
+  launch_start(op, P->d_fpart, sine_norm_blocks(P->dim, P->n, s.nrhs), R, nsys, state_at(P, sys0), P->d_gate + sys0,
+               P->run_tol, st);
+  launch_sine_back(s, st, ps.ctr);
+}
+
 int solve_batch_fp64(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool preset) {
   hipStream_t st = P->stream;
   Work<double>& W = P->w64;
@@ -1000,6 +1060,27 @@ int solve_batch_fp64(bura_plan_t P, const double* f, int nrhs, size_t sys0, int 
   // no deferred iterate update pending on any system of the batch (slots that
   // stay inactive keep alpha = 0, so the final update skips them)
   launch_zero(S.alpha, (size_t)nsys * sizeof(double), st);
+  if (starts_direct(P)) {
+    direct_start(P, OP_INIT, f, nrhs, sys0, nsys, W.x + o, W.z + o);
+    {
+      ProfScope ps(P, BURA_K_RESIDUAL64);
+      launch_residual_fp64(P->dim, L0, f, W.x + o, W.r + o, P->d_shift64 + sys0, S.active, P->partial, nrhs, nsys, st,
+                           ps.ctr);
+    }
+    {
+      ProfScope ps(P, BURA_K_OTHER);
+      launch_scalars(OP_RESTART, P->partial, residual_blocks(P->dim, P->n, nsys), nsys, S, P->run_tol,
+                     P->opts.max_iter, st);
+    }
+    HIPCHK(hipGetLastError());
+    const int a = count_active(P, P->st.active, sys0, nsys);
+    if (a < 0) {
+      g_last_error = "device error in the direct solution";
+      return BURA_EDEVICE;
+    }
+    // systems over their tolerance iterate from there
+    return a == 0 ? BURA_OK : run_pcg<double>(P, W, sys0, nsys, P->run_tol, P->opts.max_iter, combine_finishes_x(P));
+  }
   {
     ProfScope ps(P, BURA_K_OTHER);
     Launch<double>::copy_rhs(L0, P->dim, f, W.r + o, W.x + o, nrhs, S.active, P->partial, nsys, st);
@@ -1078,6 +1159,22 @@ int solve_batch_mixed(bura_plan_t P, const double* f, int nrhs, size_t sys0, int
                           P->stream));
   }
   launch_zero(S.alpha, (size_t)nsys * sizeof(double), st);   // see solve_batch_fp64
+  if (starts_direct(P)) {
+    direct_start(P, OP_START, f, nrhs, sys0, nsys, P->x64 + o, (double*)W.z + o);
+    {
+      ProfScope ps(P, BURA_K_RESIDUAL64);
+      launch_residual64(P->dim, P->var, L0, f, P->x64 + o, W.x + o, W.r + o, P->d_shift64 + sys0, S.active64,
+                        P->partial, nrhs, nsys, false, st, ps.ctr);
+    }
+    {
+      ProfScope ps(P, BURA_K_OTHER);
+      SysState Ss = S;
+      Ss.started = 1;
+      launch_scalars(OP_OUTER, P->partial, residual_blocks(P->dim, P->n, nsys), nsys, Ss, P->run_tol,
+                     P->opts.max_outer, st);
+    }
+    return mixed_outer_loop(P, f, nrhs, sys0, nsys);
+  }
   // with the fused update and residual pass the first update assigns x64,
   // so the first residual need not clear it
   const bool x_zero = residual_marches_rows(P->dim, P->n, nsys);
@@ -1184,6 +1281,7 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
   if (!P || !f || !u || nrhs < 1 || nrhs > P->opts.nrhs_max) return BURA_EINVAL;
   if (!(tol >= 0.0) || !std::isfinite(tol)) return BURA_EINVAL;
   P->run_tol = tol > 0.0 ? tol : P->opts.tol;
+  P->run_nrhs = nrhs;
   if (P->slots != (slot != nullptr)) return BURA_EINVAL;
   if (slot && check_slot_terms(P, nrhs, *slot)) return BURA_EINVAL;
   HIPCHK(hipSetDevice(P->device));
@@ -1539,6 +1637,12 @@ int tune_tiles(bura_plan_t P) {
     }
   }
   hipStream_t st = P->stream;
+  struct NoDirect {   // the multigrid iteration is what is timed
+    bura_plan_t P;
+    bool was;
+    ~NoDirect() { P->direct = was; }
+  } no_direct{P, P->direct};
+  P->direct = false;
   // one right-hand side for every system (nrhs = 1 below): uniform in [-1, 1)
   // from a fixed 64-bit linear congruential sequence
   std::vector<double> hf((size_t)P->N);
@@ -1849,6 +1953,20 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
     if ((rc = dev_alloc(P, (void**)&P->st.tol_inner, S * 8))) return fail(rc);
     P->st.inner_floor = o.inner_tol;
   }
+  if (direct_allowed(P)) {
+    // the direct solution's tables; a plan that they would take over its
+    // budget or its static workspace runs without them
+    const bool fits = ws ? P->ws_used + direct_bytes(P) + 1024 <= ws_cap
+                         : o.hbm_budget == 0 || footprint(P, mixed ? 4 : 8, mixed) + direct_bytes(P) <= o.hbm_budget;
+    if (fits) {
+      const size_t rows = P->dim == 3 ? (size_t)P->n * P->n : (size_t)P->n;
+      P->direct = !dev_alloc(P, (void**)&P->d_sine, sine_table_doubles(P->n) * 8) &&
+                  !dev_alloc(P, (void**)&P->d_fpart, (size_t)o.nrhs_max * ((rows + 31) / 32) * 8) &&
+                  !dev_alloc(P, (void**)&P->d_gate, S * sizeof(int));
+      if (P->direct) launch_sine_tables(P->n, P->d_sine, P->stream);
+      (void)hipGetLastError();   // no memory for them: the plan iterates from zero
+    }
+  }
   const size_t state_mirror = S * (6 * 8 + 8 * 4) + S * 8 + (size_t)P->nout * o.nrhs_max * 8;
   if (ws) {
     // host mirrors in ordinary memory (8-byte aligned: the state comes first)
@@ -1860,7 +1978,7 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
       return fail(BURA_ENOMEM);
     if (hipHostMalloc(&P->h_state, state_mirror, hipHostMallocDefault) != hipSuccess) return fail(BURA_ENOMEM);
   }
-  if (o.autotune) {
+  if (o.autotune && !(P->direct && o.tol <= kDirectTol)) {
     if (hipStreamSynchronize(P->stream) != hipSuccess) return fail(BURA_EDEVICE);
     if ((rc = tune_tiles(P))) return fail(rc);
   }
@@ -2568,6 +2686,7 @@ int bura_plan_set_tiles(bura_plan_t plan, const int* v, int len) {
   HIPCHK(hipSetDevice(plan->device));
   HIPCHK(hipStreamSynchronize(plan->stream));
   destroy_graphs(plan);   // captured launches carry their grid shapes
+  plan->direct = false;   // the kernels these shapes belong to
   plan->tile_spmv = v[0];
   for (int l = 0; l < nf; ++l) {
     plan->tile_down[l] = v[1 + 2 * l];

@@ -81,9 +81,17 @@ struct SysState {
   // (halved for margin), but no smaller than inner_floor (opts.inner_tol)
   double* tol_inner = nullptr;
   double inner_floor = 0.0;
+  // the refinement's first test is on the residual of a starting iterate (the
+  // direct solution): ||f|| is known already (OP_START)
+  int started = 0;
 };
 
-enum ScalarOp { OP_INIT = 0, OP_ALPHA = 1, OP_RESID = 2, OP_BETA = 3, OP_OUTER = 4 };
+// OP_START, OP_RESTART: the solve starts from the direct solution (see
+// launch_start): ||f||^2 of a MIXED system; the residual of an FP64 system's
+// starting iterate (whose ||f||^2 goes through OP_INIT).
+enum ScalarOp {
+  OP_INIT = 0, OP_ALPHA = 1, OP_RESID = 2, OP_BETA = 3, OP_OUTER = 4, OP_START = 5, OP_RESTART = 6
+};
 
 // Scalar update folded into the kernel that produces the reduction: the last
 // block of each system (counted in cnt[sys]) sums the block partials in the
@@ -147,6 +155,48 @@ struct Launch {
   static void copy_rhs(const LevelDev<T>& L, int dim, const double* f, T* r, T* x, int nrhs,
                        const int* active, double* partial, int nsys, hipStream_t st);
 };
+
+// ---- direct solution in the sine basis (bura_direct.hip) -------------------
+// Constant coefficients: x_s = (A + shift_s)^-1 f_{s % stride} in FP64 for the
+// systems s < nsys whose gate is 1 (0: left alone, 2: x = 0), from the
+// right-hand sides f[r], r < nrhs.  x, work: [nsys][N], nsys >= nrhs.
+// launch_sine_forward transforms f (and writes the block partials of |f_r|^2,
+// sine_norm_blocks per right-hand side, when partial != nullptr); its result
+// stays in x / work for launch_sine_back.  tab: launch_sine_tables.
+struct SineSolve {
+  int dim, n, nrhs, nsys, stride;
+  const double* f;
+  double* x;
+  double* work;
+  const double* tab;
+  double wc;             // face weight of the scaled operator
+  const double* shift;
+  const int* gate;
+};
+size_t sine_table_doubles(int n);
+void launch_sine_tables(int n, double* tab, hipStream_t st);
+int sine_norm_blocks(int dim, int n, int nrhs);
+void launch_sine_forward(const SineSolve& s, hipStream_t st, unsigned long long* ctr, double* partial);
+void launch_sine_back(const SineSolve& s, hipStream_t st, unsigned long long* ctr);
+
+// The direct solution starts the solves whose tolerance is at most this.  A
+// looser one needs a few multigrid iterations only, and the FP32 ones of a
+// MIXED solve leave the error its caller asked for, not more work.
+constexpr double kDirectTol = 1e-6;
+
+// Start the systems of [0, nsys) (arrays indexed from the same first system):
+// sum the partials of |f|^2 of each system's right-hand side s % R, apply op
+// (OP_INIT or OP_START) and set its gate (see SineSolve): 1 where the direct
+// solution is wanted, 2 where x = 0 is (a zero or non-finite right-hand side,
+// or a tolerance over kDirectTol), 0 for a system that is not active.
+void launch_start(int op, const double* partial, int nblk, int R, int nsys, const SysState& S, int* gate, double tol,
+                  hipStream_t st);
+
+// r = f - (A + s) x of the active systems in FP64, partial = |r|^2 (constant
+// coefficients; residual_blocks partials per system)
+void launch_residual_fp64(int dim, const LevelDev<double>& L, const double* f, const double* x, double* r,
+                          const double* shift, const int* active, double* partial, int nrhs, int nsys, hipStream_t st,
+                          unsigned long long* ctr);
 
 // FP64-only steps of the refinement loop and the combine.
 void launch_residual64(int dim, bool var, const LevelDev<double>& L, const double* f, const double* x64, float* e,

@@ -2911,10 +2911,12 @@ __global__ __launch_bounds__(256) void k_copy_rhs(long long N, const double* __r
 // thread's own registers, every load issued before the arithmetic (a
 // one-point-per-thread launch reads each x value from the caches five times)
 constexpr int kRes2Rows = 4, kRes2Cols = 128;
-template <bool VAR>
+// RT: float for the refinement (r32, and e = 0), double for the residual of an
+// FP64 plan's starting iterate (e not written)
+template <bool VAR, typename RT = float>
 __global__ __launch_bounds__(kBlock) void k_residual64_2(LevelDev<double> L, const double* __restrict__ f,
                                                          const double* __restrict__ x64, float* __restrict__ e,
-                                                         float* __restrict__ r32, const double* __restrict__ shift,
+                                                         RT* __restrict__ r32, const double* __restrict__ shift,
                                                          const int* __restrict__ active64, int nrhs,
                                                          double* __restrict__ partial,
                                                          unsigned long long* __restrict__ ctr) {
@@ -2968,8 +2970,8 @@ __global__ __launch_bounds__(kBlock) void k_residual64_2(LevelDev<double> L, con
         }
         const double rv64 = fv[r] - ax;
         const long long g = off + (long long)j * n + i;
-        r32[g] = (float)rv64;
-        e[g] = 0.0f;
+        r32[g] = (RT)rv64;
+        if constexpr (sizeof(RT) == 4) e[g] = 0.0f;
         rr += rv64 * rv64;
       }
     }
@@ -2999,10 +3001,10 @@ struct XUpdate {
   const int* iters;
   int assign;           // x64 = e instead of x64 += e (x64 not read: the first update of a solve)
 };
-template <bool VAR, bool UPD>
+template <bool VAR, bool UPD, typename RT = float>
 __global__ __launch_bounds__(1024) void k_residual64_2r(LevelDev<double> L, const double* __restrict__ f,
                                                         double* __restrict__ x64, float* __restrict__ e,
-                                                        float* __restrict__ r32, const double* __restrict__ shift,
+                                                        RT* __restrict__ r32, const double* __restrict__ shift,
                                                         const int* __restrict__ active64, int nrhs,
                                                         double* __restrict__ partial,
                                                         unsigned long long* __restrict__ ctr, XUpdate xu) {
@@ -3024,7 +3026,8 @@ __global__ __launch_bounds__(1024) void k_residual64_2r(LevelDev<double> L, cons
   const unsigned cb = (unsigned)ic * 8u, rowb = (unsigned)n * 8u;
   const RowBuf<double> xsb(xs, L.N), fsb(fs, L.N);
   const RowBuf<double> w0b(VAR ? L.wf0 : xs, VAR ? (long long)(n + 1) * n : 1), w1b(VAR ? L.wf1 : xs, VAR ? (long long)(n + 1) * n : 1);
-  const RowBuf<float> rb32(r32 + off, L.N), eb(e + off, L.N);
+  const RowBuf<RT> rb32(r32 + off, L.N);
+  const RowBuf<float> eb(e + off, L.N);
   // the pending update of the inner solve (UPD)
   const int its = UPD && xu.pa ? xu.iters[sys] : 0;
   const float a = UPD && xu.pa ? (float)xu.alpha[sys] : 0.0f;
@@ -3091,9 +3094,9 @@ __global__ __launch_bounds__(1024) void k_residual64_2r(LevelDev<double> L, cons
     const double rv64 = rf[s] - ax;
     if (col_on) {
       const unsigned g = (unsigned)row * 4u, ib = (unsigned)i * 4u;
-      rb32.template st<false>((float)rv64, ib, g);
+      rb32.template st<false>((RT)rv64, ib * (unsigned)(sizeof(RT) / 4), g * (unsigned)(sizeof(RT) / 4));
       // UPD: the segment's first and last rows are left to k_update_seg_rows
-      if (!UPD || (j != j0 && j != j1 - 1)) {
+      if (sizeof(RT) == 4 && (!UPD || (j != j0 && j != j1 - 1))) {
         eb.template st<false>(0.0f, ib, g);
         if (UPD) xsb.template st<false>(c, 2u * ib, 2u * g);
       }
@@ -3140,10 +3143,10 @@ static inline bool residual_rows(int dim, int n, long long nsys) {
 }
 
 // k_residual64 in 3D, marching along z with kMarchRows rows per thread
-template <bool VAR>
+template <bool VAR, typename RT = float>
 __global__ __launch_bounds__(kBlock) void k_residual64_3(LevelDev<double> L, const double* __restrict__ f,
                                                          const double* __restrict__ x64, float* __restrict__ e,
-                                                         float* __restrict__ r32, const double* __restrict__ shift,
+                                                         RT* __restrict__ r32, const double* __restrict__ shift,
                                                          const int* __restrict__ active64, int nrhs,
                                                          double* __restrict__ partial,
                                                          unsigned long long* __restrict__ ctr) {
@@ -3192,8 +3195,8 @@ __global__ __launch_bounds__(kBlock) void k_residual64_3(LevelDev<double> L, con
                                                   w.ir ? xr[r] : 0.0, w.down(r, centre, hd), w.up(r, centre, hu),
                                                   below[r], above[r], s, nullptr);
         const double rv = fv[r] - ax;
-        r32[off + p] = (float)rv;
-        e[off + p] = 0.0f;
+        r32[off + p] = (RT)rv;
+        if constexpr (sizeof(RT) == 4) e[off + p] = 0.0f;
         rr += rv * rv;
       }
 #pragma unroll
@@ -3395,6 +3398,35 @@ __device__ void apply_op(int op, double tot, const SysState& S, int sys, double 
       }
       break;
     }
+    case OP_START: {  // tot = ||f||^2; the first OP_OUTER follows, on the direct solution's residual
+      S.alpha[sys] = 0.0;
+      if (!isfinite(tot)) {
+        S.flags[sys] |= 1;
+        S.relres64[sys] = tot;
+        S.active64[sys] = 0;
+        S.active[sys] = 0;
+        break;
+      }
+      S.fnorm2[sys] = tot;
+      if (!(tot > 0.0)) {
+        S.relres64[sys] = 0.0;
+        S.outer[sys] = 1;
+        S.active64[sys] = 0;
+        S.active[sys] = 0;
+      }
+      break;
+    }
+    case OP_RESTART: {  // tot = ||f - (A+s) x||^2 of the direct solution
+      const double rel = sqrt(tot / S.bnorm2[sys]);
+      S.relres[sys] = rel;
+      if (!isfinite(rel)) {
+        S.flags[sys] |= 1;
+        S.active[sys] = 0;
+      } else if (rel <= (S.tol_pcg ? S.tol_pcg[sys] : tol)) {
+        S.active[sys] = 0;
+      }
+      break;
+    }
     case OP_OUTER: {  // tot = ||f - (A+s) x64||^2 ; first call: x64 = 0 so tot = ||f||^2
       const int o = S.outer[sys];
       S.alpha[sys] = 0.0;   // the inner solve's deferred update has been applied (or is void)
@@ -3405,7 +3437,7 @@ __device__ void apply_op(int op, double tot, const SysState& S, int sys, double 
         S.active[sys] = 0;
         break;
       }
-      if (o == 0) S.fnorm2[sys] = tot;
+      if (o == 0 && !S.started) S.fnorm2[sys] = tot;
       const double fn = S.fnorm2[sys];
       const double rel = fn > 0.0 ? sqrt(tot / fn) : 0.0;
       S.relres64[sys] = rel;
@@ -3442,6 +3474,24 @@ __global__ __launch_bounds__(256) void k_scalars(int op, const double* __restric
   const double tot = block_sum(v);
   if (threadIdx.x != 0) return;
   apply_op(op, tot, S, sys, tol, max_iter);
+}
+
+// One block per system: see launch_start.
+__global__ __launch_bounds__(256) void k_start(int op, const double* __restrict__ partial, int nblk, int R,
+                                               SysState S, int* __restrict__ gate, double tol) {
+  const int sys = blockIdx.x;
+  const bool mixed = op == OP_START;
+  if (!(mixed ? S.active64 : S.active)[sys]) {
+    if (threadIdx.x == 0) gate[sys] = 0;
+    return;
+  }
+  double v = 0.0;
+  for (int b = threadIdx.x; b < nblk; b += blockDim.x) v += partial[(size_t)(sys % R) * nblk + b];
+  const double tot = block_sum(v);
+  if (threadIdx.x != 0) return;
+  apply_op(op, tot, S, sys, tol, 0);
+  const double* per = mixed ? S.tol_outer : S.tol_pcg;
+  gate[sys] = tot > 0.0 && isfinite(tot) && (per ? per[sys] : tol) <= kDirectTol ? 1 : 2;
 }
 
 // --------------------------------------------------------------------------
@@ -3913,6 +3963,30 @@ void launch_residual64(int dim, bool var, const LevelDev<double>& L, const doubl
       hipLaunchKernelGGL((k_residual64_2<false>), g2, b2, 0, st, L, f, x64, e, r32, shift, active64, nrhs, partial,
                          ctr);
   }
+}
+
+void launch_residual_fp64(int dim, const LevelDev<double>& L, const double* f, const double* x, double* r,
+                          const double* shift, const int* active, double* partial, int nrhs, int nsys, hipStream_t st,
+                          unsigned long long* ctr) {
+  float* no_e = nullptr;
+  if (dim == 3) {
+    hipLaunchKernelGGL((k_residual64_3<false, double>), stencil_grid(dim, L.n, nsys), stencil_block(dim, L.n), 0, st,
+                       L, f, x, no_e, r, shift, active, nrhs, partial, ctr);
+  } else if (residual_rows(dim, L.n, nsys)) {
+    const dim3 g = rows_grid((L.n + kRes2rRows - 1) / kRes2rRows, nsys), blk(rows_threads(L.n));
+    hipLaunchKernelGGL((k_residual64_2r<false, false, double>), g, blk, 0, st, L, f, const_cast<double*>(x), no_e, r,
+                       shift, active, nrhs, partial, ctr, XUpdate{});
+  } else {
+    constexpr int rows_per_block = (kBlock / kRes2Cols) * kRes2Rows;
+    const dim3 g2((L.n + kRes2Cols - 1) / kRes2Cols, (L.n + rows_per_block - 1) / rows_per_block, nsys);
+    hipLaunchKernelGGL((k_residual64_2<false, double>), g2, dim3(kRes2Cols, kBlock / kRes2Cols), 0, st, L, f, x, no_e,
+                       r, shift, active, nrhs, partial, ctr);
+  }
+}
+
+void launch_start(int op, const double* partial, int nblk, int R, int nsys, const SysState& S, int* gate, double tol,
+                  hipStream_t st) {
+  hipLaunchKernelGGL(k_start, dim3(nsys), dim3(256), 0, st, op, partial, nblk, R, S, gate, tol);
 }
 
 bool residual_marches_rows(int dim, int n, long long nsys) { return residual_rows(dim, n, nsys); }
