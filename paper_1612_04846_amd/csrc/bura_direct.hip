@@ -186,15 +186,18 @@ __global__ __launch_bounds__(kSineThreads) void k_sine(SinePass a) {
   // waves 2 x 2: ri D rows, rj D columns of this wave within the tile
   const int ri = (wave >> 1) * 16 * WT, rj = (wave & 1) * 16 * WT;
   const int nk = g == 1 ? (h1 + KC - 1) / KC : 0;
-  if (nk > 0) load(0);
+  // back, the sums start at the highest coefficients: a solution is dominated by
+  // its lowest ones, and each step rounds relative to the sum so far
+  auto at = [&](int t) { return (INV ? nk - 1 - t : t) * KC; };
+  if (nk > 0) load(at(0));
   for (int t = 0; t < nk; ++t) {
     if (t) __syncthreads();   // every read of the previous values is done
-    stage(t * KC);
+    stage(at(t));
     __syncthreads();
-    if (t + 1 < nk) load((t + 1) * KC);
+    if (t + 1 < nk) load(at(t + 1));
 #pragma unroll
     for (int s = 0; s < KC / 4; ++s) {
-      const int kr = 4 * s + lk;
+      const int kr = 4 * (INV ? KC / 4 - 1 - s : s) + lk;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         double av[WT], bv[WT];

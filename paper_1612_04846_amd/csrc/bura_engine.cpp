@@ -130,6 +130,7 @@ struct bura_plan_s {
   double* d_wsys = nullptr;
   double* d_tol = nullptr;
   void* h_slot = nullptr;
+  double* d_slot = nullptr;
   // device buffers
   Work<double> w64;
   Work<float> w32;
@@ -184,7 +185,7 @@ struct bura_plan_s {
   // squared norms of the outputs (device, and their host copy after the state)
   double lam_lb = 0.0;
   std::vector<double> w_applied;
-  double* d_upart = nullptr;   // rows x ceil(N/256) partial sums
+  double* d_upart = nullptr;   // rows x combine_blocks(N) partial sums
   double* d_unorm = nullptr;   // rows = nout x nrhs_max
   double* d_tol_err = nullptr; // MIXED: per-system refinement tolerances set by opts.err_tol
   // direct solution in the sine basis (constant coefficients, bura_direct.hip):
@@ -1007,11 +1008,6 @@ int run_pcg(bura_plan_t P, Work<T>& W, size_t sys0, int nsys, double tol, int ma
   return BURA_OK;
 }
 
-int set_flags(bura_plan_t P, int* dev, size_t sys0, int nsys, int value) {
-  launch_fill_int(dev + sys0, nsys, value, P->stream);
-  return BURA_OK;
-}
-
 // FP64 plans without stages leave each system's last deferred iterate update
 // to the combine, which reads x anyway (k_finish_x would read and write it
 // once more); a later stage of a sequential form reads x itself, so staged
@@ -1049,17 +1045,32 @@ void direct_start(bura_plan_t P, int op, const double* f, int R, size_t sys0, in
   launch_sine_back(s, st, ps.ctr);
 }
 
-int solve_batch_fp64(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool preset) {
+int mixed_outer_loop(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool x_zero = false);
+
+// The systems of a batch that the direct solution left over their tolerance
+// iterate from there.
+int finish_batch(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys) {
+  if (P->opts.precision == BURA_MIXED) return mixed_outer_loop(P, f, nrhs, sys0, nsys);
+  const int a = count_active(P, P->st.active, sys0, nsys);
+  if (a < 0) {
+    g_last_error = "device error in the direct solution";
+    return BURA_EDEVICE;
+  }
+  return a == 0 ? BURA_OK
+                : run_pcg<double>(P, P->w64, sys0, nsys, P->run_tol, P->opts.max_iter, combine_finishes_x(P));
+}
+
+// Both batch solvers find the state as launch_begin leaves it: the used
+// systems active, counters 0 and no iterate update pending (slots that stay
+// inactive keep alpha = 0, so the final update skips them).  With spec set a
+// batch that starts from the direct solution is queued without waiting for its
+// test; the caller looks at the active flags later (finish_batch).
+int solve_batch_fp64(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool spec) {
   hipStream_t st = P->stream;
   Work<double>& W = P->w64;
   const LevelDev<double> L0 = level_view<double>(P, 0);
   const size_t o = sys0 * (size_t)P->N;
   const SysState S = state_at(P, sys0);
-  int rc;
-  if (!preset && (rc = set_flags(P, P->st.active, sys0, nsys, 1))) return rc;
-  // no deferred iterate update pending on any system of the batch (slots that
-  // stay inactive keep alpha = 0, so the final update skips them)
-  launch_zero(S.alpha, (size_t)nsys * sizeof(double), st);
   if (starts_direct(P)) {
     direct_start(P, OP_INIT, f, nrhs, sys0, nsys, W.x + o, W.z + o);
     {
@@ -1073,13 +1084,7 @@ int solve_batch_fp64(bura_plan_t P, const double* f, int nrhs, size_t sys0, int 
                      P->opts.max_iter, st);
     }
     HIPCHK(hipGetLastError());
-    const int a = count_active(P, P->st.active, sys0, nsys);
-    if (a < 0) {
-      g_last_error = "device error in the direct solution";
-      return BURA_EDEVICE;
-    }
-    // systems over their tolerance iterate from there
-    return a == 0 ? BURA_OK : run_pcg<double>(P, W, sys0, nsys, P->run_tol, P->opts.max_iter, combine_finishes_x(P));
+    return spec ? BURA_OK : finish_batch(P, f, nrhs, sys0, nsys);
   }
   {
     ProfScope ps(P, BURA_K_OTHER);
@@ -1097,7 +1102,7 @@ int solve_batch_fp64(bura_plan_t P, const double* f, int nrhs, size_t sys0, int 
 // x64 += e, the FP64 residual and the outer test, until no system is active.
 // x_zero: x64 was not cleared (k_first_residual with zero_x false) and the
 // first update assigns it (the fused update and residual pass only)
-int mixed_outer_loop(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool x_zero = false) {
+int mixed_outer_loop(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool x_zero) {
   hipStream_t st = P->stream;
   Work<float>& W = P->w32;
   const LevelDev<double> L0 = level_view<double>(P, 0);
@@ -1143,22 +1148,12 @@ int mixed_outer_loop(bura_plan_t P, const double* f, int nrhs, size_t sys0, int 
   return BURA_OK;
 }
 
-int solve_batch_mixed(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool preset) {
+int solve_batch_mixed(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool spec) {
   hipStream_t st = P->stream;
   Work<float>& W = P->w32;
   const LevelDev<double> L0 = level_view<double>(P, 0);
   const size_t o = sys0 * (size_t)P->N;
   const SysState S = state_at(P, sys0);
-  int rc;
-  if (!preset) {
-    if ((rc = set_flags(P, P->st.active64, sys0, nsys, 1))) return rc;
-    if ((rc = set_flags(P, P->st.active, sys0, nsys, 1))) return rc;
-  } else {
-    // inner flags follow the outer ones (OP_OUTER re-arms them per system)
-    HIPCHK(hipMemcpyAsync(P->st.active + sys0, P->st.active64 + sys0, nsys * sizeof(int), hipMemcpyDeviceToDevice,
-                          P->stream));
-  }
-  launch_zero(S.alpha, (size_t)nsys * sizeof(double), st);   // see solve_batch_fp64
   if (starts_direct(P)) {
     direct_start(P, OP_START, f, nrhs, sys0, nsys, P->x64 + o, (double*)W.z + o);
     {
@@ -1173,7 +1168,8 @@ int solve_batch_mixed(bura_plan_t P, const double* f, int nrhs, size_t sys0, int
       launch_scalars(OP_OUTER, P->partial, residual_blocks(P->dim, P->n, nsys), nsys, Ss, P->run_tol,
                      P->opts.max_outer, st);
     }
-    return mixed_outer_loop(P, f, nrhs, sys0, nsys);
+    HIPCHK(hipGetLastError());
+    return spec ? BURA_OK : finish_batch(P, f, nrhs, sys0, nsys);
   }
   // with the fused update and residual pass the first update assigns x64,
   // so the first residual need not clear it
@@ -1239,12 +1235,14 @@ int check_slot_terms(const bura_plan_t P, int nrhs, const SlotTerms& t) {
   return BURA_OK;
 }
 
+size_t slot_bytes(const bura_plan_t P) { return (size_t)P->S * (3 * 8 + 4 + 4); }
+
 // Upload one solve's per-system weights, shifts, tolerances and active flags
-// (system j * R + r is used iff r < nrhs and j < nterms[r]).
+// (system j * R + r is used iff r < nrhs and j < nterms[r]) to the staging
+// area that launch_begin unpacks.
 int upload_slots(bura_plan_t P, int nrhs, const SlotTerms& t) {
   const int K = P->nterms, R = P->opts.nrhs_max;
   const size_t S = (size_t)P->S;
-  const bool mixed = P->opts.precision == BURA_MIXED;
   double* hw = (double*)P->h_slot;
   double* hs = hw + S;
   double* ht = hs + S;
@@ -1261,17 +1259,7 @@ int upload_slots(bura_plan_t P, int nrhs, const SlotTerms& t) {
       hf[i] = used ? 1 : 0;
     }
   }
-  hipStream_t st = P->stream;
-  HIPCHK(hipMemcpyAsync(P->d_wsys, hw, S * 8, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(P->d_shift64, hs, S * 8, hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemcpyAsync(P->d_tol, ht, S * 8, hipMemcpyHostToDevice, st));
-  if (mixed) {
-    HIPCHK(hipMemcpyAsync(P->w32.shift, hs32, S * 4, hipMemcpyHostToDevice, st));
-    HIPCHK(hipMemcpyAsync(P->st.active64, hf, S * 4, hipMemcpyHostToDevice, st));
-  } else {
-    HIPCHK(hipMemcpyAsync(P->w64.shift, hs, S * 8, hipMemcpyHostToDevice, st));
-  }
-  HIPCHK(hipMemcpyAsync(P->st.active, hf, S * 4, hipMemcpyHostToDevice, st));
+  HIPCHK(hipMemcpyAsync(P->d_slot, P->h_slot, slot_bytes(P), hipMemcpyHostToDevice, P->stream));
   return BURA_OK;
 }
 
@@ -1296,58 +1284,69 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
     HIPCHK(hipEventRecord(P->join_ev, P->user_stream));
     HIPCHK(hipStreamWaitEvent(P->stream, P->join_ev, 0));
   }
-  if ((rc = set_flags(P, P->st.flags, 0, (int)S_used, 0))) return rc;
-  if ((rc = set_flags(P, P->st.total_iters, 0, (int)S_used, 0))) return rc;
-  if ((rc = set_flags(P, P->st.outer, 0, (int)S_used, 0))) return rc;
-  auto batch_rhs = [&](const double* rhs, size_t sys0, int nsys, bool preset) {
-    // the kernels take rhs = sys % R; pass rhs with R slots (rhs >= nrhs never active)
-    return mixed ? solve_batch_mixed(P, rhs, R, sys0, nsys, preset)
-                 : solve_batch_fp64(P, rhs, R, sys0, nsys, preset);
+  // the scalar state and the used systems, with a slot solve's terms
+  auto begin = [&]() {
+    SlotUpload up{};
+    if (slot) {
+      up.staged = P->d_slot;
+      up.w = P->d_wsys;
+      up.s64 = P->d_shift64;
+      up.s64b = mixed ? nullptr : P->w64.shift;
+      up.s32 = mixed ? P->w32.shift : nullptr;
+      up.tol = P->d_tol;
+    }
+    launch_begin(P->st, (int)S_used, R, nrhs, up, P->stream);
   };
-  auto batch = [&](size_t sys0, int nsys, bool preset) { return batch_rhs(f, sys0, nsys, preset); };
-  const double* xsol = mixed ? P->x64 : P->w64.x;
-  if (slot) {
-    // every rhs with its own terms, all in one batch; unused slots inactive
-    if ((rc = upload_slots(P, nrhs, *slot))) return rc;
-    rc = batch(0, (int)S_used, true);
-  } else if (!P->stages.empty()) {
-    // sequential form: each stage solves its terms against its input, then
-    // combines into the stage buffer (or u for the last stage)
-    rc = BURA_OK;
-    for (size_t si = 0; si < P->stages.size() && rc == BURA_OK; ++si) {
-      const Stage& g = P->stages[si];
-      const bool last = si + 1 == P->stages.size();
-      const double* in = g.input == Stage::F ? f
-                         : g.input == Stage::PREV ? P->d_buf
-                                                  : xsol + (size_t)g.sol_term * R * P->N;
-      const size_t sys0 = (size_t)g.tb * R;
-      const int nt = g.te - g.tb;
-      if (nrhs == R) {
-        rc = batch_rhs(in, sys0, nt * R, false);
-      } else {
-        launch_slot_flags(P->st.active + sys0, nt, R, nrhs, P->stream);
-        if (mixed) launch_slot_flags(P->st.active64 + sys0, nt, R, nrhs, P->stream);
-        rc = batch_rhs(in, sys0, nt * R, true);
-      }
-      if (rc) break;
-      ProfScope ps(P, BURA_K_COMBINE);
-      launch_combine(P->N, xsol + sys0 * P->N, P->d_w + g.tb, nt, nrhs, R, last ? u : P->d_buf, P->stream, ps.ctr,
-                     g.base ? P->d_buf : nullptr, g.base_w);
-    }
-  } else if (P->opts.schedule == BURA_PER_POLE) {
-    if (nrhs < R) {
-      if ((rc = set_flags(P, P->st.active, 0, (int)S_used, 0))) return rc;
-      if ((rc = set_flags(P, P->st.active64, 0, (int)S_used, 0))) return rc;
-    }
-    for (int j = 0; j < P->nterms && rc == BURA_OK; ++j) rc = batch((size_t)j * R, nrhs, false);
-  } else if (nrhs == R) {
-    rc = batch(0, (int)S_used, false);
-  } else {
-    // fewer rhs than slots: one batch over all systems, unused slots inactive
-    launch_slot_flags(P->st.active, P->nterms, R, nrhs, P->stream);
-    if (mixed) launch_slot_flags(P->st.active64, P->nterms, R, nrhs, P->stream);
-    rc = batch(0, (int)S_used, true);
+  if (slot && (rc = upload_slots(P, nrhs, *slot))) return rc;
+  begin();
+  // A solve that the direct solution starts is queued to its end without
+  // waiting for the residual test, whose flags come back with the report; the
+  // systems still active then iterate and the combine runs again.  The stages
+  // of a sequential form read earlier ones, so there the whole solve runs
+  // again with a wait per stage: it is queued in one go only where the direct
+  // solution is sure to pass, its residual being rounding, at most about
+  // 3e-16 / (lambda_min + s) of |f|.
+  bool spec = starts_direct(P);
+  if (spec && !P->stages.empty()) {
+    double smin = HUGE_VAL;
+    for (double v : P->s) smin = std::min(smin, v);
+    spec = 3e-16 / (P->lam_lb + smin) <= P->run_tol;
   }
+  auto batch = [&](const double* rhs, size_t sys0, int nsys) {
+    // the kernels take rhs = sys % R; pass rhs with R slots (rhs >= nrhs never active)
+    return mixed ? solve_batch_mixed(P, rhs, R, sys0, nsys, spec) : solve_batch_fp64(P, rhs, R, sys0, nsys, spec);
+  };
+  const double* xsol = mixed ? P->x64 : P->w64.x;
+  auto solve_all = [&]() -> int {
+    int rc = BURA_OK;
+    if (!P->stages.empty()) {
+      // sequential form: each stage solves its terms against its input, then
+      // combines into the stage buffer (or u for the last stage)
+      for (size_t si = 0; si < P->stages.size() && rc == BURA_OK; ++si) {
+        const Stage& g = P->stages[si];
+        const bool last = si + 1 == P->stages.size();
+        const double* in = g.input == Stage::F ? f
+                           : g.input == Stage::PREV ? P->d_buf
+                                                    : xsol + (size_t)g.sol_term * R * P->N;
+        const size_t sys0 = (size_t)g.tb * R;
+        const int nt = g.te - g.tb;
+        if ((rc = batch(in, sys0, nt * R))) break;
+        ProfScope ps(P, BURA_K_COMBINE);
+        CombineTerms ct{};
+        ct.begin[1] = nt;
+        launch_combine(P->N, xsol + sys0 * P->N, P->d_w + g.tb, ct, 1, nrhs, R, last ? u : P->d_buf, P->stream, ps.ctr,
+                       g.base ? P->d_buf : nullptr, g.base_w);
+      }
+    } else if (P->opts.schedule == BURA_PER_POLE) {
+      for (int j = 0; j < P->nterms && rc == BURA_OK; ++j) rc = batch(f, (size_t)j * R, nrhs);
+    } else {
+      // every system in one batch (slot solves: every rhs with its own terms);
+      // unused slots stay inactive
+      rc = batch(f, 0, (int)S_used);
+    }
+    return rc;
+  };
+  rc = solve_all();
   if (rc) return rc;
   const size_t S = (size_t)P->S;
   const size_t sb = S * (6 * 8 + 8 * 4);
@@ -1358,30 +1357,22 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
   // squared norm of every output row
   auto combine = [&]() -> int {
     const bool pend = combine_finishes_x(P);
-    if (slot) {
+    if (P->stages.empty()) {
       ProfScope ps(P, BURA_K_COMBINE);
-      launch_combine(P->N, xsol, P->d_wsys, P->nterms, nrhs, R, u, P->stream, ps.ctr, nullptr, 0.0, true,
-                     pend ? P->w64.p : nullptr, pend ? P->w64.p2 : nullptr, P->st.alpha, P->st.iters);
+      CombineTerms ct{};
+      for (int i = 0; i < P->nout; ++i) ct.begin[i + 1] = P->out_end[i];
+      launch_combine(P->N, xsol, slot ? P->d_wsys : P->d_w, ct, P->nout, nrhs, R, u, P->stream, ps.ctr, nullptr, 0.0,
+                     slot != nullptr, pend ? P->w64.p : nullptr, pend ? P->w64.p2 : nullptr, P->st.alpha, P->st.iters,
+                     P->d_upart, P->d_unorm);
     }
-    for (int i = 0; i < P->nout && P->stages.empty() && !slot; ++i) {
-      ProfScope ps(P, BURA_K_COMBINE);
-      const int b = P->out_begin[i], e = P->out_end[i];
-      const size_t ob = (size_t)b * R;   // first system of output i
-      launch_combine(P->N, xsol + ob * P->N, P->d_w + b, e - b, nrhs, R, u + (size_t)i * nrhs * P->N, P->stream,
-                     ps.ctr, nullptr, 0.0, false, pend ? P->w64.p + ob * P->N : nullptr,
-                     pend ? P->w64.p2 + ob * P->N : nullptr, P->st.alpha + ob, P->st.iters + ob);
-    }
-    if (rows > 0) launch_row_norms(u, P->N, rows, P->d_upart, P->d_unorm, P->stream);
     HIPCHK(hipGetLastError());
     return BURA_OK;
   };
-  // report: one copy of the per-system scalar state (and the output norms)
+  // report: one copy of the per-system scalar state, the refinement's residuals
+  // and the output norms (one block on the device too)
   auto fetch = [&]() -> int {
-    HIPCHK(hipMemcpyAsync(P->h_state, P->state_block, sb, hipMemcpyDeviceToHost, P->stream));
-    HIPCHK(hipMemcpyAsync((char*)P->h_state + sb, P->st.relres64, S * 8, hipMemcpyDeviceToHost, P->stream));
-    if (rows > 0)
-      HIPCHK(hipMemcpyAsync((char*)P->h_state + sb + S * 8, P->d_unorm, (size_t)rows * 8, hipMemcpyDeviceToHost,
-                            P->stream));
+    HIPCHK(hipMemcpyAsync(P->h_state, P->state_block, sb + S * 8 + (size_t)rows * 8, hipMemcpyDeviceToHost,
+                          P->stream));
     HIPCHK(hipStreamSynchronize(P->stream));
     prof_flush(P);
     return BURA_OK;
@@ -1432,6 +1423,25 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
     return mx;
   };
   if ((rc = combine()) || (rc = fetch())) return rc;
+  if (spec) {
+    const int* act = (const int*)(hd + 6 * S) + (mixed ? 4 * S : 0);
+    auto any = [&](size_t sys0, size_t nsys) {
+      return std::any_of(act + sys0, act + sys0 + nsys, [](int v) { return v != 0; });
+    };
+    if (any(0, S_used)) {
+      spec = false;
+      if (!P->stages.empty()) {
+        begin();
+        rc = solve_all();
+      } else if (P->opts.schedule == BURA_PER_POLE) {
+        for (int j = 0; j < P->nterms && rc == BURA_OK; ++j)
+          if (any((size_t)j * R, nrhs)) rc = finish_batch(P, f, R, (size_t)j * R, nrhs);
+      } else {
+        rc = finish_batch(P, f, R, 0, (int)S_used);
+      }
+      if (rc || (rc = combine()) || (rc = fetch())) return rc;
+    }
+  }
   double eb = rows > 0 ? bound(nullptr) : -1.0;
   const double etol = P->opts.err_tol;
   if (mixed && etol > 0.0 && rows > 0) {
@@ -1685,9 +1695,7 @@ int tune_tiles(bura_plan_t P) {
   auto timed = [&]() {
     float ms = 0.0f;
     // the per-solve counters a solve starts from (as in do_solve)
-    set_flags(P, P->st.flags, 0, P->S, 0);
-    set_flags(P, P->st.total_iters, 0, P->S, 0);
-    set_flags(P, P->st.outer, 0, P->S, 0);
+    launch_begin(P->st, P->S, 1, 1, SlotUpload{}, st);
     ok = ok && hipEventRecord(e0, st) == hipSuccess;
     const int rc = ok ? solve_once() : BURA_EDEVICE;
     ok = ok && rc == BURA_OK && hipEventRecord(e1, st) == hipSuccess && hipEventSynchronize(e1) == hipSuccess &&
@@ -1922,7 +1930,9 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
     return fail(BURA_EDEVICE);
   // state arrays: 6 double + 7 int arrays of length S
   const size_t S = (size_t)P->S;
-  const size_t bytes = S * (6 * 8 + 8 * 4);
+  // then the refinement's residuals and the output norms (rows = outputs x rhs)
+  const size_t unorm_rows = (size_t)P->nout * o.nrhs_max;
+  const size_t bytes = S * (6 * 8 + 8 * 4) + S * 8 + unorm_rows * 8;
   if ((rc = dev_alloc(P, &P->state_block, bytes))) return fail(rc);
   if ((rc = dev_zero(P, P->state_block, bytes))) return fail(rc);
   double* dp = (double*)P->state_block;
@@ -1932,19 +1942,15 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
   int* ip = (int*)(dp + 6 * S);
   P->st.active = ip; P->st.iters = ip + S; P->st.total_iters = ip + 2 * S; P->st.flags = ip + 3 * S;
   P->st.active64 = ip + 4 * S; P->st.outer = ip + 5 * S;
-  // relres64 needs doubles: carve from a separate allocation
-  if ((rc = dev_alloc(P, (void**)&P->st.relres64, S * 8))) return fail(rc);
-  if ((rc = dev_zero(P, P->st.relres64, S * 8))) return fail(rc);
+  P->st.relres64 = (double*)((char*)P->state_block + S * (6 * 8 + 8 * 4));
+  P->d_unorm = P->st.relres64 + S;
   if ((rc = dev_alloc(P, (void**)&P->d_cnt, S * sizeof(unsigned int)))) return fail(rc);
   if ((rc = dev_zero(P, P->d_cnt, S * sizeof(unsigned int)))) return fail(rc);
   if ((rc = dev_alloc(P, (void**)&P->prof.d_ctr, BURA_K_COUNT * sizeof(unsigned long long)))) return fail(rc);
   if ((rc = dev_zero(P, P->prof.d_ctr, BURA_K_COUNT * sizeof(unsigned long long)))) return fail(rc);
-  // output norms for the error bound (rows = outputs x rhs)
   {
-    const size_t rows = (size_t)P->nout * o.nrhs_max;
-    const size_t nb = (size_t)((P->N + 255) / 256);
-    if ((rc = dev_alloc(P, (void**)&P->d_upart, rows * nb * 8))) return fail(rc);
-    if ((rc = dev_alloc(P, (void**)&P->d_unorm, rows * 8))) return fail(rc);
+    const size_t nb = (size_t)combine_blocks(P->N);
+    if ((rc = dev_alloc(P, (void**)&P->d_upart, unorm_rows * nb * 8))) return fail(rc);
     if (mixed && (rc = dev_alloc(P, (void**)&P->d_tol_err, S * 8))) return fail(rc);
   }
   if (mixed) {
@@ -2108,14 +2114,13 @@ int serve_slot_done(bura_plan_t P, int slot, double* u_dev, bura_report_t* rep) 
   const size_t S = (size_t)P->S;
   {
     ProfScope ps(P, BURA_K_COMBINE);
-    launch_combine(P->N, P->x64 + (size_t)slot * P->N, P->d_wsys + slot, K, 1, R, u_dev, st, ps.ctr, nullptr, 0.0,
-                   true);
+    CombineTerms ct{};
+    ct.begin[1] = K;
+    launch_combine(P->N, P->x64 + (size_t)slot * P->N, P->d_wsys + slot, ct, 1, 1, R, u_dev, st, ps.ctr, nullptr, 0.0,
+                   true, nullptr, nullptr, nullptr, nullptr, P->d_upart, P->d_unorm);
   }
-  launch_row_norms(u_dev, P->N, 1, P->d_upart, P->d_unorm, st);
   const size_t sb = S * (6 * 8 + 8 * 4);
-  HIPCHK(hipMemcpyAsync(P->h_state, P->state_block, sb, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync((char*)P->h_state + sb, P->st.relres64, S * 8, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipMemcpyAsync((char*)P->h_state + sb + S * 8, P->d_unorm, 8, hipMemcpyDeviceToHost, st));
+  HIPCHK(hipMemcpyAsync(P->h_state, P->state_block, sb + S * 8 + 8, hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
   const double* hd = (const double*)P->h_state;
   const int* hi = (const int*)(hd + 6 * S);
@@ -2314,11 +2319,12 @@ int bura_plan_create_slots(const bura_grid_t* grid, int max_terms, const bura_op
   int rc = create(grid, t, opts, &P);
   if (rc) return rc;
   const size_t S = (size_t)P->S;
-  if ((rc = dev_alloc(P, (void**)&P->d_wsys, S * 8)) || (rc = dev_alloc(P, (void**)&P->d_tol, S * 8))) {
+  if ((rc = dev_alloc(P, (void**)&P->d_wsys, S * 8)) || (rc = dev_alloc(P, (void**)&P->d_tol, S * 8)) ||
+      (rc = dev_alloc(P, (void**)&P->d_slot, slot_bytes(P)))) {
     bura_plan_destroy(P);
     return rc;
   }
-  if (hipHostMalloc(&P->h_slot, S * (3 * 8 + 4 + 4), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc(&P->h_slot, slot_bytes(P), hipHostMallocDefault) != hipSuccess) {
     bura_plan_destroy(P);
     return BURA_ENOMEM;
   }

@@ -217,18 +217,24 @@ bool launch_update_residual64(int dim, bool var, const LevelDev<double>& L, cons
 void launch_x_from_e(const LevelDev<double>& L, int dim, const float* e, double* x64, const int* active64,
                      int nsys, hipStream_t st, const float* pa = nullptr, const float* pb = nullptr,
                      const double* alpha = nullptr, const int* iters = nullptr);
-// u_r = base_w base_r + sum_j w_j x_{j stride + r}; with w_per_system the weight
-// of term j of rhs r is w[j stride + r] and zero weights skip their term.
+// Output o < nout of right-hand side r < nrhs: u[o nrhs + r] = base_w base_r +
+// sum over j in [begin[o], begin[o + 1]) of w_j x_{j stride + r}; with
+// w_per_system the weight of term j of rhs r is w[j stride + r] and zero
+// weights skip their term.
 // With pa != nullptr system s = j stride + r still has its last deferred
 // update pending (alpha[s], p = pa or pb by the parity of iters[s]; arrays
 // indexed from the same first system as x), applied to x_s as it is read.
-void launch_combine(long long N, const double* x, const double* w, int nterms, int nrhs, int stride, double* u,
-                    hipStream_t st, unsigned long long* ctr, const double* base = nullptr, double base_w = 0.0,
-                    bool w_per_system = false, const double* pa = nullptr, const double* pb = nullptr,
-                    const double* alpha = nullptr, const int* iters = nullptr);
-// out[r] = ||u_r||_2^2 for rows r < rows of [rows][N] (partial: rows x
-// ceil(N/256) doubles of scratch); fixed summation order per row
-void launch_row_norms(const double* u, long long N, int rows, double* partial, double* out, hipStream_t st);
+// With partial != nullptr (combine_blocks doubles per output row of scratch)
+// norms[o nrhs + r] = |u|^2, in a fixed summation order per row.
+struct CombineTerms {
+  int begin[BURA_MAX_TERMS + 1];
+};
+int combine_blocks(long long N);
+void launch_combine(long long N, const double* x, const double* w, const CombineTerms& t, int nout, int nrhs,
+                    int stride, double* u, hipStream_t st, unsigned long long* ctr, const double* base = nullptr,
+                    double base_w = 0.0, bool w_per_system = false, const double* pa = nullptr,
+                    const double* pb = nullptr, const double* alpha = nullptr, const int* iters = nullptr,
+                    double* partial = nullptr, double* norms = nullptr);
 void launch_apply64(int dim, bool var, const LevelDev<double>& L, const double* x, double* y, double shift,
                     int nvec, hipStream_t st);
 void launch_scalars(int op, const double* partial, int nblk, int nsys, SysState st_, double tol,
@@ -246,7 +252,19 @@ void launch_merge_init(int* init, int* active64, int n, hipStream_t st);
 // dst = src, 16-byte aligned, non-overlapping (counter calibration)
 void launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
 void launch_fill_int(int* p, long long n, int v, hipStream_t st);
-void launch_slot_flags(int* p, int nterms, int R, int nrhs, hipStream_t st);
+// The state at the start of a solve: flags and counters 0, no deferred update
+// pending, the used systems active (system j R + r for r < nrhs).  A slot
+// solve's terms come in one upload, staged = [S] weights, shifts, tolerances
+// (double), shifts (float), used flags (int), and go to their arrays here.
+struct SlotUpload {
+  const double* staged = nullptr;
+  double* w = nullptr;
+  double* s64 = nullptr;
+  double* s64b = nullptr;   // FP64 plans: the PCG's copy of the shifts
+  float* s32 = nullptr;     // MIXED
+  double* tol = nullptr;
+};
+void launch_begin(const SysState& S, int nsys, int R, int nrhs, const SlotUpload& up, hipStream_t st);
 
 int stencil_blocks(int dim, int n);   // blocks per system of a stencil launch (tile grid)
 int flat_blocks(long long N);        // blocks per system of an element-wise launch

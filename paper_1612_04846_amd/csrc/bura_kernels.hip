@@ -3274,52 +3274,74 @@ __global__ __launch_bounds__(256) void k_x_from_e(long long N, const float* __re
   }
 }
 
-// u[r] = base_w base[r] + sum_j w_j x[j * stride + r], summed in the fixed order
-// base, j = 0..nterms-1 (eq. (16); the base term serves the sequential forms).
-// base may be u itself (each element is read before it is written).
+// Output o (blockIdx.z), right-hand side r (blockIdx.y):
+// u[o rows + r] = base_w base[r] + sum_j w_j x[j * stride + r] over the output's
+// terms, summed in the fixed order base, j = begin..end-1 (eq. (16); the base
+// term serves the sequential forms).  base may be u itself (each element is
+// read before it is written).
 // With pa != nullptr each system's last deferred iterate update is still
 // pending and is applied here, as k_finish_x would (same expression), while x
 // is read: x_j + alpha_j p_j, never stored (p = pa or pb by the parity of the
 // system's iteration count).
+// With partial != nullptr the block's sum of u^2 goes there (k_row_sum adds
+// them: the output norms of the error bound, without reading u again).
+// kCombineItems points per thread, every load of a term in flight before the
+// sums (1023^2, 10 terms: one point per thread moved 4.2 TB/s).
+constexpr int kCombineItems = 4;
 __global__ __launch_bounds__(256) void k_combine(long long N, const double* x, const double* __restrict__ w,
-                                                 int nterms, int stride, double* u, const double* base,
+                                                 CombineTerms t, int stride, double* u, const double* base,
                                                  double base_w, unsigned long long* __restrict__ ctr, int wsys,
                                                  const double* __restrict__ pa, const double* __restrict__ pb,
-                                                 const double* __restrict__ alpha, const int* __restrict__ iters) {
-  const int r = blockIdx.y;
-  const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
-  count_bytes<COUNT_FLAT>(ctr, (unsigned long long)N * 8ULL * (nterms * (pa ? 2 : 1) + 1 + (base ? 1 : 0)));
-  if (p >= N) return;
-  double acc = base ? base_w * base[(long long)r * N + p] : 0.0;
-  for (int j = 0; j < nterms; ++j) {
+                                                 const double* __restrict__ alpha, const int* __restrict__ iters,
+                                                 double* __restrict__ partial) {
+  constexpr int K = kCombineItems;
+  const int r = blockIdx.y, o = blockIdx.z;
+  const int jb = t.begin[o], je = t.begin[o + 1];
+  const int row = o * gridDim.y + r;
+  const long long p0 = (long long)blockIdx.x * 256 * K + threadIdx.x;
+  count_bytes<COUNT_FLAT>(ctr, (unsigned long long)N * 8ULL * ((je - jb) * (pa ? 2 : 1) + 1 + (base ? 1 : 0)));
+  long long pt[K];
+  double acc[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    pt[i] = min(p0 + 256 * i, N - 1);
+    acc[i] = base ? base_w * base[(long long)r * N + pt[i]] : 0.0;
+  }
+#pragma unroll 2
+  for (int j = jb; j < je; ++j) {
     const long long sys = (long long)j * stride + r;
     const double wv = wsys ? w[sys] : w[j];
     // per-system weights: a zero weight marks an unused slot, whose x is not read
     if (wsys && wv == 0.0) continue;
-    double xv = x[sys * N + p];
+    double xv[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) xv[i] = x[sys * N + pt[i]];
     if (pa) {
       const int it = iters[sys];
       const double a = alpha[sys];
-      if (it > 0 && a != 0.0) xv = xv + a * (((it - 1) & 1) ? pa : pb)[sys * N + p];
+      if (it > 0 && a != 0.0) {
+        const double* pl = (((it - 1) & 1) ? pa : pb) + sys * N;
+#pragma unroll
+        for (int i = 0; i < K; ++i) xv[i] = xv[i] + a * pl[pt[i]];
+      }
     }
-    acc += wv * xv;
+#pragma unroll
+    for (int i = 0; i < K; ++i) acc[i] += wv * xv[i];
   }
-  u[(long long)r * N + p] = acc;
+  double uu = 0.0;
+#pragma unroll
+  for (int i = 0; i < K; ++i)
+    if (p0 + 256 * i < N) {
+      u[(long long)row * N + pt[i]] = acc[i];
+      uu += acc[i] * acc[i];
+    }
+  if (partial) write_partial(partial, row, uu, blockIdx.x, gridDim.x);
 }
 
-// Squared l2 norm of each row of u ([rows][N], FP64): per-block partials, then
-// one block per row sums them in a fixed order (the result does not depend on
-// which other rows share the launch).
-__global__ __launch_bounds__(256) void k_row_norm2(const double* __restrict__ u, long long N,
-                                                   double* __restrict__ partial) {
-  const int r = blockIdx.y;
-  const long long p = (long long)blockIdx.x * 256 + threadIdx.x;
-  const double v = p < N ? u[(long long)r * N + p] : 0.0;
-  write_partial(partial, r, v * v, blockIdx.x, gridDim.x);
-}
-
-__global__ __launch_bounds__(256) void k_row_sum(const double* __restrict__ partial, int nblk,
-                                                 double* __restrict__ out) {
+// out[r] = the sum of the nblk partials of row r, in a fixed order (the result
+// does not depend on which other rows share the launch)
+__global__ __launch_bounds__(1024) void k_row_sum(const double* __restrict__ partial, int nblk,
+                                                  double* __restrict__ out) {
   const int r = blockIdx.x;
   double v = 0.0;
   for (int b = threadIdx.x; b < nblk; b += blockDim.x) v += partial[(size_t)r * nblk + b];
@@ -4023,19 +4045,18 @@ void launch_x_from_e(const LevelDev<double>& L, int dim, const float* e, double*
                      iters);
 }
 
-void launch_combine(long long N, const double* x, const double* w, int nterms, int nrhs, int stride, double* u,
-                    hipStream_t st, unsigned long long* ctr, const double* base, double base_w, bool w_per_system,
-                    const double* pa, const double* pb, const double* alpha, const int* iters) {
-  const dim3 g((unsigned)((N + 255) / 256), nrhs);
-  hipLaunchKernelGGL(k_combine, g, dim3(256), 0, st, N, x, w, nterms, stride, u, base, base_w, ctr,
-                     w_per_system ? 1 : 0, pa, pb, alpha, iters);
+void launch_combine(long long N, const double* x, const double* w, const CombineTerms& t, int nout, int nrhs,
+                    int stride, double* u, hipStream_t st, unsigned long long* ctr, const double* base, double base_w,
+                    bool w_per_system, const double* pa, const double* pb, const double* alpha, const int* iters,
+                    double* partial, double* norms) {
+  const int nb = combine_blocks(N);
+  hipLaunchKernelGGL(k_combine, dim3((unsigned)nb, nrhs, nout), dim3(256), 0, st, N, x, w, t, stride, u, base, base_w,
+                     ctr, w_per_system ? 1 : 0, pa, pb, alpha, iters, partial);
+  if (partial)
+    hipLaunchKernelGGL(k_row_sum, dim3(nout * nrhs), dim3(nb > 256 ? 1024 : 256), 0, st, partial, nb, norms);
 }
 
-void launch_row_norms(const double* u, long long N, int rows, double* partial, double* out, hipStream_t st) {
-  const int nb = (int)((N + 255) / 256);
-  hipLaunchKernelGGL(k_row_norm2, dim3(nb, rows), dim3(256), 0, st, u, N, partial);
-  hipLaunchKernelGGL(k_row_sum, dim3(rows), dim3(256), 0, st, partial, nb, out);
-}
+int combine_blocks(long long N) { return (int)((N + 256 * kCombineItems - 1) / (256 * kCombineItems)); }
 
 void launch_apply64(int dim, bool var, const LevelDev<double>& L, const double* x, double* y, double shift, int nvec,
                     hipStream_t st) {
@@ -4098,15 +4119,34 @@ __global__ void k_fill_int(int* __restrict__ p, long long n, int v) {
   if (i < n) p[i] = v;
 }
 
-// flags of system j * R + r: 1 for r < nrhs, 0 otherwise
-__global__ void k_slot_flags(int* __restrict__ p, int nterms, int R, int nrhs) {
+// The scalar state at the start of a solve, in one launch: counters and flags
+// cleared, no iterate update pending, and the used systems active: with up ==
+// nullptr system j R + r for r < nrhs, else as the uploaded slot terms say,
+// which are unpacked to the per-system arrays.
+__global__ __launch_bounds__(256) void k_begin(SysState S, int nsys, int R, int nrhs, SlotUpload up) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nterms * R) p[i] = (i % R) < nrhs ? 1 : 0;
+  if (i >= nsys) return;
+  S.flags[i] = 0;
+  S.total_iters[i] = 0;
+  S.outer[i] = 0;
+  S.alpha[i] = 0.0;
+  int on = (i % R) < nrhs;
+  if (up.staged) {
+    const double* h = up.staged;
+    up.w[i] = h[i];
+    up.s64[i] = h[nsys + i];
+    up.tol[i] = h[2 * nsys + i];
+    const float* h32 = reinterpret_cast<const float*>(h + 3 * (size_t)nsys);
+    if (up.s32) up.s32[i] = h32[i];
+    if (up.s64b) up.s64b[i] = h[nsys + i];
+    on = reinterpret_cast<const int*>(h32 + nsys)[i];
+  }
+  S.active[i] = on;
+  S.active64[i] = on;
 }
 
-void launch_slot_flags(int* p, int nterms, int R, int nrhs, hipStream_t st) {
-  const int n = nterms * R;
-  hipLaunchKernelGGL(k_slot_flags, dim3((n + 255) / 256), dim3(256), 0, st, p, nterms, R, nrhs);
+void launch_begin(const SysState& S, int nsys, int R, int nrhs, const SlotUpload& up, hipStream_t st) {
+  hipLaunchKernelGGL(k_begin, dim3((nsys + 255) / 256), dim3(256), 0, st, S, nsys, R, nrhs, up);
 }
 
 void launch_fill_int(int* p, long long n, int v, hipStream_t st) {
