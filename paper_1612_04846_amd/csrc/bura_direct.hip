@@ -30,6 +30,7 @@ typedef double double4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kSineThreads = 256;   // four waves, 2 x 2 over the tile
 constexpr int kSineK = 16;          // transformed-axis values staged per step
+constexpr int kFftMin = 64;         // smallest n + 1 = 2^p that runs as fast Fourier transforms
 
 // One transform along one axis of a batch of grids.
 struct SinePass {
@@ -293,25 +294,380 @@ void run_pass(SinePass a, long long batches, hipStream_t st) {
   }
 }
 
+// --------------------------------------------------------------------------
+// n + 1 = 2^p: the same transform by fast Fourier transforms
+//
+// Two lines a, b are one complex sequence z = a + i b, extended to length
+// L = 2 (n + 1) as an odd sequence; its Fourier transform is Z_k = 2 S b_k -
+// 2 i S a_k.  That is twice the arithmetic of a transform that used the odd
+// symmetry, but the pass stays bound by its two memory passes (16 bytes a
+// value): 5 L log2 L flops per two lines against the n^2 / 2 of the products.
+//
+// A thread holds 16 complex values: radix-16 steps, the last one L / 256 (L /
+// 16 for L = 128), in the self-sorting order, the values exchanged through LDS
+// between steps, real parts first and then imaginary parts (half the LDS of
+// complex values, so two workgroups of 512 threads fit a CU).
+// --------------------------------------------------------------------------
+struct FftPass {
+  const double* in;
+  double* out;
+  const double2* tw;     // exp(-2 pi i m / L), m < L
+  int n;
+  int tiles;             // workgroups across the lines of a batch
+  long long groups;      // batches * tiles
+  long long per;         // groups per XCD
+  long long in_stride, out_stride, ld, lines;
+  int planes, rhs_of;
+  const int* gate;
+  int zero;
+  const double* mu;      // 1D eigenvalues in the split order of the products
+  int axes;
+  double wc;
+  const double* shift;
+  double* partial;
+  unsigned long long* ctr;
+};
+
+struct cplx {
+  double x, y;
+};
+__device__ __forceinline__ cplx operator+(cplx a, cplx b) { return {a.x + b.x, a.y + b.y}; }
+__device__ __forceinline__ cplx operator-(cplx a, cplx b) { return {a.x - b.x, a.y - b.y}; }
+__device__ __forceinline__ cplx operator*(cplx a, cplx b) {
+  return {fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)};
+}
+__device__ __forceinline__ cplx mul_mi(cplx a) { return {a.y, -a.x}; }   // -i a
+
+// Fourier transforms of R values, v[s], v[s + d], v[s + 2 d], ..., in place and
+// in order
+template <int R>
+__device__ __forceinline__ void dft(cplx* v, int s, int d) {
+  if constexpr (R == 2) {
+    const cplx a = v[s], b = v[s + d];
+    v[s] = a + b;
+    v[s + d] = a - b;
+  } else if constexpr (R == 4) {
+    const cplx a = v[s] + v[s + 2 * d], b = v[s] - v[s + 2 * d];
+    const cplx c = v[s + d] + v[s + 3 * d], e = mul_mi(v[s + d] - v[s + 3 * d]);
+    v[s] = a + c;
+    v[s + d] = b + e;
+    v[s + 2 * d] = a - c;
+    v[s + 3 * d] = b - e;
+  } else if constexpr (R == 8) {
+    const double h = 0.70710678118654752440;
+    dft<4>(v, s, 2 * d);       // even positions
+    dft<4>(v, s + d, 2 * d);   // odd positions
+    cplx o1 = v[s + 3 * d], o2 = v[s + 5 * d], o3 = v[s + 7 * d];
+    o1 = {h * (o1.x + o1.y), h * (o1.y - o1.x)};
+    o2 = mul_mi(o2);
+    o3 = {h * (o3.y - o3.x), -h * (o3.x + o3.y)};
+    const cplx e0 = v[s], e1 = v[s + 2 * d], e2 = v[s + 4 * d], e3 = v[s + 6 * d], o0 = v[s + d];
+    v[s] = e0 + o0;
+    v[s + d] = e1 + o1;
+    v[s + 2 * d] = e2 + o2;
+    v[s + 3 * d] = e3 + o3;
+    v[s + 4 * d] = e0 - o0;
+    v[s + 5 * d] = e1 - o1;
+    v[s + 6 * d] = e2 - o2;
+    v[s + 7 * d] = e3 - o3;
+  } else if constexpr (R == 16) {
+    const double c1 = 0.92387953251128675613, s1 = 0.38268343236508977173, h = 0.70710678118654752440;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) dft<4>(v, s + q * d, 4 * d);
+    // v[q + 4 k] is coefficient k of column q: times exp(-2 pi i q k / 16)
+    auto tw = [&](int q, int k, double cr, double ci) {
+      cplx& a = v[s + (q + 4 * k) * d];
+      a = a * cplx{cr, ci};
+    };
+    tw(1, 1, c1, -s1);
+    tw(1, 2, h, -h);
+    tw(1, 3, s1, -c1);
+    tw(2, 1, h, -h);
+    v[s + 10 * d] = mul_mi(v[s + 10 * d]);
+    tw(2, 3, -h, -h);
+    tw(3, 1, s1, -c1);
+    tw(3, 2, -h, -h);
+    tw(3, 3, -c1, s1);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dft<4>(v, s + 4 * k * d, d);
+    // v[4 k + m] is coefficient k + 4 m: transpose
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int m = k + 1; m < 4; ++m) {
+        const cplx a = v[s + (4 * k + m) * d];
+        v[s + (4 * k + m) * d] = v[s + (4 * m + k) * d];
+        v[s + (4 * m + k) * d] = a;
+      }
+  }
+}
+
+// v[s + i d] *= w^i, i < R, from w, w^2, w^4, w^8 (at most three roundings)
+template <int R>
+__device__ __forceinline__ void twiddle(cplx* v, int s, int d, const double2* __restrict__ tw, int m, int mask) {
+  cplx w[R > 8 ? 16 : (R > 4 ? 8 : 4)];
+#pragma unroll
+  for (int i = 1; i < R; i <<= 1) {
+    const double2 a = tw[(m * i) & mask];
+    w[i] = {a.x, a.y};
+  }
+#pragma unroll
+  for (int i = 3; i < R; ++i) {
+    const int top = i >= 8 ? 8 : (i >= 4 ? 4 : 2);
+    if (i != top) w[i] = w[top] * w[i - top];
+  }
+#pragma unroll
+  for (int i = 1; i < R; ++i) v[s + i * d] = v[s + i * d] * w[i];
+}
+
+// Workgroup shape: T = L/16 threads per pair of lines.  Rows: 256 threads (at
+// least one pair).  Columns: pairs side by side so that a row of the tile is
+// 128 bytes (64 at L = 2048, 32 at 4096, where LDS holds no more).
+template <int LOG>
+constexpr int fft_pairs(bool row) {
+  constexpr int T = (1 << LOG) / 16;
+  return row ? (T >= 256 ? 1 : 256 / T) : (LOG <= 8 ? 16 : LOG <= 10 ? 8 : LOG == 11 ? 4 : 2);
+}
+
+template <int LOG, bool ROW, bool SCALE>
+__global__ __launch_bounds__((1 << LOG) / 16 * fft_pairs<LOG>(ROW)) void k_sine_fft(FftPass a) {
+  constexpr int L = 1 << LOG, N = L / 2, T = L / 16, P = fft_pairs<LOG>(ROW);
+  constexpr int RL = LOG == 7 ? 8 : (L / 256);   // the last step's radix (1: there is none)
+  __shared__ double sh[L * P];
+  const long long id = blockIdx.x;
+  // neighbouring tiles on one XCD: a tile row of columns may be half a line
+  const long long grp = (id & 7) * a.per + (id >> 3);
+  if (grp >= a.groups) return;
+  const long long batch = grp / a.tiles;
+  const int tile = (int)(grp - batch * a.tiles);
+  const int sys = (int)(batch / a.planes);
+  const int g = a.gate ? a.gate[sys] : 1;
+  if (g == 0 || (g == 2 && !a.zero)) return;
+  const int tid = threadIdx.x;
+  const int pair = ROW ? tid / T : tid % P, t = ROW ? tid % T : tid / P;
+  const long long l0 = ((long long)tile * P + pair) * 2;   // lines l0 and l0 + 1
+  const bool on0 = l0 < a.lines, on1 = l0 + 1 < a.lines;
+  const long long ib = a.rhs_of > 0 ? (long long)(sys % a.rhs_of) : batch;
+  const double* __restrict__ in = a.in + ib * a.in_stride;
+  double* __restrict__ out = a.out + batch * a.out_stride;
+  const int n = a.n;
+  if (a.ctr && tid == 0) {
+    const long long ln = min((long long)2 * P, a.lines - (long long)tile * P * 2);
+    atomicAdd(a.ctr, (unsigned long long)(2 * ln * n) * 8ULL);
+  }
+  // value j (1-based) of a line
+  auto addr = [&](int j, long long l) { return ROW ? l * n + (j - 1) : (long long)(j - 1) * a.ld + l; };
+  if (g == 2) {
+    for (int j = t; j < N; j += T) {
+      if (j >= 1 && on0) out[addr(j, l0)] = 0.0;
+      if (j >= 1 && on1) out[addr(j, l0 + 1)] = 0.0;
+    }
+    return;
+  }
+  double mu0 = 0.0, mu1 = 0.0;
+  // the split order of the eigenvalue table: odd numbers first
+  auto mu_at = [&](long long k) { return a.mu[(k & 1) ? (k - 1) / 2 : N / 2 + k / 2 - 1]; };
+  if (SCALE) {
+    auto across = [&](long long l) {
+      l = min(l, a.lines - 1);
+      return a.axes == 1 ? mu_at(l + 1) : mu_at(l / n + 1) + mu_at(l % n + 1);
+    };
+    mu0 = fma(a.wc, across(l0), a.shift[sys]);
+    mu1 = fma(a.wc, across(l0 + 1), a.shift[sys]);
+  }
+  cplx v[16];
+  double ssq = 0.0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    // odd extension: z_j = x_j, z_{L-j} = -x_j, 0 at 0 and N
+    const int e = t + i * T;
+    const int j = i < 8 ? e : L - e;
+    const bool in_grid = j >= 1 && j < N;
+    v[i] = {0.0, 0.0};
+    if (in_grid && on0) v[i].x = in[addr(j, l0)];
+    if (in_grid && on1) v[i].y = in[addr(j, l0 + 1)];
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    if (ROW && !SCALE && i < 8) ssq += v[i].x * v[i].x + v[i].y * v[i].y;
+    if (SCALE) {
+      const int e = t + i * T;
+      const int j = min(max(i < 8 ? e : L - e, 1), N - 1);
+      const double m = mu_at(j);
+      v[i].x *= recip(fma(a.wc, m, mu0));
+      v[i].y *= recip(fma(a.wc, m, mu1));
+    }
+    if (i >= 8) v[i] = {-v[i].x, -v[i].y};
+  }
+  // LDS position of value q of this thread's pair: the low four bits of q are
+  // mixed with the next four, so the strided writes of a step spread over the banks
+  auto at = [&](int q) {
+    const int z = q ^ ((q >> 4) & 15);
+    return ROW ? pair * L + z : z * P + pair;
+  };
+  // hand the values over: put(i) is where value i goes, get(i) what comes back
+  auto exchange = [&](auto put, auto get) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sh[at(put(i))] = v[i].x;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i].x = sh[at(get(i))];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sh[at(put(i))] = v[i].y;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i].y = sh[at(get(i))];
+  };
+  dft<16>(v, 0, 1);
+  constexpr int M = 16 / RL;   // the last step's transforms per thread
+  if constexpr (LOG >= 8) {
+    exchange([&](int i) { return t * 16 + i; }, [&](int i) { return t + i * T; });
+    const int k = t & 15;
+    twiddle<16>(v, 0, 1, a.tw, k * (L / 256), L - 1);
+    dft<16>(v, 0, 1);
+    if constexpr (RL > 1)
+      exchange([&](int i) { return (t >> 4) * 256 + k + i * 16; },
+               [&](int i) { return t + (i / RL) * T + (i % RL) * 256; });
+  } else {
+    exchange([&](int i) { return t * 16 + i; }, [&](int i) { return t + (i / RL) * T + (i % RL) * 16; });
+  }
+  if constexpr (RL > 1) {
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      twiddle<RL>(v, m * RL, 1, a.tw, t + m * T, L - 1);
+      dft<RL>(v, m * RL, 1);
+    }
+  }
+  // coefficient k of value i; those past N repeat the first half
+  const double sc = 0.5 * sqrt(2.0 / N);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    constexpr int NS = L / RL;
+    const int k = RL > 1 ? t + (i / RL) * T + (i % RL) * NS : (t >> 4) * 256 + (t & 15) + i * 16;
+    if (k < 1 || k >= N) continue;
+    if (on0) out[addr(k, l0)] = -sc * v[i].y;
+    if (on1) out[addr(k, l0 + 1)] = sc * v[i].x;
+  }
+  if (ROW && !SCALE && a.partial) {
+    // fixed-order block sum of the squares
+    constexpr int NW = (T * P + 63) / 64;
+    __shared__ double sw[NW];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ssq += __shfl_xor(ssq, o, 64);
+    if ((tid & 63) == 0) sw[tid >> 6] = ssq;
+    __syncthreads();
+    if (tid == 0) {
+      double tot = 0.0;
+      for (int w = 0; w < NW; ++w) tot += sw[w];
+      a.partial[grp] = tot;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_fft_table(int L, double2* tw) {
+  const int m = blockIdx.x * 256 + threadIdx.x;
+  if (m >= L) return;
+  double s, c;
+  sincospi(2.0 * m / L, &s, &c);
+  tw[m] = make_double2(c, -s);
+}
+
+template <int LOG, bool ROW, bool SCALE>
+void run_fft_log(FftPass a, long long batches, hipStream_t st) {
+  constexpr int P = fft_pairs<LOG>(ROW);
+  a.tiles = (int)((a.lines + 2 * P - 1) / (2 * P));
+  a.groups = batches * a.tiles;
+  a.per = (a.groups + 7) / 8;
+  hipLaunchKernelGGL((k_sine_fft<LOG, ROW, SCALE>), dim3((unsigned)(8 * a.per)), dim3((1 << LOG) / 16 * P), 0, st, a);
+}
+
+template <bool ROW, bool SCALE>
+void run_fft(const SinePass& p, const double2* tw, long long batches, hipStream_t st) {
+  FftPass a{};
+  a.in = p.in;
+  a.out = p.out;
+  a.tw = tw;
+  a.n = p.n;
+  a.in_stride = p.in_stride;
+  a.out_stride = p.out_stride;
+  a.ld = p.ld;
+  a.lines = p.lines;
+  a.planes = p.planes;
+  a.rhs_of = p.rhs_of;
+  a.gate = p.gate;
+  a.zero = p.zero;
+  a.mu = p.mu;
+  a.axes = p.axes;
+  a.wc = p.wc;
+  a.shift = p.shift;
+  a.partial = p.partial;
+  a.ctr = p.ctr;
+  switch (p.n + 1) {
+    case 64: run_fft_log<7, ROW, SCALE>(a, batches, st); break;
+    case 128: run_fft_log<8, ROW, SCALE>(a, batches, st); break;
+    case 256: run_fft_log<9, ROW, SCALE>(a, batches, st); break;
+    case 512: run_fft_log<10, ROW, SCALE>(a, batches, st); break;
+    case 1024: run_fft_log<11, ROW, SCALE>(a, batches, st); break;
+    case 2048: run_fft_log<12, ROW, SCALE>(a, batches, st); break;
+  }
+}
+
+// one pass of either kind
+template <bool ROW, bool INV, bool SCALE>
+void pass(const SinePass& a, const double2* tw, long long batches, hipStream_t st) {
+  if (tw) run_fft<ROW, SCALE>(a, tw, batches, st);
+  else run_pass<ROW, INV, SCALE>(a, batches, st);
+}
+
+// grids whose transforms are fast Fourier transforms
+bool by_fft(int n) {
+  const int N = n + 1;
+  return (N & n) == 0 && N >= kFftMin && N <= 2048;
+}
+
+// lines per workgroup of the forward row pass
+int fft_row_lines(int n) {
+  const int T = (n + 1) / 8;
+  return 2 * (T >= 256 ? 1 : 256 / T);
+}
+
 }  // namespace
 
 int sine_half(int n) { return (((n + 1) / 2) + 63) / 64 * 64; }
 
-size_t sine_table_doubles(int n) { return 4 * (size_t)sine_half(n) * sine_half(n) + (size_t)n; }
+// the 1D eigenvalues, then the twiddle factors or the four half matrices
+static size_t mu_doubles(int n) { return ((size_t)n + 1) / 2 * 2; }
+
+size_t sine_table_doubles(int n) {
+  return mu_doubles(n) + (by_fft(n) ? 4 * (size_t)(n + 1) : 4 * (size_t)sine_half(n) * sine_half(n));
+}
 
 void launch_sine_tables(int n, double* tab, hipStream_t st) {
+  const bool fft = by_fft(n);
   const int hp = sine_half(n);
-  const long long hh = (long long)hp * hp;
+  const long long hh = fft ? 0 : (long long)hp * hp;
+  double* mats = tab + mu_doubles(n);
   hipLaunchKernelGGL(k_sine_tables, dim3((unsigned)((std::max<long long>(hh, n) + 255) / 256)), dim3(256), 0, st, n,
-                     (n + 1) / 2, n / 2, hp, tab, tab + 4 * hh);
+                     (n + 1) / 2, n / 2, fft ? 0 : hp, mats, tab);
+  if (fft)
+    hipLaunchKernelGGL(k_fft_table, dim3((2 * (n + 1) + 255) / 256), dim3(256), 0, st, 2 * (n + 1), (double2*)mats);
 }
 
 int sine_norm_blocks(int dim, int n, int nrhs) {
   const long long rows = dim == 3 ? (long long)n * n : n;
+  if (by_fft(n)) return (int)((rows + fft_row_lines(n) - 1) / fft_row_lines(n));
   const int hp = (n + 1) / 2;
   const long long t64 = (rows + 63) / 64;
   const long long big = ((nrhs * t64 + 7) / 8) * 8 * ((hp + 63) / 64);
   return (int)(big >= 512 ? t64 : (rows + 31) / 32);
+}
+
+int sine_norm_max_blocks(int dim, int n) {
+  const long long rows = dim == 3 ? (long long)n * n : n;
+  const int lines = by_fft(n) ? fft_row_lines(n) : 32;
+  return (int)((rows + lines - 1) / lines);
 }
 
 void launch_sine_forward(const SineSolve& s, hipStream_t st, unsigned long long* ctr, double* partial) {
@@ -324,8 +680,9 @@ void launch_sine_forward(const SineSolve& s, hipStream_t st, unsigned long long*
   a.h0 = n / 2;
   a.hp = hp;
   a.planes = 1;
-  a.t0 = s.tab;
-  a.t1 = s.tab + hh;
+  const double2* tw = by_fft(n) ? (const double2*)(s.tab + mu_doubles(n)) : nullptr;
+  a.t0 = s.tab + mu_doubles(n);
+  a.t1 = a.t0 + hh;
   a.ctr = ctr;
   a.ld = n;
   // x: f -> work
@@ -334,14 +691,14 @@ void launch_sine_forward(const SineSolve& s, hipStream_t st, unsigned long long*
   a.in_stride = a.out_stride = N;
   a.lines = N / n;
   a.partial = partial;
-  run_pass<true, false, false>(a, s.nrhs, st);
+  pass<true, false, false>(a, tw, s.nrhs, st);
   a.partial = nullptr;
   // y: work -> x
   a.in = s.work;
   a.out = s.x;
   a.lines = n;
   a.in_stride = a.out_stride = nn;
-  run_pass<false, false, false>(a, s.dim == 3 ? (long long)s.nrhs * n : s.nrhs, st);
+  pass<false, false, false>(a, tw, s.dim == 3 ? (long long)s.nrhs * n : s.nrhs, st);
   if (s.dim == 3) {
     // z: x -> work
     a.in = s.x;
@@ -349,7 +706,7 @@ void launch_sine_forward(const SineSolve& s, hipStream_t st, unsigned long long*
     a.ld = nn;
     a.lines = nn;
     a.in_stride = a.out_stride = N;
-    run_pass<false, false, false>(a, s.nrhs, st);
+    pass<false, false, false>(a, tw, s.nrhs, st);
   }
 }
 
@@ -363,9 +720,10 @@ void launch_sine_back(const SineSolve& s, hipStream_t st, unsigned long long* ct
   a.h0 = n / 2;
   a.hp = hp;
   a.planes = 1;
-  a.t0 = s.tab + 2 * hh;
-  a.t1 = s.tab + 3 * hh;
-  a.mu = s.tab + 4 * hh;
+  const double2* tw = by_fft(n) ? (const double2*)(s.tab + mu_doubles(n)) : nullptr;
+  a.t0 = s.tab + mu_doubles(n) + 2 * hh;
+  a.t1 = a.t0 + hh;
+  a.mu = s.tab;
   a.axes = s.dim - 1;
   a.wc = s.wc;
   a.shift = s.shift;
@@ -379,7 +737,7 @@ void launch_sine_back(const SineSolve& s, hipStream_t st, unsigned long long* ct
   a.ld = s.dim == 3 ? nn : n;
   a.lines = s.dim == 3 ? nn : n;
   a.in_stride = a.out_stride = N;
-  run_pass<false, true, true>(a, s.nsys, st);
+  pass<false, true, true>(a, tw, s.nsys, st);
   a.rhs_of = 0;
   if (s.dim == 3) {
     // y, plane by plane: x -> work
@@ -389,7 +747,7 @@ void launch_sine_back(const SineSolve& s, hipStream_t st, unsigned long long* ct
     a.lines = n;
     a.planes = n;
     a.in_stride = a.out_stride = nn;
-    run_pass<false, true, false>(a, (long long)s.nsys * n, st);
+    pass<false, true, false>(a, tw, (long long)s.nsys * n, st);
     a.planes = 1;
   }
   // x: work -> x
@@ -399,7 +757,7 @@ void launch_sine_back(const SineSolve& s, hipStream_t st, unsigned long long* ct
   a.lines = N / n;
   a.in_stride = a.out_stride = N;
   a.zero = 1;
-  run_pass<true, true, false>(a, s.nsys, st);
+  pass<true, true, false>(a, tw, s.nsys, st);
 }
 
 }  // namespace bura

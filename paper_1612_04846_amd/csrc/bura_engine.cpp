@@ -610,8 +610,8 @@ bool direct_allowed(const bura_plan_t P) {
 }
 
 size_t direct_bytes(const bura_plan_t P) {
-  const size_t rows = P->dim == 3 ? (size_t)P->n * P->n : (size_t)P->n;
-  return sine_table_doubles(P->n) * 8 + (size_t)P->opts.nrhs_max * ((rows + 31) / 32) * 8 + (size_t)P->S * 4;
+  return sine_table_doubles(P->n) * 8 + (size_t)P->opts.nrhs_max * sine_norm_max_blocks(P->dim, P->n) * 8 +
+         (size_t)P->S * 4;
 }
 
 // q = (A + s) p needs a buffer unless the kernel that takes the PCG residual
@@ -1965,9 +1965,9 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
     const bool fits = ws ? P->ws_used + direct_bytes(P) + 1024 <= ws_cap
                          : o.hbm_budget == 0 || footprint(P, mixed ? 4 : 8, mixed) + direct_bytes(P) <= o.hbm_budget;
     if (fits) {
-      const size_t rows = P->dim == 3 ? (size_t)P->n * P->n : (size_t)P->n;
+      const size_t fpart = (size_t)o.nrhs_max * sine_norm_max_blocks(P->dim, P->n) * 8;
       P->direct = !dev_alloc(P, (void**)&P->d_sine, sine_table_doubles(P->n) * 8) &&
-                  !dev_alloc(P, (void**)&P->d_fpart, (size_t)o.nrhs_max * ((rows + 31) / 32) * 8) &&
+                  !dev_alloc(P, (void**)&P->d_fpart, fpart) &&
                   !dev_alloc(P, (void**)&P->d_gate, S * sizeof(int));
       if (P->direct) launch_sine_tables(P->n, P->d_sine, P->stream);
       (void)hipGetLastError();   // no memory for them: the plan iterates from zero

@@ -176,6 +176,7 @@ struct SineSolve {
 size_t sine_table_doubles(int n);
 void launch_sine_tables(int n, double* tab, hipStream_t st);
 int sine_norm_blocks(int dim, int n, int nrhs);
+int sine_norm_max_blocks(int dim, int n);   // for any nrhs
 void launch_sine_forward(const SineSolve& s, hipStream_t st, unsigned long long* ctr, double* partial);
 void launch_sine_back(const SineSolve& s, hipStream_t st, unsigned long long* ctr);
 

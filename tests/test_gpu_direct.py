@@ -1,8 +1,9 @@
 """GPU parity of the direct solution that starts constant-coefficient solves.
 
 Plans with constant coefficients and the library's own damping form every
-shifted system's solution in the sine basis first (two products per axis on
-the FP64 matrix cores), test its FP64 residual and iterate only from there.
+shifted system's solution in the sine basis first (two transforms per axis:
+products on the FP64 matrix cores, or fast Fourier transforms where n + 1 is
+a power of two), test its FP64 residual and iterate only from there.
 The sizes sit at the edges of the 32- and 64-wide tiles and of the halves the
 transforms split into (odd sizes have an unpaired middle value), with one
 right-hand side (32 x 32 tiles) and with enough of them for 64 x 64 ones.
@@ -47,6 +48,8 @@ def _rel(u, ref):
 SIZES = [(2, n, 1) for n in (1, 2, 3, 16, 31, 32, 33, 63, 64, 65, 127, 128, 129)]
 SIZES += [(3, n, 1) for n in (1, 2, 5, 16, 17, 31, 33, 64, 65)]
 SIZES += [(2, 65, 64), (2, 130, 24), (3, 31, 8)]   # 64 x 64 tiles
+# fast Fourier transforms (n + 1 = 2^p; 63 and 127 are above), each length
+SIZES += [(2, 255, 3), (2, 511, 2), (2, 1023, 1), (2, 2047, 1), (3, 63, 2), (3, 127, 1)]
 
 
 @pytest.mark.parametrize("dim,n,nrhs", SIZES)
