@@ -633,7 +633,189 @@ int fft_row_lines(int n) {
   return 2 * (T >= 256 ? 1 : 256 / T);
 }
 
+// --------------------------------------------------------------------------
+// The residual test and the combine (see launch_check)
+//
+// Bound by one read of every system's x (8 bytes a point): a thread owns a
+// block of points, keeps f and the sums of the outputs there in registers and
+// goes through the terms of its output, so x is read once for both.  The
+// separate passes read it twice, and the residual pass of the refinement also
+// writes r and e, which only a system over its tolerance needs (1023^2, 30
+// systems: 139 + 69 -> 109 us; 255^3, 9 systems: 803 + 260 -> 611 us).
+// --------------------------------------------------------------------------
+constexpr int kCheckRows = 4;   // rows per thread
+
+// the sums of a workgroup's four waves over each term's points, one barrier
+// for all terms
+struct CheckSums {
+  double* wave;   // [term][4] in LDS
+  __device__ __forceinline__ void add(int slot, double v) const {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    const int tid = threadIdx.x + threadIdx.y * blockDim.x;
+    if ((tid & 63) == 0) wave[slot * 4 + (tid >> 6)] = v;
+  }
+  __device__ __forceinline__ double total(int slot) const {
+    const double* w = wave + slot * 4;
+    return (w[0] + w[1]) + (w[2] + w[3]);
+  }
+};
+
+// 2D: the next term's loads are in flight while a term is used.  3D: one plane
+// per workgroup, and each XCD (workgroups are dealt to the 8 XCDs round-robin)
+// keeps a range of rows and walks the planes, so the planes above and below
+// come from its L2 (10 terms x 3 planes x 1/8 of 255^2 points: 2 of 4 MB).
+template <int DIM, bool COMB>
+__global__ __launch_bounds__(256) void k_check(CheckArgs a, CombineTerms t) {
+  constexpr int R = kCheckRows;
+  __shared__ double wave_sums[(BURA_MAX_TERMS + 1) * 4];
+  const CheckSums sums{wave_sums};
+  const int n = a.n;
+  const int z = blockIdx.z;
+  const int out = COMB ? z / a.nrhs : 0, r = COMB ? z % a.nrhs : z % a.stride;
+  const int jb = COMB ? t.begin[out] : z / a.stride, je = COMB ? t.begin[out + 1] : jb + 1;
+  const int xt = (n + blockDim.x - 1) / blockDim.x, yt = (n + blockDim.y * R - 1) / (blockDim.y * R);
+  const int tiles = xt * yt;
+  int tile = blockIdx.x, k = 0;
+  if (DIM == 3) {
+    const int per = (tiles + 7) / 8, q = blockIdx.x >> 3;
+    k = q / per;
+    tile = (blockIdx.x & 7) * per + q % per;
+    if (tile >= tiles) return;
+  }
+  const int blk = k * tiles + tile, nblk = DIM == 3 ? tiles * n : tiles;
+  const int by = tile / xt;
+  const int i = (tile - by * xt) * blockDim.x + threadIdx.x, j0 = (by * blockDim.y + threadIdx.y) * R;
+  const bool on = i < n && j0 < n;
+  const int ic = min(i, n - 1);
+  const long long nn = (long long)n * n, pk = k * nn;
+  // in-plane offsets of the rows j0 - 1 .. j0 + R, on the grid
+  int row[R + 2];
+#pragma unroll
+  for (int q = 0; q < R + 2; ++q) row[q] = min(max(j0 - 1 + q, 0), n - 1) * n;
+  const int il = max(ic - 1, 0), ir = min(ic + 1, n - 1);
+  const long long pb = (k > 0 ? k - 1 : 0) * nn, pa = min(k + 1, n - 1) * nn;
+  if (!COMB && !a.active[z]) return;
+  if (a.ctr && blk == 0 && threadIdx.x == 0 && threadIdx.y == 0)
+    atomicAdd(a.ctr, (unsigned long long)a.N * 8ULL * ((je - jb) + 1 + (COMB ? 1 : 0)));
+  double fv[R], acc[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const long long p = (long long)r * a.N + pk + row[q + 1] + ic;
+    fv[q] = a.f[p];
+    acc[q] = COMB && a.base ? a.base_w * a.base[p] : 0.0;
+  }
+  const double wc = a.wc;
+  struct Block {   // the points of a thread and their neighbours
+    double c[R + 2], l[R], r[R], b[DIM == 3 ? R : 1], f[DIM == 3 ? R : 1];
+  };
+  auto load = [&](int j, Block& p) {
+    const double* __restrict__ xs = a.x + ((long long)j * a.stride + r) * a.N;
+#pragma unroll
+    for (int q = 0; q < R + 2; ++q) p.c[q] = xs[pk + row[q] + ic];
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      p.l[q] = xs[pk + row[q + 1] + il];
+      p.r[q] = xs[pk + row[q + 1] + ir];
+      if (DIM == 3) {
+        p.b[DIM == 3 ? q : 0] = xs[pb + row[q + 1] + ic];
+        p.f[DIM == 3 ? q : 0] = xs[pa + row[q + 1] + ic];
+      }
+    }
+  };
+  auto term = [&](int j, const Block& p) {
+    const long long sys = (long long)j * a.stride + r;
+    const bool act = a.active[sys] != 0;
+    const double wv = COMB ? (a.wsys ? a.w[sys] : a.w[j]) : 0.0;
+    // per-system weights: a zero weight marks an unused slot, whose x does not count
+    const bool used = COMB && !(a.wsys && wv == 0.0);
+    if (!act && !used) return;
+    const double s = a.shift[sys];
+    double rr = 0.0;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const double c = p.c[q + 1];
+      const double dn = j0 + q > 0 ? p.c[q] : 0.0, up = j0 + q + 1 < n ? p.c[q + 2] : 0.0;
+      const double lv = i > 0 ? p.l[q] : 0.0, rv = i < n - 1 ? p.r[q] : 0.0;
+      double d = (c - lv) + (c - rv) + (c - dn) + (c - up);
+      if (DIM == 3)
+        d += (c - (k > 0 ? p.b[DIM == 3 ? q : 0] : 0.0)) + (c - (k + 1 < n ? p.f[DIM == 3 ? q : 0] : 0.0));
+      const double res = fv[q] - (wc * d + s * c);
+      if (on && j0 + q < n) rr += res * res;
+      if (used) acc[q] += wv * c;
+    }
+    if (act) sums.add(j - jb, rr);
+  };
+  Block cur;
+  if (DIM == 2 && COMB) {
+    Block next;
+    load(jb, cur);
+    for (int j = jb; j < je; j += 2) {
+      if (j + 1 < je) load(j + 1, next);
+      term(j, cur);
+      if (j + 1 >= je) break;
+      if (j + 2 < je) load(j + 2, cur);
+      term(j + 1, next);
+    }
+  } else {
+    for (int j = jb; j < je; ++j) {
+      load(j, cur);
+      term(j, cur);
+    }
+  }
+  double uu = 0.0;
+  if (COMB && on) {
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+      if (j0 + q < n) {
+        a.u[(long long)z * a.N + pk + row[q + 1] + ic] = acc[q];
+        uu += acc[q] * acc[q];
+      }
+  }
+  if (COMB && a.upartial) sums.add(BURA_MAX_TERMS, uu);
+  __syncthreads();
+  const int tid = threadIdx.x + threadIdx.y * blockDim.x;
+  if (tid < je - jb) {
+    const long long sys = (long long)(jb + tid) * a.stride + r;
+    if (a.active[sys]) a.partial[sys * nblk + blk] = sums.total(tid);
+  }
+  if (COMB && a.upartial && tid == 64) a.upartial[(size_t)z * nblk + blk] = sums.total(BURA_MAX_TERMS);
+}
+
+dim3 check_block(int n) {
+  const int x = n >= 192 ? 256 : (n >= 96 ? 128 : 64);
+  return dim3(x, 256 / x);
+}
+
+int check_tiles(int n) {
+  const dim3 b = check_block(n);
+  return ((n + b.x - 1) / b.x) * ((n + b.y * kCheckRows - 1) / (b.y * kCheckRows));
+}
+
 }  // namespace
+
+int check_blocks(int dim, int n) { return check_tiles(n) * (dim == 3 ? n : 1); }
+
+// The terms of an output go one after the other there, about 1.3 us each on a
+// grid too small to hide their loads: from about one workgroup per CU on the
+// one pass is the shorter (511^2, 256 workgroups, 9 terms: 15 against 11 + 7 us;
+// 63^3, 252: 23 against 28; 127^2, 16 workgroups, 10 terms: 15 against 4 + 5).
+bool check_combines(int dim, int n, int rows) { return (long long)check_blocks(dim, n) * rows >= 200; }
+
+void launch_check(int dim, const CheckArgs& a, const CombineTerms& t, int nout, int nsys, hipStream_t st) {
+  const dim3 b = check_block(a.n);
+  const int tiles = check_tiles(a.n);
+  const dim3 g(dim == 3 ? (tiles + 7) / 8 * 8 * a.n : tiles, 1, a.u ? nout * a.nrhs : nsys);
+#define BURA_CHECK(D, C) hipLaunchKernelGGL((k_check<D, C>), g, b, 0, st, a, t)
+  if (dim == 3) {
+    if (a.u) BURA_CHECK(3, true);
+    else BURA_CHECK(3, false);
+  } else {
+    if (a.u) BURA_CHECK(2, true);
+    else BURA_CHECK(2, false);
+  }
+#undef BURA_CHECK
+}
 
 int sine_half(int n) { return (((n + 1) / 2) + 63) / 64 * 64; }
 

@@ -1020,11 +1020,57 @@ bool combine_finishes_x(const bura_plan_t P) {
 // decide per right-hand side, on the device: launch_start)
 bool starts_direct(const bura_plan_t P) { return P->direct && (P->slots || P->run_tol <= kDirectTol); }
 
-// The direct solution of the active systems [sys0, sys0 + nsys) into x (0
-// where it does not apply), with ||f||^2 through op.  R: right-hand sides per
-// term in the system order.
-void direct_start(bura_plan_t P, int op, const double* f, int R, size_t sys0, int nsys, double* x, double* work) {
+// What the combine of a batch writes (see launch_combine; x from the batch's
+// first system).
+struct Combine {
+  const double* w = nullptr;
+  CombineTerms t{};
+  int nout = 1;
+  int nrhs = 0;
+  bool wsys = false;
+  double* u = nullptr;
+  const double* base = nullptr;
+  double base_w = 0.0;
+  bool norms = false;
+};
+
+int mixed_outer_loop(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool x_zero = false);
+
+// The systems of a batch that the direct solution left over their tolerance
+// iterate from there, from their residual.
+int finish_batch(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys) {
+  const bool mixed = P->opts.precision == BURA_MIXED;
+  const SysState S = state_at(P, sys0);
+  const int a = count_active(P, mixed ? P->st.active64 : P->st.active, sys0, nsys);
+  if (a < 0) {
+    g_last_error = "device error in the direct solution";
+    return BURA_EDEVICE;
+  }
+  if (a == 0) return BURA_OK;
+  const LevelDev<double> L0 = level_view<double>(P, 0);
+  const size_t o = sys0 * (size_t)P->N;
+  {
+    ProfScope ps(P, BURA_K_RESIDUAL64);
+    if (mixed)
+      launch_residual64(P->dim, P->var, L0, f, P->x64 + o, P->w32.x + o, P->w32.r + o, P->d_shift64 + sys0, S.active64,
+                        P->partial, nrhs, nsys, false, P->stream, ps.ctr);
+    else
+      launch_residual_fp64(P->dim, L0, f, P->w64.x + o, P->w64.r + o, P->d_shift64 + sys0, S.active, P->partial, nrhs,
+                           nsys, P->stream, ps.ctr);
+  }
+  return mixed ? mixed_outer_loop(P, f, nrhs, sys0, nsys)
+               : run_pcg<double>(P, P->w64, sys0, nsys, P->run_tol, P->opts.max_iter, combine_finishes_x(P));
+}
+
+// Solve the active systems [sys0, sys0 + nsys) directly (x = 0 where that does
+// not apply), test their residuals and, with comb != nullptr, combine them.
+// R: right-hand sides per term in the system order.
+void direct_batch(bura_plan_t P, const double* f, int R, size_t sys0, int nsys, const Combine* comb) {
   hipStream_t st = P->stream;
+  const bool mixed = P->opts.precision == BURA_MIXED;
+  const size_t o = sys0 * (size_t)P->N;
+  SysState S = state_at(P, sys0);
+  double* x = (mixed ? P->x64 : P->w64.x) + o;
   SineSolve s{};
   s.dim = P->dim;
   s.n = P->n;
@@ -1033,59 +1079,59 @@ void direct_start(bura_plan_t P, int op, const double* f, int R, size_t sys0, in
   s.stride = R;
   s.f = f;
   s.x = x;
-  s.work = work;
+  s.work = (mixed ? (double*)P->w32.z : P->w64.z) + o;
   s.tab = P->d_sine;
   s.wc = P->lev[0].wc;
   s.shift = P->d_shift64 + sys0;
   s.gate = P->d_gate + sys0;
-  ProfScope ps(P, BURA_K_DIRECT);
-  launch_sine_forward(s, st, ps.ctr, P->d_fpart);
-  launch_start(op, P->d_fpart, sine_norm_blocks(P->dim, P->n, s.nrhs), R, nsys, state_at(P, sys0), P->d_gate + sys0,
-               P->run_tol, st);
-  launch_sine_back(s, st, ps.ctr);
-}
-
-int mixed_outer_loop(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool x_zero = false);
-
-// The systems of a batch that the direct solution left over their tolerance
-// iterate from there.
-int finish_batch(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys) {
-  if (P->opts.precision == BURA_MIXED) return mixed_outer_loop(P, f, nrhs, sys0, nsys);
-  const int a = count_active(P, P->st.active, sys0, nsys);
-  if (a < 0) {
-    g_last_error = "device error in the direct solution";
-    return BURA_EDEVICE;
+  {
+    ProfScope ps(P, BURA_K_DIRECT);
+    launch_sine_forward(s, st, ps.ctr, P->d_fpart);
+    launch_start(mixed ? OP_START : OP_INIT, P->d_fpart, sine_norm_blocks(P->dim, P->n, s.nrhs), R, nsys, S,
+                 P->d_gate + sys0, P->run_tol, st);
+    launch_sine_back(s, st, ps.ctr);
   }
-  return a == 0 ? BURA_OK
-                : run_pcg<double>(P, P->w64, sys0, nsys, P->run_tol, P->opts.max_iter, combine_finishes_x(P));
+  {
+    ProfScope ps(P, BURA_K_RESIDUAL64);
+    CheckArgs c{};
+    c.n = P->n;
+    c.N = P->N;
+    c.wc = P->lev[0].wc;
+    c.x = x;
+    c.f = f;
+    c.shift = s.shift;
+    c.active = mixed ? S.active64 : S.active;
+    c.stride = R;
+    c.partial = P->partial;
+    c.ctr = ps.ctr;
+    if (comb) {
+      c.w = comb->w;
+      c.wsys = comb->wsys;
+      c.u = comb->u;
+      c.base = comb->base;
+      c.base_w = comb->base_w;
+      c.upartial = comb->norms ? P->d_upart : nullptr;
+      c.nrhs = comb->nrhs;
+    }
+    launch_check(P->dim, c, comb ? comb->t : CombineTerms{}, comb ? comb->nout : 1, nsys, st);
+  }
+  ProfScope ps(P, BURA_K_OTHER);
+  const int nb = check_blocks(P->dim, P->n);
+  S.started = 1;
+  launch_scalars(mixed ? OP_OUTER : OP_RESTART, P->partial, nb, nsys, S, P->run_tol,
+                 mixed ? P->opts.max_outer : P->opts.max_iter, st);
+  if (comb && comb->norms) launch_row_sum(P->d_upart, nb, comb->nout * comb->nrhs, P->d_unorm, st);
 }
 
 // Both batch solvers find the state as launch_begin leaves it: the used
 // systems active, counters 0 and no iterate update pending (slots that stay
-// inactive keep alpha = 0, so the final update skips them).  With spec set a
-// batch that starts from the direct solution is queued without waiting for its
-// test; the caller looks at the active flags later (finish_batch).
-int solve_batch_fp64(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool spec) {
+// inactive keep alpha = 0, so the final update skips them).
+int solve_batch_fp64(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys) {
   hipStream_t st = P->stream;
   Work<double>& W = P->w64;
   const LevelDev<double> L0 = level_view<double>(P, 0);
   const size_t o = sys0 * (size_t)P->N;
   const SysState S = state_at(P, sys0);
-  if (starts_direct(P)) {
-    direct_start(P, OP_INIT, f, nrhs, sys0, nsys, W.x + o, W.z + o);
-    {
-      ProfScope ps(P, BURA_K_RESIDUAL64);
-      launch_residual_fp64(P->dim, L0, f, W.x + o, W.r + o, P->d_shift64 + sys0, S.active, P->partial, nrhs, nsys, st,
-                           ps.ctr);
-    }
-    {
-      ProfScope ps(P, BURA_K_OTHER);
-      launch_scalars(OP_RESTART, P->partial, residual_blocks(P->dim, P->n, nsys), nsys, S, P->run_tol,
-                     P->opts.max_iter, st);
-    }
-    HIPCHK(hipGetLastError());
-    return spec ? BURA_OK : finish_batch(P, f, nrhs, sys0, nsys);
-  }
   {
     ProfScope ps(P, BURA_K_OTHER);
     Launch<double>::copy_rhs(L0, P->dim, f, W.r + o, W.x + o, nrhs, S.active, P->partial, nsys, st);
@@ -1148,29 +1194,12 @@ int mixed_outer_loop(bura_plan_t P, const double* f, int nrhs, size_t sys0, int 
   return BURA_OK;
 }
 
-int solve_batch_mixed(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys, bool spec) {
+int solve_batch_mixed(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys) {
   hipStream_t st = P->stream;
   Work<float>& W = P->w32;
   const LevelDev<double> L0 = level_view<double>(P, 0);
   const size_t o = sys0 * (size_t)P->N;
   const SysState S = state_at(P, sys0);
-  if (starts_direct(P)) {
-    direct_start(P, OP_START, f, nrhs, sys0, nsys, P->x64 + o, (double*)W.z + o);
-    {
-      ProfScope ps(P, BURA_K_RESIDUAL64);
-      launch_residual64(P->dim, P->var, L0, f, P->x64 + o, W.x + o, W.r + o, P->d_shift64 + sys0, S.active64,
-                        P->partial, nrhs, nsys, false, st, ps.ctr);
-    }
-    {
-      ProfScope ps(P, BURA_K_OTHER);
-      SysState Ss = S;
-      Ss.started = 1;
-      launch_scalars(OP_OUTER, P->partial, residual_blocks(P->dim, P->n, nsys), nsys, Ss, P->run_tol,
-                     P->opts.max_outer, st);
-    }
-    HIPCHK(hipGetLastError());
-    return spec ? BURA_OK : finish_batch(P, f, nrhs, sys0, nsys);
-  }
   // with the fused update and residual pass the first update assigns x64,
   // so the first residual need not clear it
   const bool x_zero = residual_marches_rows(P->dim, P->n, nsys);
@@ -1263,6 +1292,15 @@ int upload_slots(bura_plan_t P, int nrhs, const SlotTerms& t) {
   return BURA_OK;
 }
 
+void combine_batch(bura_plan_t P, size_t sys0, int R, const Combine& c) {
+  const double* x = (P->opts.precision == BURA_MIXED ? P->x64 : P->w64.x) + sys0 * (size_t)P->N;
+  const bool pend = combine_finishes_x(P);   // plans without stages: sys0 = 0
+  ProfScope ps(P, BURA_K_COMBINE);
+  launch_combine(P->N, x, c.w, c.t, c.nout, c.nrhs, R, c.u, P->stream, ps.ctr, c.base, c.base_w, c.wsys,
+                 pend ? P->w64.p : nullptr, pend ? P->w64.p2 : nullptr, P->st.alpha, P->st.iters,
+                 c.norms ? P->d_upart : nullptr, P->d_unorm);
+}
+
 int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t* rep,
              const SlotTerms* slot = nullptr, double tol = 0.0) {
   const auto t0 = std::chrono::steady_clock::now();
@@ -1306,7 +1344,7 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
   // again with a wait per stage: it is queued in one go only where the direct
   // solution is sure to pass, its residual being rounding, at most about
   // 3e-16 / (lambda_min + s) of |f|.
-  bool spec = starts_direct(P);
+  bool spec = starts_direct(P);   // (the solve is queued to its end)
   if (spec && !P->stages.empty()) {
     double smin = HUGE_VAL;
     for (double v : P->s) smin = std::min(smin, v);
@@ -1314,9 +1352,35 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
   }
   auto batch = [&](const double* rhs, size_t sys0, int nsys) {
     // the kernels take rhs = sys % R; pass rhs with R slots (rhs >= nrhs never active)
-    return mixed ? solve_batch_mixed(P, rhs, R, sys0, nsys, spec) : solve_batch_fp64(P, rhs, R, sys0, nsys, spec);
+    return mixed ? solve_batch_mixed(P, rhs, R, sys0, nsys) : solve_batch_fp64(P, rhs, R, sys0, nsys);
+  };
+  const bool direct = starts_direct(P);
+  // a batch that starts from the direct solution: with its combine in the pass
+  // of the residual test where nothing waits for that test
+  auto batch_direct = [&](const double* rhs, size_t sys0, int nsys, const Combine* c) -> int {
+    const bool fuse = spec && c && check_combines(P->dim, P->n, c->nout * c->nrhs);
+    direct_batch(P, rhs, R, sys0, nsys, fuse ? c : nullptr);
+    HIPCHK(hipGetLastError());
+    if (!spec) {
+      if (const int rc = finish_batch(P, rhs, R, sys0, nsys)) return rc;
+    }
+    if (c && !fuse) combine_batch(P, sys0, R, *c);
+    return BURA_OK;
   };
   const double* xsol = mixed ? P->x64 : P->w64.x;
+  // outputs with an error bound (rows of u): every output of a plan without
+  // stages, one per rhs of a slot plan
+  const int rows = slot ? nrhs : (P->stages.empty() ? P->nout * nrhs : 0);
+  // u_i = sum_{j in output i} w_j x_j (fixed order, FP64) and the squared norm
+  // of every output row
+  Combine all;
+  all.w = slot ? P->d_wsys : P->d_w;
+  for (int i = 0; i < P->nout; ++i) all.t.begin[i + 1] = P->out_end[i];
+  all.nout = P->nout;
+  all.nrhs = nrhs;
+  all.wsys = slot != nullptr;
+  all.u = u;
+  all.norms = true;
   auto solve_all = [&]() -> int {
     int rc = BURA_OK;
     if (!P->stages.empty()) {
@@ -1330,19 +1394,29 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
                                                     : xsol + (size_t)g.sol_term * R * P->N;
         const size_t sys0 = (size_t)g.tb * R;
         const int nt = g.te - g.tb;
-        if ((rc = batch(in, sys0, nt * R))) break;
-        ProfScope ps(P, BURA_K_COMBINE);
-        CombineTerms ct{};
-        ct.begin[1] = nt;
-        launch_combine(P->N, xsol + sys0 * P->N, P->d_w + g.tb, ct, 1, nrhs, R, last ? u : P->d_buf, P->stream, ps.ctr,
-                       g.base ? P->d_buf : nullptr, g.base_w);
+        Combine c;
+        c.w = P->d_w + g.tb;
+        c.t.begin[1] = nt;
+        c.nrhs = nrhs;
+        c.u = last ? u : P->d_buf;
+        c.base = g.base ? P->d_buf : nullptr;
+        c.base_w = g.base_w;
+        if (direct) {
+          rc = batch_direct(in, sys0, nt * R, &c);
+        } else if (!(rc = batch(in, sys0, nt * R))) {
+          combine_batch(P, sys0, R, c);
+        }
       }
     } else if (P->opts.schedule == BURA_PER_POLE) {
-      for (int j = 0; j < P->nterms && rc == BURA_OK; ++j) rc = batch(f, (size_t)j * R, nrhs);
-    } else {
+      for (int j = 0; j < P->nterms && rc == BURA_OK; ++j)
+        rc = direct ? batch_direct(f, (size_t)j * R, nrhs, nullptr) : batch(f, (size_t)j * R, nrhs);
+      if (rc == BURA_OK) combine_batch(P, 0, R, all);
+    } else if (direct) {
       // every system in one batch (slot solves: every rhs with its own terms);
       // unused slots stay inactive
-      rc = batch(f, 0, (int)S_used);
+      rc = batch_direct(f, 0, (int)S_used, &all);
+    } else if (!(rc = batch(f, 0, (int)S_used))) {
+      combine_batch(P, 0, R, all);
     }
     return rc;
   };
@@ -1350,21 +1424,8 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
   if (rc) return rc;
   const size_t S = (size_t)P->S;
   const size_t sb = S * (6 * 8 + 8 * 4);
-  // outputs with an error bound (rows of u): every output of a plan without
-  // stages, one per rhs of a slot plan
-  const int rows = slot ? nrhs : (P->stages.empty() ? P->nout * nrhs : 0);
-  // combine u_i = sum_{j in output i} w_j x_j (fixed order, FP64), then the
-  // squared norm of every output row
   auto combine = [&]() -> int {
-    const bool pend = combine_finishes_x(P);
-    if (P->stages.empty()) {
-      ProfScope ps(P, BURA_K_COMBINE);
-      CombineTerms ct{};
-      for (int i = 0; i < P->nout; ++i) ct.begin[i + 1] = P->out_end[i];
-      launch_combine(P->N, xsol, slot ? P->d_wsys : P->d_w, ct, P->nout, nrhs, R, u, P->stream, ps.ctr, nullptr, 0.0,
-                     slot != nullptr, pend ? P->w64.p : nullptr, pend ? P->w64.p2 : nullptr, P->st.alpha, P->st.iters,
-                     P->d_upart, P->d_unorm);
-    }
+    if (P->stages.empty()) combine_batch(P, 0, R, all);
     HIPCHK(hipGetLastError());
     return BURA_OK;
   };
@@ -1422,7 +1483,8 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
     }
     return mx;
   };
-  if ((rc = combine()) || (rc = fetch())) return rc;
+  HIPCHK(hipGetLastError());
+  if ((rc = fetch())) return rc;
   if (spec) {
     const int* act = (const int*)(hd + 6 * S) + (mixed ? 4 * S : 0);
     auto any = [&](size_t sys0, size_t nsys) {
@@ -1679,7 +1741,7 @@ int tune_tiles(bura_plan_t P) {
   const int R = P->opts.nrhs_max;
   auto solve_once = [&]() {
     auto batch = [&](size_t sys0, int nsys) {
-      return mixed ? solve_batch_mixed(P, df, 1, sys0, nsys, false) : solve_batch_fp64(P, df, 1, sys0, nsys, false);
+      return mixed ? solve_batch_mixed(P, df, 1, sys0, nsys) : solve_batch_fp64(P, df, 1, sys0, nsys);
     };
     int rc = BURA_OK;
     if (!P->stages.empty()) {
@@ -1922,6 +1984,8 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
       return fail(BURA_EDEVICE);
   }
   P->partial_len = (size_t)P->S * (size_t)max_partial_blocks(P->dim, P->n, P->N);
+  if (direct_allowed(P))
+    P->partial_len = std::max(P->partial_len, (size_t)P->S * (size_t)check_blocks(P->dim, P->n));
   if ((rc = dev_alloc(P, (void**)&P->partial, P->partial_len * 8))) return fail(rc);
   if ((rc = dev_alloc(P, (void**)&P->d_w, nterms * 8))) return fail(rc);
   if (!P->stages.empty() && (rc = dev_alloc(P, (void**)&P->d_buf, (size_t)o.nrhs_max * P->N * 8))) return fail(rc);
@@ -1949,7 +2013,8 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
   if ((rc = dev_alloc(P, (void**)&P->prof.d_ctr, BURA_K_COUNT * sizeof(unsigned long long)))) return fail(rc);
   if ((rc = dev_zero(P, P->prof.d_ctr, BURA_K_COUNT * sizeof(unsigned long long)))) return fail(rc);
   {
-    const size_t nb = (size_t)combine_blocks(P->N);
+    size_t nb = (size_t)combine_blocks(P->N);
+    if (direct_allowed(P)) nb = std::max(nb, (size_t)check_blocks(P->dim, P->n));
     if ((rc = dev_alloc(P, (void**)&P->d_upart, unorm_rows * nb * 8))) return fail(rc);
     if (mixed && (rc = dev_alloc(P, (void**)&P->d_tol_err, S * 8))) return fail(rc);
   }

@@ -156,6 +156,11 @@ struct Launch {
                        const int* active, double* partial, int nsys, hipStream_t st);
 };
 
+// The terms of each output: [begin[o], begin[o + 1])
+struct CombineTerms {
+  int begin[BURA_MAX_TERMS + 1];
+};
+
 // ---- direct solution in the sine basis (bura_direct.hip) -------------------
 // Constant coefficients: x_s = (A + shift_s)^-1 f_{s % stride} in FP64 for the
 // systems s < nsys whose gate is 1 (0: left alone, 2: x = 0), from the
@@ -193,6 +198,38 @@ constexpr double kDirectTol = 1e-6;
 void launch_start(int op, const double* partial, int nblk, int R, int nsys, const SysState& S, int* gate, double tol,
                   hipStream_t st);
 
+// The residual test of a direct solution and the combine in one pass over x:
+// partial[s] = block partials of |f - (A + shift_s) x_s|^2 of the active systems
+// s (check_blocks per system), and with u != nullptr the outputs and their norm
+// partials (upartial, check_blocks per output row), as launch_combine forms
+// them.  u == nullptr: the residuals of the systems [0, nsys) only.  f may be
+// the buffer u.
+struct CheckArgs {
+  int n;
+  long long N;
+  double wc;
+  const double* x;
+  const double* f;
+  const double* shift;
+  const int* active;
+  int stride;            // right-hand sides per term in the system order
+  double* partial;
+  unsigned long long* ctr;
+  // combine
+  const double* w;
+  int wsys;              // w[j stride + r] instead of w[j]
+  double* u;
+  const double* base;
+  double base_w;
+  double* upartial;
+  int nrhs;
+};
+int check_blocks(int dim, int n);
+// whether one pass for both leaves the launch enough workgroups
+bool check_combines(int dim, int n, int rows);
+void launch_check(int dim, const CheckArgs& a, const CombineTerms& t, int nout, int nsys, hipStream_t st);
+void launch_row_sum(const double* partial, int nblk, int rows, double* out, hipStream_t st);
+
 // r = f - (A + s) x of the active systems in FP64, partial = |r|^2 (constant
 // coefficients; residual_blocks partials per system)
 void launch_residual_fp64(int dim, const LevelDev<double>& L, const double* f, const double* x, double* r,
@@ -227,9 +264,6 @@ void launch_x_from_e(const LevelDev<double>& L, int dim, const float* e, double*
 // indexed from the same first system as x), applied to x_s as it is read.
 // With partial != nullptr (combine_blocks doubles per output row of scratch)
 // norms[o nrhs + r] = |u|^2, in a fixed summation order per row.
-struct CombineTerms {
-  int begin[BURA_MAX_TERMS + 1];
-};
 int combine_blocks(long long N);
 void launch_combine(long long N, const double* x, const double* w, const CombineTerms& t, int nout, int nrhs,
                     int stride, double* u, hipStream_t st, unsigned long long* ctr, const double* base = nullptr,

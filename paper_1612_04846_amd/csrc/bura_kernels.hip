@@ -4052,8 +4052,11 @@ void launch_combine(long long N, const double* x, const double* w, const Combine
   const int nb = combine_blocks(N);
   hipLaunchKernelGGL(k_combine, dim3((unsigned)nb, nrhs, nout), dim3(256), 0, st, N, x, w, t, stride, u, base, base_w,
                      ctr, w_per_system ? 1 : 0, pa, pb, alpha, iters, partial);
-  if (partial)
-    hipLaunchKernelGGL(k_row_sum, dim3(nout * nrhs), dim3(nb > 256 ? 1024 : 256), 0, st, partial, nb, norms);
+  if (partial) launch_row_sum(partial, nb, nout * nrhs, norms, st);
+}
+
+void launch_row_sum(const double* partial, int nblk, int rows, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_row_sum, dim3(rows), dim3(nblk > 256 ? 1024 : 256), 0, st, partial, nblk, out);
 }
 
 int combine_blocks(long long N) { return (int)((N + 256 * kCombineItems - 1) / (256 * kCombineItems)); }
