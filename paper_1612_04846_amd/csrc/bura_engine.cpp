@@ -38,8 +38,6 @@ thread_local std::string g_last_error;
     }                                                       \
   } while (0)
 
-constexpr size_t kLdsCap = 64 * 1024;
-
 struct HostLevel {
   int n = 0;
   long long N = 0;
@@ -553,18 +551,24 @@ int build_levels(bura_plan_t P, const bura_grid_t* g) {
   return BURA_OK;
 }
 
-// choose the first LDS level: the largest level l >= 1 whose sub-hierarchy fits in LDS
+// two zero-padded iterates of level l, in elements
+size_t lds_elems(const bura_plan_t P, int l) {
+  const size_t m = (size_t)P->lev[l].n + 2;
+  return 2 * m * m * (P->dim == 3 ? m : 1);
+}
+
+// choose the first LDS level: the largest level l >= 1 whose sub-hierarchy one
+// workgroup takes (k_coarse: kCoarsePoints points per thread there, one on the
+// levels below, the iterates within kCoarseLds)
 void choose_lds(bura_plan_t P, size_t elem) {
   const int L = (int)P->lev.size();
-  if (L < 2) {
-    P->lc = -1;
-    P->lds_bytes = 0;
-    return;
-  }
+  P->lc = -1;
+  P->lds_bytes = 0;
   for (int l = 1; l < L; ++l) {
     size_t tot = 0;
-    for (int q = l; q < L; ++q) tot += 3 * (size_t)P->lev[q].N * elem;
-    if (tot <= kLdsCap && (L - l) <= kMaxLdsLevels) {
+    for (int q = l; q < L; ++q) tot += lds_elems(P, q) * elem;
+    if (tot <= kCoarseLds && (L - l) <= kMaxLdsLevels && P->lev[l].N <= (long long)kCoarsePoints * kCoarseThreads &&
+        (l + 1 == L || P->lev[l + 1].N <= kCoarseThreads)) {
       P->lc = l;
       P->lds_bytes = tot;
       return;
@@ -573,8 +577,6 @@ void choose_lds(bura_plan_t P, size_t elem) {
   // the coarsest level alone does not fit (coarsening stopped early at a
   // large even n, e.g. 201 -> 100): no exact coarse solve is possible, so the
   // plan falls back to Jacobi-preconditioned CG on the fine level
-  P->lc = -1;
-  P->lds_bytes = 0;
 }
 
 template <typename T>
@@ -586,9 +588,8 @@ LdsHierarchy<T> lds_view(const bura_plan_t P) {
   for (int q = 0; q < H.nlev; ++q) {
     H.lev[q] = level_view<T>(P, P->lc + q);
     H.off[q] = off;
-    off += 3 * (int)P->lev[P->lc + q].N;
+    off += (int)lds_elems(P, P->lc + q);
   }
-  H.cycles = 1;   // one V-cycle through the in-LDS levels: the hierarchy is then a plain V-cycle
   H.nu = 2;
   H.bottom_sweeps = 8 * P->lev[L - 1].n + 8;
   H.omega = (T)(P->opts.omega > 0 ? P->opts.omega : default_omega(P->dim));

@@ -18,6 +18,10 @@ constexpr int kTileY = 4;              // rows per tile
 constexpr int kBlock = kTileX * kTileY;
 constexpr int kSlots = 2;              // reduction slots per block
 constexpr int kMaxLdsLevels = 8;
+// the coarse solve: threads of its workgroup, the points a thread may own on
+// its first level (one on the levels below), and the LDS its iterates may take
+constexpr int kCoarseThreads = 1024, kCoarsePoints = 6;
+constexpr size_t kCoarseLds = 96 * 1024;
 // Launch-shape variants of the 2D stencil-product and fused level kernels
 // (tile sizes in bura_kernels.hip); 0 is the default shape.
 constexpr int kTileVariants = BURA_TILE_VARIANTS;
@@ -48,8 +52,7 @@ template <typename T>
 struct LdsHierarchy {
   int nlev;
   LevelDev<T> lev[kMaxLdsLevels];
-  int off[kMaxLdsLevels];   // element offset of level l's x/b/t arrays in LDS (each N_l long)
-  int cycles;               // V-cycles per coarse solve
+  int off[kMaxLdsLevels];   // element offset of level l's two padded iterates in LDS ((n_l + 2)^dim each)
   int nu;                   // sweeps per smoothing step
   int bottom_sweeps;        // Jacobi sweeps on the last level if it is larger than one point
   T omega;                  // bottom-level damping

@@ -856,9 +856,21 @@ __global__ __launch_bounds__(256) void k_restrict3(LevelDev<T> Lf, LevelDev<T> L
 }
 
 // --------------------------------------------------------------------------
-// coarse solve: `cycles` V-cycles on the levels in H, one workgroup per system,
-// all vectors in LDS.  Symmetric (nu Jacobi sweeps before and after), so the
+// coarse solve: one V-cycle on the levels in H, one workgroup per system, the
+// iterates in LDS.  Symmetric (nu Jacobi sweeps before and after), so the
 // composite is an SPD preconditioner component.
+//
+// Bound by latency: about 40 dependent steps of one LDS round trip each.  So a
+// thread owns its points of a level and keeps their right-hand side, face
+// weights and inverse diagonal in registers for both halves of the cycle
+// (loaded once, before the level's first step); an iterate has two zero-padded
+// buffers, read from one and written to the other, which takes one barrier a
+// step and no boundary tests; and a coarse point's right-hand side goes
+// straight into its owner's registers.  Against the version that walked the
+// points of every step in a loop, read the face weights in each sweep and
+// copied the iterate back: 63^2 FP32, 2048 systems 83 -> 46 us; 15^3 FP32 with
+// variable coefficients 25 -> 13 us; FP64 takes 47^2 here (15 us) where 23^2
+// (20 us) and the two level kernels of 47^2 (10 us) had run.
 // --------------------------------------------------------------------------
 // weight i of a half-cycle (selected without indexing the array, which would
 // put the by-value argument in scratch memory)
@@ -884,114 +896,188 @@ __device__ __forceinline__ void ijk_of(int p, int n, float rn, int& i, int& j, i
   }
 }
 
-// omega for every sweep, or (per != nullptr) the half-cycle weights, reversed
-// for post-smoothing
-template <typename T, int DIM, bool VAR>
-__device__ void lds_smooth(const LevelDev<T>& L, T* X, const T* B, T* Tm, T s, T omega, int sweeps,
-                           const Sweeps<T>* per = nullptr, bool reverse = false) {
-  const int n = L.n;
-  const float rn = 1.0f / (float)n;
-  const int nthr = blockDim.x;
-  for (int sw = 0; sw < sweeps; ++sw) {
-    const T om = per ? sweep_w(*per, reverse ? sweeps - 1 - sw : sw) : omega;
-    for (int p = threadIdx.x; p < L.N; p += nthr) {
+__device__ __forceinline__ float coarse_recip(float d) { return __builtin_amdgcn_rcpf(d); }
+__device__ __forceinline__ double coarse_recip(double d) { return 1.0 / d; }
+
+// The P points of this thread on one LDS level: padded position (a position
+// inside the grid for a lane without a point, which computes but does not
+// write), face weights and inverse diagonal.
+template <typename T, int DIM, bool VAR, int P>
+struct LdsPoints {
+  int S1, S2;
+  int q[P];
+  bool on[P];
+  T wc, w[VAR ? 2 * DIM : 1][P], dg[VAR ? P : 1], di[VAR ? P : 1];
+  __device__ __forceinline__ LdsPoints(const LevelDev<T>& L, T s) {
+    const int n = L.n, N = (int)L.N;
+    const float rn = 1.0f / (float)n;
+    S1 = n + 2;
+    S2 = S1 * S1;
+    wc = L.wc;
+    if (!VAR) {
+      dg[0] = wc * T(2 * DIM) + s;
+      di[0] = coarse_recip(dg[0]);
+    }
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+      const int p = threadIdx.x + kCoarseThreads * u;
+      on[u] = p < N;
       int i, j, k;
-      ijk_of<DIM>(p, n, rn, i, j, k);
-      T dg;
-      const T ax = apply_pt<T, DIM, VAR>(L, X, i, j, k, p, s, &dg);
-      Tm[p] = X[p] + om * (B[p] - ax) / dg;
+      ijk_of<DIM>(on[u] ? p : 0, n, rn, i, j, k);
+      q[u] = ((DIM == 3 ? k + 1 : 0) * S1 + j + 1) * S1 + i + 1;
+      if (VAR) {
+        const int fx = (k * n + j) * (n + 1) + i, fy = (k * (n + 1) + j) * n + i;
+        w[0][u] = L.wf0[fx];
+        w[VAR ? 1 : 0][u] = L.wf0[fx + 1];
+        w[VAR ? 2 : 0][u] = L.wf1[fy];
+        w[VAR ? 3 : 0][u] = L.wf1[fy + n];
+        if (DIM == 3) {
+          const int fz = (k * n + j) * n + i;
+          w[VAR && DIM == 3 ? 4 : 0][u] = L.wf2[fz];
+          w[VAR && DIM == 3 ? 5 : 0][u] = L.wf2[fz + n * n];
+        }
+        T d = w[0][u];
+#pragma unroll
+        for (int f = 1; f < 2 * DIM; ++f) d += w[VAR ? f : 0][u];
+        dg[VAR ? u : 0] = d + s;
+        di[VAR ? u : 0] = coarse_recip(d + s);
+      }
+    }
+  }
+  __device__ __forceinline__ T diag(int u) const { return dg[VAR ? u : 0]; }
+  __device__ __forceinline__ T inv(int u) const { return di[VAR ? u : 0]; }
+  // face weights times the neighbours
+  __device__ __forceinline__ T around(const T* A, int u) const {
+    const T* c = A + q[u];
+    if (!VAR) {
+      T sum = (c[-1] + c[1]) + (c[-S1] + c[S1]);
+      if (DIM == 3) sum += c[-S2] + c[S2];
+      return wc * sum;
+    }
+    T sum = w[0][u] * c[-1] + w[VAR ? 1 : 0][u] * c[1] + w[VAR ? 2 : 0][u] * c[-S1] + w[VAR ? 3 : 0][u] * c[S1];
+    if (DIM == 3) sum += w[VAR && DIM == 3 ? 4 : 0][u] * c[-S2] + w[VAR && DIM == 3 ? 5 : 0][u] * c[S2];
+    return sum;
+  }
+  // one sweep X -> Y, then they change places
+  __device__ __forceinline__ void sweep(T*& X, T*& Y, const T* b, T om) const {
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+      const T xc = X[q[u]];
+      const T xn = xc + om * ((b[u] + around(X, u)) * inv(u) - xc);
+      if (on[u]) Y[q[u]] = xn;
     }
     __syncthreads();
-    for (int p = threadIdx.x; p < L.N; p += nthr) X[p] = Tm[p];
+    T* const t = X;
+    X = Y;
+    Y = t;
+  }
+};
+
+// One level and everything below it, with the right-hand side b of this
+// thread's points; returns the buffer that holds the level's iterate (every
+// write of it behind a barrier).  The points are set up again after the coarser
+// levels: held across them, the face weights of all levels together spill.
+template <typename T, int DIM, bool VAR, int P, int LV>
+__device__ __forceinline__ T* lds_cycle(const LdsHierarchy<T>& H, T* sm, T s, const T* b) {
+  const LevelDev<T>& L = H.lev[LV];
+  const int n = L.n, S1 = n + 2, S2 = S1 * S1;
+  T* X = sm + H.off[LV];
+  T* Y = X + (DIM == 3 ? S2 * S1 : S2);
+  {
+    const LdsPoints<T, DIM, VAR, P> pt(L, s);
+    // the first sweep, from zero
+    const bool bottom = LV + 1 >= H.nlev;
+    const T om0 = bottom ? (L.N == 1 ? T(1) : H.omega) : sweep_w(H.pre, 0);
+#pragma unroll
+    for (int u = 0; u < P; ++u)
+      if (pt.on[u]) X[pt.q[u]] = om0 * b[u] * pt.inv(u);
+    __syncthreads();
+    if (bottom) {
+      if (L.N > 1)
+        for (int m = 1; m < H.bottom_sweeps; ++m) pt.sweep(X, Y, b, H.omega);
+      return X;
+    }
+    for (int m = 1; m < H.nu; ++m) pt.sweep(X, Y, b, sweep_w(H.pre, m));
+    // the residual into Y
+#pragma unroll
+    for (int u = 0; u < P; ++u)
+      if (pt.on[u]) Y[pt.q[u]] = b[u] - (pt.diag(u) * X[pt.q[u]] - pt.around(X, u));
     __syncthreads();
   }
+  if constexpr (LV + 1 < kMaxLdsLevels) {
+    // full weighting of the residual into the coarse right-hand side
+    const LevelDev<T>& Lc = H.lev[LV + 1];
+    const int nc = Lc.n;
+    T bc[1];
+    {
+      int I, J, K;
+      ijk_of<DIM>((int)threadIdx.x < (int)Lc.N ? threadIdx.x : 0, nc, 1.0f / (float)nc, I, J, K);
+      const T wt[3] = {T(0.25), T(0.5), T(0.25)};
+      const T* c = Y + ((DIM == 3 ? 2 * K + 2 : 0) * S1 + 2 * J + 2) * S1 + 2 * I + 2;
+      T acc = T(0);
+#pragma unroll
+      for (int dk = (DIM == 3 ? -1 : 0); dk <= (DIM == 3 ? 1 : 0); ++dk)
+#pragma unroll
+        for (int dj = -1; dj <= 1; ++dj)
+#pragma unroll
+          for (int dx = -1; dx <= 1; ++dx)
+            acc += (DIM == 3 ? wt[dk + 1] : T(1)) * wt[dj + 1] * wt[dx + 1] * c[dk * S2 + dj * S1 + dx];
+      bc[0] = acc;
+    }
+    const T* C = lds_cycle<T, DIM, VAR, 1, LV + 1>(H, sm, s, bc);
+    const LdsPoints<T, DIM, VAR, P> pt(L, s);
+    // x += P x_c: an odd index lies on a coarse point, an even one halfway
+    // between two (the padding is the boundary); only this thread's points of X
+    // change before the barrier
+    const int T1 = nc + 2, T2 = T1 * T1;
+    const float rn = 1.0f / (float)n;
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+      int i, j, k;
+      ijk_of<DIM>(pt.on[u] ? threadIdx.x + kCoarseThreads * u : 0, n, rn, i, j, k);
+      const int oi = (i & 1) ? 0 : 1, oj = (j & 1) ? 0 : T1, ok = (DIM == 2 || (k & 1)) ? 0 : T2;
+      const T* c = C + ((DIM == 3 ? (k + 1) / 2 : 0) * T1 + (j + 1) / 2) * T1 + (i + 1) / 2;
+      // an index on a coarse point takes it twice, halved: exact
+      T v = T(0.25) * ((c[0] + c[oi]) + (c[oj] + c[oj + oi]));
+      if (DIM == 3) v = T(0.5) * (v + T(0.25) * ((c[ok] + c[ok + oi]) + (c[ok + oj] + c[ok + oj + oi])));
+      if (pt.on[u]) X[pt.q[u]] += v;
+    }
+    __syncthreads();
+    for (int m = H.nu - 1; m >= 0; --m) pt.sweep(X, Y, b, sweep_w(H.pre, m));
+  }
+  return X;
 }
 
-template <typename T, int DIM, bool VAR>
-__global__ __launch_bounds__(1024) void k_coarse(LdsHierarchy<T> H, const T* __restrict__ b, T* __restrict__ x,
-                                                const T* __restrict__ shift, const int* __restrict__ active,
-                                                unsigned long long* __restrict__ ctr) {
+template <typename T, int DIM, bool VAR, int PER>
+__global__ __launch_bounds__(kCoarseThreads) void k_coarse(LdsHierarchy<T> H, const T* __restrict__ b,
+                                                           T* __restrict__ x, const T* __restrict__ shift,
+                                                           const int* __restrict__ active,
+                                                           unsigned long long* __restrict__ ctr, int elems) {
   extern __shared__ unsigned char smem_raw[];
   T* sm = reinterpret_cast<T*>(smem_raw);
   const int sys = blockIdx.x;
   if (!active[sys]) return;
   count_bytes<COUNT_ONE>(ctr, 2ULL * H.lev[0].N * sizeof(T));
+  const int n = H.lev[0].n, N = (int)H.lev[0].N;
+  const long long off = (long long)sys * N;
+  T bv[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) bv[u] = b[off + min((int)threadIdx.x + kCoarseThreads * u, N - 1)];
+  for (int i = threadIdx.x; i < elems; i += kCoarseThreads) sm[i] = T(0);
   const T s = shift[sys];
-  const int nthr = blockDim.x;
-  const LevelDev<T>& L0 = H.lev[0];
-  T* X0 = sm + H.off[0];
-  T* B0 = X0 + L0.N;
-  for (int p = threadIdx.x; p < L0.N; p += nthr) {
-    B0[p] = b[(long long)sys * L0.N + p];
-    X0[p] = T(0);
-  }
   __syncthreads();
-  for (int cyc = 0; cyc < H.cycles; ++cyc) {
-    for (int l = 0; l + 1 < H.nlev; ++l) {
-      const LevelDev<T>& Lf = H.lev[l];
-      const LevelDev<T>& Lc = H.lev[l + 1];
-      T* X = sm + H.off[l];
-      T* B = X + Lf.N;
-      T* Tm = B + Lf.N;
-      lds_smooth<T, DIM, VAR>(Lf, X, B, Tm, s, H.omega, H.nu, &H.pre, false);
-      // residual on the fine level into Tm, then full weighting into B_c
-      const float rf = 1.0f / (float)Lf.n, rc = 1.0f / (float)Lc.n;
-      for (int p = threadIdx.x; p < Lf.N; p += nthr) {
-        int i, j, k;
-        ijk_of<DIM>(p, Lf.n, rf, i, j, k);
-        Tm[p] = B[p] - apply_pt<T, DIM, VAR>(Lf, X, i, j, k, p, s, nullptr);
-      }
-      __syncthreads();
-      T* Xc = sm + H.off[l + 1];
-      T* Bc = Xc + Lc.N;
-      const T wt[3] = {T(0.25), T(0.5), T(0.25)};
-      for (int p = threadIdx.x; p < Lc.N; p += nthr) {
-        int I, J, K;
-        ijk_of<DIM>(p, Lc.n, rc, I, J, K);
-        T acc = T(0);
-        for (int dk = (DIM == 3 ? -1 : 0); dk <= (DIM == 3 ? 1 : 0); ++dk) {
-          const int fk = DIM == 3 ? 2 * K + 1 + dk : 0;
-          const T wk = DIM == 3 ? wt[dk + 1] : T(1);
-          for (int dj = -1; dj <= 1; ++dj)
-            for (int di = -1; di <= 1; ++di)
-              acc += wk * wt[dj + 1] * wt[di + 1] * Tm[((long long)fk * Lf.n + 2 * J + 1 + dj) * Lf.n + 2 * I + 1 + di];
-        }
-        Bc[p] = acc;
-        Xc[p] = T(0);
-      }
-      __syncthreads();
-    }
-    {  // bottom level
-      const int l = H.nlev - 1;
-      const LevelDev<T>& Lb = H.lev[l];
-      T* X = sm + H.off[l];
-      T* B = X + Lb.N;
-      T* Tm = B + Lb.N;
-      if (Lb.N == 1) {
-        if (threadIdx.x == 0) X[0] = B[0] / diag_pt<T, DIM, VAR>(Lb, 0, 0, 0, s);
-        __syncthreads();
-      } else {
-        lds_smooth<T, DIM, VAR>(Lb, X, B, Tm, s, H.omega, H.bottom_sweeps);
-      }
-    }
-    for (int l = H.nlev - 2; l >= 0; --l) {
-      const LevelDev<T>& Lf = H.lev[l];
-      const LevelDev<T>& Lc = H.lev[l + 1];
-      T* X = sm + H.off[l];
-      T* B = X + Lf.N;
-      T* Tm = B + Lf.N;
-      const T* Xc = sm + H.off[l + 1];
-      const float rf = 1.0f / (float)Lf.n;
-      for (int p = threadIdx.x; p < Lf.N; p += nthr) {
-        int i, j, k;
-        ijk_of<DIM>(p, Lf.n, rf, i, j, k);
-        X[p] += interp_pt<T, DIM>(Xc, Lc.n, i, j, k);
-      }
-      __syncthreads();
-      lds_smooth<T, DIM, VAR>(Lf, X, B, Tm, s, H.omega, H.nu, &H.pre, true);
+  const T* X = lds_cycle<T, DIM, VAR, PER, 0>(H, sm, s, bv);
+  const float rn = 1.0f / (float)n;
+  const int S1 = n + 2;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int p = threadIdx.x + kCoarseThreads * u;
+    if (p < N) {
+      int i, j, k;
+      ijk_of<DIM>(p, n, rn, i, j, k);
+      x[off + p] = X[((DIM == 3 ? k + 1 : 0) * S1 + j + 1) * S1 + i + 1];
     }
   }
-  for (int p = threadIdx.x; p < L0.N; p += nthr) x[(long long)sys * L0.N + p] = X0[p];
 }
 
 // --------------------------------------------------------------------------
@@ -3694,12 +3780,24 @@ template <typename T>
 void Launch<T>::coarse_solve(int dim, bool var, const LdsHierarchy<T>& H, const T* b, T* x, const T* shift,
                              const int* active, int nsys, size_t lds_bytes, hipStream_t st,
                              unsigned long long* ctr) {
-  // 512 threads: the coarsest levels have few points per thread (63^2 has 8
-  // at 512), and two workgroups per CU fit the LDS either way; against 1024
-  // threads the 511^2 solve ran 0.8 % faster
-  const dim3 g(nsys), blk(512);
-#define K_CO(D, V, dummy) hipLaunchKernelGGL((k_coarse<T, D, V>), g, blk, lds_bytes, st, H, b, x, shift, active, ctr)
-  BURA_DISPATCH_DV(dim, var, K_CO, 0);
+  const int per = (int)((H.lev[0].N + kCoarseThreads - 1) / kCoarseThreads);
+  const int elems = (int)(lds_bytes / sizeof(T));
+#define K_CO(D, V, P)                                                                                            \
+  do {                                                                                                           \
+    auto* kern = k_coarse<T, D, V, P>;                                                                           \
+    if (lds_bytes > 64 * 1024)                                                                                   \
+      (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);  \
+    hipLaunchKernelGGL(kern, dim3(nsys), dim3(kCoarseThreads), lds_bytes, st, H, b, x, shift, active, ctr, elems); \
+  } while (0)
+#define K_COP(D, V, dummy)     \
+  do {                         \
+    if (per <= 1) K_CO(D, V, 1); \
+    else if (per == 2) K_CO(D, V, 2); \
+    else if (per <= 4) K_CO(D, V, 4); \
+    else K_CO(D, V, 6);        \
+  } while (0)
+  BURA_DISPATCH_DV(dim, var, K_COP, 0);
+#undef K_COP
 #undef K_CO
 }
 
