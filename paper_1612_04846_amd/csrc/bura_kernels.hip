@@ -76,7 +76,7 @@ struct Column {
   int i, j, k0, k1;   // the thread's first column (i, j) (rows j .. j + rows - 1) and its planes [k0, k1)
 };
 
-__device__ __forceinline__ Column march_column(const Tile& tl, int n, int rows) {
+__device__ __forceinline__ Column march_column(const Tile& tl, int n, int rows, int planes = kMarchZ) {
   Column c;
   // the workgroup's shape is chosen per grid (march_x on the host)
   const int my = blockDim.y;
@@ -84,8 +84,8 @@ __device__ __forceinline__ Column march_column(const Tile& tl, int n, int rows) 
   const int kc = tl.y / yt;
   c.i = tl.x * blockDim.x + threadIdx.x;
   c.j = ((tl.y - kc * yt) * my + threadIdx.y) * rows;
-  c.k0 = kc * kMarchZ;
-  c.k1 = min(c.k0 + kMarchZ, n);
+  c.k0 = kc * planes;
+  c.k1 = min(c.k0 + planes, n);
   return c;
 }
 
@@ -341,21 +341,21 @@ __global__ __launch_bounds__(kBlock) void k_jacobi(LevelDev<T> L, const T* __res
   }
 }
 
-// k_jacobi in 3D, marching along z (one workgroup per kMarchZ planes,
+// k_jacobi in 3D, marching along z (one workgroup per `planes` planes,
 // kMarchRows rows per thread).
 template <typename T, bool VAR, bool ZERO, bool DOT>
 __global__ __launch_bounds__(kBlock) void k_jacobi3(LevelDev<T> L, const T* __restrict__ b,
                                                     const T* __restrict__ xin, T* __restrict__ xout,
                                                     const T* __restrict__ shift, const int* __restrict__ active,
                                                     T omega, double* __restrict__ partial,
-                                                    unsigned long long* __restrict__ ctr, Fin fin) {
+                                                    unsigned long long* __restrict__ ctr, Fin fin, int planes) {
   constexpr int R = kMarchRows;
   const Tile tl = block_tile();
   const int sys = tl.z;
   if (!active[sys]) return;
   count_bytes_tile(tl, ctr, (unsigned long long)L.N * sizeof(T) * ((ZERO ? 2 : 3) + (VAR && sys == 0 ? 3 : 0)));
   const int n = L.n;
-  const Column c = march_column(tl, n, R);
+  const Column c = march_column(tl, n, R, planes);
   double dot = 0.0;
   if (c.i < n && c.j < n) {
     const long long off = (long long)sys * L.N, nn = (long long)n * n;
@@ -666,19 +666,19 @@ __device__ __forceinline__ void axis_pair(int f, int nc, int& a, int& b, T& wa, 
   }
 }
 
-// x_f += P x_c: one thread per fine column (i, j) over kMarchZ fine planes.  The
+// x_f += P x_c: one thread per fine column (i, j) over `planes` (even) fine planes.  The
 // in-plane interpolant of each coarse plane is formed once and kept for the
 // two or three fine planes that use it.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_prolong3(LevelDev<T> Lc, LevelDev<T> Lf, const T* __restrict__ xc,
                                                      T* __restrict__ xf, const int* __restrict__ active,
-                                                     unsigned long long* __restrict__ ctr) {
+                                                     unsigned long long* __restrict__ ctr, int planes) {
   const Tile tl = block_tile();
   const int sys = tl.z;
   if (!active[sys]) return;
   count_bytes_tile(tl, ctr, (unsigned long long)Lf.N * sizeof(T) * 2 + (unsigned long long)Lc.N * sizeof(T));
   const int nf = Lf.n, nc = Lc.n;
-  const Column c = march_column(tl, nf, 1);
+  const Column c = march_column(tl, nf, 1, planes);
   if (c.i >= nf || c.j >= nf) return;
   int ia, ib, ja, jb;
   T wia, wib, wja, wjb;
@@ -715,7 +715,7 @@ __global__ __launch_bounds__(kBlock) void k_prolong3(LevelDev<T> Lc, LevelDev<T>
 }
 
 // b_c = R (b - (A+s) x) in 3D.  A workgroup owns kRcx x kRcy coarse columns over
-// kMarchZ coarse planes, i.e. the (2 kRcx + 1) x (2 kRcy + 1) fine columns under
+// `planes` coarse planes, i.e. the (2 kRcx + 1) x (2 kRcy + 1) fine columns under
 // them.  Plane by plane, each fine point's residual is formed once and put in
 // LDS; each coarse column then takes the weighted 3 x 3 sum of its plane, and
 // the weighted sums of fine planes 2K, 2K+1, 2K+2 give coarse plane K (plane
@@ -737,7 +737,7 @@ template <typename T, bool VAR>
 __global__ __launch_bounds__(256) void k_restrict3(LevelDev<T> Lf, LevelDev<T> Lc, const T* __restrict__ b,
                                                    const T* __restrict__ x, T* __restrict__ bc,
                                                    const T* __restrict__ shift, const int* __restrict__ active,
-                                                   unsigned long long* __restrict__ ctr) {
+                                                   unsigned long long* __restrict__ ctr, int planes) {
   constexpr int PER = (kRfn + 255) / 256;
   __shared__ T rb[kRfn];
   __shared__ T xt[kRhn];
@@ -749,7 +749,7 @@ __global__ __launch_bounds__(256) void k_restrict3(LevelDev<T> Lf, LevelDev<T> L
   const int yt = (nc + kRcy - 1) / kRcy;
   const int kc = tl.y / yt;
   const int I0 = tl.x * kRcx, J0 = (tl.y - kc * yt) * kRcy;
-  const int K0 = kc * kMarchZ, K1 = min(K0 + kMarchZ, nc);
+  const int K0 = kc * planes, K1 = min(K0 + planes, nc);
   const int tid = threadIdx.x;
   const T s = shift[sys];
   const T* bs = b + (long long)sys * Lf.N;
@@ -3621,12 +3621,32 @@ static inline dim3 point_grid(int dim, int n, int nsys) {
 static inline int march_x(int n) { return n >= 192 ? 256 : (n >= 96 ? 128 : 64); }
 static inline dim3 march_block(int n) { return dim3(march_x(n), kBlock / march_x(n)); }
 
-static inline dim3 march_grid(int n, int nsys, int rows) {
+// Planes per workgroup of a marching launch with `tiles` workgroups per layer
+// of planes (over all its systems): kMarchZ, halved while that leaves fewer
+// than 8 workgroups per CU.  A workgroup walks its planes one memory latency at
+// a time, so on the coarse levels of a few systems 8 planes are 8 - 28 us
+// whatever the grid (127^3, 9 systems, variable coefficients, on its 63^3 and
+// 31^3 levels: sweeps 9.6 and 8.1 -> 7.2 and 4.8 us, sweeps from zero 20 and 17
+// -> under 8, restrictions 23 and 24 -> 15 and 8); shorter walks read their
+// first and last plane again.  Only for kernels that write no partials: those
+// are grouped by kMarchZ, whatever else shares the launch.
+static inline int march_planes(int n, long long tiles, int least) {
+  int mz = kMarchZ;
+  while (mz > least && tiles * ((n + mz - 1) / mz) < 2048) mz /= 2;
+  return mz;
+}
+
+static inline dim3 march_grid(int n, int nsys, int rows, int planes = kMarchZ) {
   const int mx = march_x(n), my = kBlock / mx;
   const int xt = (n + mx - 1) / mx;
   const int yt = (n + my * rows - 1) / (my * rows);
-  const int zt = (n + kMarchZ - 1) / kMarchZ;
+  const int zt = (n + planes - 1) / planes;
   return dim3(xt, yt * zt, nsys);
+}
+
+static inline long long march_tiles(int n, int nsys, int rows) {
+  const int mx = march_x(n), my = kBlock / mx;
+  return (long long)((n + mx - 1) / mx) * ((n + my * rows - 1) / (my * rows)) * nsys;
 }
 
 // the smoothing sweeps, the stencil product and the FP64 residual (the kernels
@@ -3701,13 +3721,16 @@ template <typename T>
 void Launch<T>::jacobi(int dim, bool var, const LevelDev<T>& L, const T* b, const T* xin, T* xout, const T* shift,
                        const int* active, T omega, bool zero_guess, double* partial, int nsys, hipStream_t st,
                        unsigned long long* ctr, Fin fin) {
-  const dim3 g = stencil_grid(dim, L.n, nsys), blk = stencil_block(dim, L.n);
   const bool dot = partial != nullptr;
+  // (a sweep from zero reads no other plane, so it may take them one by one)
+  const int mz = dim == 3 && !dot ? march_planes(L.n, march_tiles(L.n, nsys, kMarchRows), zero_guess ? 1 : 2) : kMarchZ;
+  const dim3 g = dim == 3 ? march_grid(L.n, nsys, kMarchRows, mz) : stencil_grid(dim, L.n, nsys);
+  const dim3 blk = stencil_block(dim, L.n);
 #define K_JAC(D, V, Z, DT)                                                                                      \
   do {                                                                                                          \
     if (D == 3)                                                                                                 \
       hipLaunchKernelGGL((k_jacobi3<T, V, Z, DT>), g, blk, 0, st, L, b, xin, xout, shift, active, omega, partial, \
-                         ctr, fin);                                                                             \
+                         ctr, fin, mz);                                                                         \
     else                                                                                                        \
       hipLaunchKernelGGL((k_jacobi<T, 2, V, Z, DT>), g, blk, 0, st, L, b, xin, xout, shift, active, omega,       \
                          partial, ctr, fin);                                                                    \
@@ -3754,9 +3777,11 @@ void Launch<T>::restrict_residual(int dim, bool var, const LevelDev<T>& Lf, cons
                                   unsigned long long* ctr) {
   if (dim == 3) {
     const int nc = Lc.n;
-    const dim3 g3((nc + kRcx - 1) / kRcx, ((nc + kRcy - 1) / kRcy) * ((nc + kMarchZ - 1) / kMarchZ), nsys);
-    if (var) hipLaunchKernelGGL((k_restrict3<T, true>), g3, dim3(256), 0, st, Lf, Lc, b, x, bc, shift, active, ctr);
-    else hipLaunchKernelGGL((k_restrict3<T, false>), g3, dim3(256), 0, st, Lf, Lc, b, x, bc, shift, active, ctr);
+    const int xt = (nc + kRcx - 1) / kRcx, yt = (nc + kRcy - 1) / kRcy;
+    const int mz = march_planes(nc, (long long)xt * yt * nsys, 1);
+    const dim3 g3(xt, yt * ((nc + mz - 1) / mz), nsys);
+    if (var) hipLaunchKernelGGL((k_restrict3<T, true>), g3, dim3(256), 0, st, Lf, Lc, b, x, bc, shift, active, ctr, mz);
+    else hipLaunchKernelGGL((k_restrict3<T, false>), g3, dim3(256), 0, st, Lf, Lc, b, x, bc, shift, active, ctr, mz);
     return;
   }
   const dim3 g = point_grid(dim, Lc.n, nsys), blk(kTileX, kTileY);
@@ -3771,9 +3796,11 @@ void Launch<T>::prolong_add(int dim, const LevelDev<T>& Lc, const LevelDev<T>& L
   if (dim == 2)
     hipLaunchKernelGGL((k_prolong<T, 2>), point_grid(2, Lf.n, nsys), dim3(kTileX, kTileY), 0, st, Lc, Lf, xc, xf,
                        active, ctr);
-  else
-    hipLaunchKernelGGL((k_prolong3<T>), march_grid(Lf.n, nsys, 1), march_block(Lf.n), 0, st, Lc, Lf, xc, xf,
-                       active, ctr);
+  else {
+    const int mz = march_planes(Lf.n, march_tiles(Lf.n, nsys, 1), 2);
+    hipLaunchKernelGGL((k_prolong3<T>), march_grid(Lf.n, nsys, 1, mz), march_block(Lf.n), 0, st, Lc, Lf, xc, xf,
+                       active, ctr, mz);
+  }
 }
 
 template <typename T>
