@@ -176,6 +176,8 @@ struct bura_plan_s {
   unsigned int* d_cnt = nullptr;       // per-system block counters for the folded updates
   hipStream_t user_stream = nullptr;   // caller's stream (opts.stream)
   hipEvent_t join_ev = nullptr;
+  unsigned* h_seq = nullptr;           // pinned: the last report the device has written (nullptr: none, copies instead)
+  unsigned seq = 0;                    // the last report asked for
   void* h_state = nullptr;             // pinned mirror of the scalar state for reports
   double run_tol = 0.0;                // stopping tolerance of the solve in progress
   // a posteriori error bound (see do_solve): a guaranteed lower bound of the
@@ -857,15 +859,57 @@ SysState state_at(const bura_plan_t P, size_t sys0) {
   return s;
 }
 
+// Reports come through pinned memory (a kernel writes them and then a sequence
+// number): a wait for that number returns 5 - 10 us earlier than a copy and a
+// stream synchronisation.  Not while profiling, whose events have to be
+// complete too.
+bool reports(const bura_plan_t P) { return P->h_seq && !P->prof.on; }
+
+// The largest report that one workgroup writes out; a copy takes over where
+// the stores to the host (about 20 GB/s) would take longer than it saves.
+constexpr size_t kReportBytes = 128 << 10;
+
+// Wait until report P->seq has arrived.  Spins for a few milliseconds, then
+// waits for the stream (which also returns what went wrong there).
+int wait_report(bura_plan_t P) {
+  volatile unsigned* seq = P->h_seq;
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int i = 1; *seq != P->seq; ++i) {
+    if ((i & 255) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(4)) {
+      HIPCHK(hipStreamSynchronize(P->stream));
+      if (*seq != P->seq) return BURA_EDEVICE;
+      break;
+    }
+  }
+  std::atomic_thread_fence(std::memory_order_acquire);
+  return BURA_OK;
+}
+
 int count_active(bura_plan_t P, const int* dev_flags, size_t sys0, int nsys) {
-  if (hipMemcpyAsync(P->h_flags, dev_flags + sys0, nsys * sizeof(int), hipMemcpyDeviceToHost, P->stream) !=
-      hipSuccess)
-    return -1;
-  if (hipStreamSynchronize(P->stream) != hipSuccess) return -1;
-  prof_flush(P);
+  if (reports(P)) {
+    launch_report_flags(dev_flags + sys0, nsys, P->h_flags, P->h_seq, ++P->seq, P->stream);
+    if (hipGetLastError() != hipSuccess || wait_report(P)) return -1;
+  } else {
+    if (hipMemcpyAsync(P->h_flags, dev_flags + sys0, nsys * sizeof(int), hipMemcpyDeviceToHost, P->stream) !=
+        hipSuccess)
+      return -1;
+    if (hipStreamSynchronize(P->stream) != hipSuccess) return -1;
+    prof_flush(P);
+  }
   int c = 0;
   for (int i = 0; i < nsys; ++i) c += P->h_flags[i] != 0;
   return c;
+}
+
+// Order the plan's stream after the caller's pending work; nothing to do where
+// there is none (the event and the wait for it are 12 - 20 us of a solve).
+int join_caller(bura_plan_t P) {
+  if (!P->join_ev) return BURA_OK;
+  if (hipStreamQuery(P->user_stream) == hipSuccess) return BURA_OK;
+  (void)hipGetLastError();
+  HIPCHK(hipEventRecord(P->join_ev, P->user_stream));
+  HIPCHK(hipStreamWaitEvent(P->stream, P->join_ev, 0));
+  return BURA_OK;
 }
 
 // PCG on systems [sys0, sys0+nsys): r holds b, x holds 0, OP_INIT done.
@@ -1065,8 +1109,11 @@ int finish_batch(bura_plan_t P, const double* f, int nrhs, size_t sys0, int nsys
 
 // Solve the active systems [sys0, sys0 + nsys) directly (x = 0 where that does
 // not apply), test their residuals and, with comb != nullptr, combine them.
-// R: right-hand sides per term in the system order.
-void direct_batch(bura_plan_t P, const double* f, int R, size_t sys0, int nsys, const Combine* comb) {
+// R: right-hand sides per term in the system order.  begin: this is the solve's
+// first launch (see launch_start).  test false: the residuals' partials are
+// left to launch_conclude.
+void direct_batch(bura_plan_t P, const double* f, int R, size_t sys0, int nsys, const Combine* comb,
+                  const SlotUpload* begin, bool test) {
   hipStream_t st = P->stream;
   const bool mixed = P->opts.precision == BURA_MIXED;
   const size_t o = sys0 * (size_t)P->N;
@@ -1089,7 +1136,7 @@ void direct_batch(bura_plan_t P, const double* f, int R, size_t sys0, int nsys, 
     ProfScope ps(P, BURA_K_DIRECT);
     launch_sine_forward(s, st, ps.ctr, P->d_fpart);
     launch_start(mixed ? OP_START : OP_INIT, P->d_fpart, sine_norm_blocks(P->dim, P->n, s.nrhs), R, nsys, S,
-                 P->d_gate + sys0, P->run_tol, st);
+                 P->d_gate + sys0, P->run_tol, st, begin, P->run_nrhs);
     launch_sine_back(s, st, ps.ctr);
   }
   {
@@ -1116,6 +1163,7 @@ void direct_batch(bura_plan_t P, const double* f, int R, size_t sys0, int nsys, 
     }
     launch_check(P->dim, c, comb ? comb->t : CombineTerms{}, comb ? comb->nout : 1, nsys, st);
   }
+  if (!test) return;
   ProfScope ps(P, BURA_K_OTHER);
   const int nb = check_blocks(P->dim, P->n);
   S.started = 1;
@@ -1293,13 +1341,14 @@ int upload_slots(bura_plan_t P, int nrhs, const SlotTerms& t) {
   return BURA_OK;
 }
 
-void combine_batch(bura_plan_t P, size_t sys0, int R, const Combine& c) {
+// sum false: the norms' partials (combine_blocks per row) are left to launch_conclude
+void combine_batch(bura_plan_t P, size_t sys0, int R, const Combine& c, bool sum = true) {
   const double* x = (P->opts.precision == BURA_MIXED ? P->x64 : P->w64.x) + sys0 * (size_t)P->N;
   const bool pend = combine_finishes_x(P);   // plans without stages: sys0 = 0
   ProfScope ps(P, BURA_K_COMBINE);
   launch_combine(P->N, x, c.w, c.t, c.nout, c.nrhs, R, c.u, P->stream, ps.ctr, c.base, c.base_w, c.wsys,
                  pend ? P->w64.p : nullptr, pend ? P->w64.p2 : nullptr, P->st.alpha, P->st.iters,
-                 c.norms ? P->d_upart : nullptr, P->d_unorm);
+                 c.norms ? P->d_upart : nullptr, sum ? P->d_unorm : nullptr);
 }
 
 int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t* rep,
@@ -1319,25 +1368,19 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
   int rc;
   // the plan works on its own stream, ordered after the caller's pending work
   // (a static-workspace plan runs on the caller's stream itself)
-  if (P->join_ev) {
-    HIPCHK(hipEventRecord(P->join_ev, P->user_stream));
-    HIPCHK(hipStreamWaitEvent(P->stream, P->join_ev, 0));
-  }
+  if ((rc = join_caller(P))) return rc;
   // the scalar state and the used systems, with a slot solve's terms
-  auto begin = [&]() {
-    SlotUpload up{};
-    if (slot) {
-      up.staged = P->d_slot;
-      up.w = P->d_wsys;
-      up.s64 = P->d_shift64;
-      up.s64b = mixed ? nullptr : P->w64.shift;
-      up.s32 = mixed ? P->w32.shift : nullptr;
-      up.tol = P->d_tol;
-    }
-    launch_begin(P->st, (int)S_used, R, nrhs, up, P->stream);
-  };
+  SlotUpload up{};
+  if (slot) {
+    up.staged = P->d_slot;
+    up.w = P->d_wsys;
+    up.s64 = P->d_shift64;
+    up.s64b = mixed ? nullptr : P->w64.shift;
+    up.s32 = mixed ? P->w32.shift : nullptr;
+    up.tol = P->d_tol;
+  }
+  auto begin = [&]() { launch_begin(P->st, (int)S_used, R, nrhs, up, P->stream); };
   if (slot && (rc = upload_slots(P, nrhs, *slot))) return rc;
-  begin();
   // A solve that the direct solution starts is queued to its end without
   // waiting for the residual test, whose flags come back with the report; the
   // systems still active then iterate and the combine runs again.  The stages
@@ -1356,16 +1399,25 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
     return mixed ? solve_batch_mixed(P, rhs, R, sys0, nsys) : solve_batch_fp64(P, rhs, R, sys0, nsys);
   };
   const bool direct = starts_direct(P);
+  // a direct solve of all systems at once: its first launch on the state is
+  // launch_start, its last one launch_conclude (while one workgroup is enough
+  // for the sums)
+  const bool whole = direct && P->stages.empty() && P->opts.schedule != BURA_PER_POLE;
+  const bool conclude = whole && spec && reports(P) && (long long)S_used * check_blocks(P->dim, P->n) <= 32768 &&
+                        S_used <= kReportBytes / 128;
+  int unblk = 0;   // conclude: partials per output row
+  if (!whole) begin();
   // a batch that starts from the direct solution: with its combine in the pass
   // of the residual test where nothing waits for that test
   auto batch_direct = [&](const double* rhs, size_t sys0, int nsys, const Combine* c) -> int {
     const bool fuse = spec && c && check_combines(P->dim, P->n, c->nout * c->nrhs);
-    direct_batch(P, rhs, R, sys0, nsys, fuse ? c : nullptr);
+    direct_batch(P, rhs, R, sys0, nsys, fuse ? c : nullptr, whole ? &up : nullptr, !conclude);
     HIPCHK(hipGetLastError());
     if (!spec) {
       if (const int rc = finish_batch(P, rhs, R, sys0, nsys)) return rc;
     }
-    if (c && !fuse) combine_batch(P, sys0, R, *c);
+    if (c && !fuse) combine_batch(P, sys0, R, *c, !conclude);
+    unblk = fuse ? check_blocks(P->dim, P->n) : combine_blocks(P->N);
     return BURA_OK;
   };
   const double* xsol = mixed ? P->x64 : P->w64.x;
@@ -1432,9 +1484,21 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
   };
   // report: one copy of the per-system scalar state, the refinement's residuals
   // and the output norms (one block on the device too)
+  bool fetched = false;
   auto fetch = [&]() -> int {
-    HIPCHK(hipMemcpyAsync(P->h_state, P->state_block, sb + S * 8 + (size_t)rows * 8, hipMemcpyDeviceToHost,
-                          P->stream));
+    const size_t bytes = sb + S * 8 + (size_t)rows * 8;
+    if (reports(P) && (conclude || bytes <= kReportBytes)) {
+      SysState Ss = P->st;
+      Ss.started = 1;
+      const bool sums = conclude && !fetched;
+      fetched = true;
+      launch_conclude(!sums ? -1 : mixed ? OP_OUTER : OP_RESTART, P->partial, check_blocks(P->dim, P->n), (int)S_used,
+                      Ss, P->run_tol, mixed ? P->opts.max_outer : P->opts.max_iter, P->d_upart, unblk, sums ? rows : 0,
+                      P->d_unorm, P->state_block, bytes, P->h_state, P->h_seq, ++P->seq, P->stream);
+      HIPCHK(hipGetLastError());
+      return wait_report(P);
+    }
+    HIPCHK(hipMemcpyAsync(P->h_state, P->state_block, bytes, hipMemcpyDeviceToHost, P->stream));
     HIPCHK(hipStreamSynchronize(P->stream));
     prof_flush(P);
     return BURA_OK;
@@ -2046,9 +2110,11 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
     P->h_state = P->host_mirror.data();
     P->h_flags = (int*)(P->host_mirror.data() + state_mirror);
   } else {
-    if (hipHostMalloc((void**)&P->h_flags, S * sizeof(int), hipHostMallocDefault) != hipSuccess)
+    if (hipHostMalloc((void**)&P->h_flags, S * sizeof(int), hipHostMallocCoherent) != hipSuccess)
       return fail(BURA_ENOMEM);
-    if (hipHostMalloc(&P->h_state, state_mirror, hipHostMallocDefault) != hipSuccess) return fail(BURA_ENOMEM);
+    if (hipHostMalloc(&P->h_state, state_mirror + 8, hipHostMallocCoherent) != hipSuccess) return fail(BURA_ENOMEM);
+    P->h_seq = (unsigned*)((char*)P->h_state + state_mirror);
+    *P->h_seq = 0;
   }
   if (o.autotune && !(P->direct && o.tol <= kDirectTol)) {
     if (hipStreamSynchronize(P->stream) != hipSuccess) return fail(BURA_EDEVICE);

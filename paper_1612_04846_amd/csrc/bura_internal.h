@@ -197,9 +197,33 @@ constexpr double kDirectTol = 1e-6;
 // sum the partials of |f|^2 of each system's right-hand side s % R, apply op
 // (OP_INIT or OP_START) and set its gate (see SineSolve): 1 where the direct
 // solution is wanted, 2 where x = 0 is (a zero or non-finite right-hand side,
-// or a tolerance over kDirectTol), 0 for a system that is not active.
+// or a tolerance over kDirectTol), 0 for a system that is not active.  With
+// begin != nullptr this is also the solve's launch_begin (of nrhs right-hand
+// sides; all its systems in one batch).
+// The state at the start of a solve: flags and counters 0, no deferred update
+// pending, the used systems active (system j R + r for r < nrhs).  A slot
+// solve's terms come in one upload, staged = [S] weights, shifts, tolerances
+// (double), shifts (float), used flags (int), and go to
+// their arrays here.
+struct SlotUpload {
+  const double* staged = nullptr;
+  double* w = nullptr;
+  double* s64 = nullptr;
+  double* s64b = nullptr;   // FP64 plans: the PCG's copy of the shifts
+  float* s32 = nullptr;     // MIXED
+  double* tol = nullptr;
+};
 void launch_start(int op, const double* partial, int nblk, int R, int nsys, const SysState& S, int* gate, double tol,
-                  hipStream_t st);
+                  hipStream_t st, const SlotUpload* begin = nullptr, int nrhs = 0);
+
+// The last launch of a solve: op (unless < 0) on the systems' partials, the
+// output norms (rows of unblk partials), then `bytes` of the state to pinned
+// host memory and the sequence number seq behind it.
+void launch_conclude(int op, const double* partial, int nblk, int nsys, const SysState& S, double tol, int max_iter,
+                     const double* upartial, int unblk, int rows, double* unorm, const void* state, size_t bytes,
+                     void* host, unsigned* host_seq, unsigned seq, hipStream_t st);
+// n flags to pinned host memory and the sequence number behind them
+void launch_report_flags(const int* flags, int n, int* host, unsigned* host_seq, unsigned seq, hipStream_t st);
 
 // The residual test of a direct solution and the combine in one pass over x:
 // partial[s] = block partials of |f - (A + shift_s) x_s|^2 of the active systems
@@ -290,18 +314,6 @@ void launch_merge_init(int* init, int* active64, int n, hipStream_t st);
 // dst = src, 16-byte aligned, non-overlapping (counter calibration)
 void launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
 void launch_fill_int(int* p, long long n, int v, hipStream_t st);
-// The state at the start of a solve: flags and counters 0, no deferred update
-// pending, the used systems active (system j R + r for r < nrhs).  A slot
-// solve's terms come in one upload, staged = [S] weights, shifts, tolerances
-// (double), shifts (float), used flags (int), and go to their arrays here.
-struct SlotUpload {
-  const double* staged = nullptr;
-  double* w = nullptr;
-  double* s64 = nullptr;
-  double* s64b = nullptr;   // FP64 plans: the PCG's copy of the shifts
-  float* s32 = nullptr;     // MIXED
-  double* tol = nullptr;
-};
 void launch_begin(const SysState& S, int nsys, int R, int nrhs, const SlotUpload& up, hipStream_t st);
 
 int stencil_blocks(int dim, int n);   // blocks per system of a stencil launch (tile grid)

@@ -3584,12 +3584,54 @@ __global__ __launch_bounds__(256) void k_scalars(int op, const double* __restric
   apply_op(op, tot, S, sys, tol, max_iter);
 }
 
-// One block per system: see launch_start.
+// The scalar state of system i at the start of a solve: counters and flags
+// cleared, no iterate update pending, the used systems active: system j R + r
+// for r < nrhs, or as the uploaded slot terms say, which are unpacked to the
+// per-system arrays.  Returns whether the system is used.
+__device__ __forceinline__ int begin_system(const SysState& S, int i, int nsys, int R, int nrhs,
+                                            const SlotUpload& up) {
+  S.flags[i] = 0;
+  S.total_iters[i] = 0;
+  S.outer[i] = 0;
+  S.alpha[i] = 0.0;
+  int on = (i % R) < nrhs;
+  if (up.staged) {
+    const double* h = up.staged;
+    up.w[i] = h[i];
+    up.s64[i] = h[nsys + i];
+    up.tol[i] = h[2 * nsys + i];
+    const float* h32 = reinterpret_cast<const float*>(h + 3 * (size_t)nsys);
+    if (up.s32) up.s32[i] = h32[i];
+    if (up.s64b) up.s64b[i] = h[nsys + i];
+    on = reinterpret_cast<const int*>(h32 + nsys)[i];
+  }
+  S.active[i] = on;
+  S.active64[i] = on;
+  return on;
+}
+
+// One block per system: see launch_start.  BEGIN: the solve's first launch on
+// the scalar state (begin_system of all nsys = gridDim.x systems).
+template <bool BEGIN>
 __global__ __launch_bounds__(256) void k_start(int op, const double* __restrict__ partial, int nblk, int R,
-                                               SysState S, int* __restrict__ gate, double tol) {
-  const int sys = blockIdx.x;
+                                               SysState S, int* __restrict__ gate, double tol, int nrhs,
+                                               SlotUpload up) {
+  const int sys = blockIdx.x, nsys = gridDim.x;
   const bool mixed = op == OP_START;
-  if (!(mixed ? S.active64 : S.active)[sys]) {
+  const double* per = mixed ? S.tol_outer : S.tol_pcg;
+  double stop = per ? per[sys] : tol;
+  int act;
+  if (BEGIN) {
+    act = (sys % R) < nrhs;
+    if (up.staged) {
+      act = reinterpret_cast<const int*>(reinterpret_cast<const float*>(up.staged + 3 * (size_t)nsys) + nsys)[sys];
+      stop = up.staged[2 * (size_t)nsys + sys];
+    }
+    if (threadIdx.x == 0) begin_system(S, sys, nsys, R, nrhs, up);
+  } else {
+    act = (mixed ? S.active64 : S.active)[sys];
+  }
+  if (!act) {
     if (threadIdx.x == 0) gate[sys] = 0;
     return;
   }
@@ -3598,8 +3640,51 @@ __global__ __launch_bounds__(256) void k_start(int op, const double* __restrict_
   const double tot = block_sum(v);
   if (threadIdx.x != 0) return;
   apply_op(op, tot, S, sys, tol, 0);
-  const double* per = mixed ? S.tol_outer : S.tol_pcg;
-  gate[sys] = tot > 0.0 && isfinite(tot) && (per ? per[sys] : tol) <= kDirectTol ? 1 : 2;
+  gate[sys] = tot > 0.0 && isfinite(tot) && stop <= kDirectTol ? 1 : 2;
+}
+
+// The end of a solve in one workgroup: op applied to every system (op < 0: none
+// is left to), the output norms summed, and the state handed to the host:
+// `words` doubles from `state` to pinned memory, then the sequence number that
+// the host waits for.  A wave sums a system's partials; for a few hundred
+// systems this is shorter than three launches and a copy, of 3 - 5 us each.
+__global__ __launch_bounds__(1024) void k_conclude(int op, const double* __restrict__ partial, int nblk, int nsys,
+                                                   SysState S, double tol, int max_iter,
+                                                   const double* __restrict__ upartial, int unblk, int rows,
+                                                   double* unorm, const double* state, int words, double* host,
+                                                   unsigned* host_seq, unsigned seq) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  auto wave_sum = [&](const double* p, int n) {
+    double v = 0.0;
+    for (int b = lane; b < n; b += 64) v += p[b];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+  };
+  if (op >= 0)
+    for (int s = wave; s < nsys; s += 16) {
+      if (!(op == OP_OUTER ? S.active64 : S.active)[s]) continue;
+      const double tot = wave_sum(partial + (size_t)s * nblk, nblk);
+      if (lane == 0) apply_op(op, tot, S, s, tol, max_iter);
+    }
+  for (int r = 15 - wave; r < rows; r += 16) {
+    const double tot = wave_sum(upartial + (size_t)r * unblk, unblk);
+    if (lane == 0) unorm[r] = tot;
+  }
+  __syncthreads();
+  for (int i = tid; i < words; i += 1024) host[i] = state[i];
+  __threadfence_system();
+  __syncthreads();
+  if (tid == 0) __hip_atomic_store(host_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// n flags to pinned memory, then the sequence number
+__global__ __launch_bounds__(1024) void k_report_flags(const int* __restrict__ flags, int n, int* host,
+                                                       unsigned* host_seq, unsigned seq) {
+  for (int i = threadIdx.x; i < n; i += 1024) host[i] = flags[i];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(host_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // --------------------------------------------------------------------------
@@ -4132,8 +4217,23 @@ void launch_residual_fp64(int dim, const LevelDev<double>& L, const double* f, c
 }
 
 void launch_start(int op, const double* partial, int nblk, int R, int nsys, const SysState& S, int* gate, double tol,
-                  hipStream_t st) {
-  hipLaunchKernelGGL(k_start, dim3(nsys), dim3(256), 0, st, op, partial, nblk, R, S, gate, tol);
+                  hipStream_t st, const SlotUpload* begin, int nrhs) {
+  if (begin)
+    hipLaunchKernelGGL(k_start<true>, dim3(nsys), dim3(256), 0, st, op, partial, nblk, R, S, gate, tol, nrhs, *begin);
+  else
+    hipLaunchKernelGGL(k_start<false>, dim3(nsys), dim3(256), 0, st, op, partial, nblk, R, S, gate, tol, nrhs,
+                       SlotUpload{});
+}
+
+void launch_conclude(int op, const double* partial, int nblk, int nsys, const SysState& S, double tol, int max_iter,
+                     const double* upartial, int unblk, int rows, double* unorm, const void* state, size_t bytes,
+                     void* host, unsigned* host_seq, unsigned seq, hipStream_t st) {
+  hipLaunchKernelGGL(k_conclude, dim3(1), dim3(1024), 0, st, op, partial, nblk, nsys, S, tol, max_iter, upartial,
+                     unblk, rows, unorm, (const double*)state, (int)(bytes / 8), (double*)host, host_seq, seq);
+}
+
+void launch_report_flags(const int* flags, int n, int* host, unsigned* host_seq, unsigned seq, hipStream_t st) {
+  hipLaunchKernelGGL(k_report_flags, dim3(1), dim3(1024), 0, st, flags, n, host, host_seq, seq);
 }
 
 bool residual_marches_rows(int dim, int n, long long nsys) { return residual_rows(dim, n, nsys); }
@@ -4177,7 +4277,7 @@ void launch_combine(long long N, const double* x, const double* w, const Combine
   const int nb = combine_blocks(N);
   hipLaunchKernelGGL(k_combine, dim3((unsigned)nb, nrhs, nout), dim3(256), 0, st, N, x, w, t, stride, u, base, base_w,
                      ctr, w_per_system ? 1 : 0, pa, pb, alpha, iters, partial);
-  if (partial) launch_row_sum(partial, nb, nout * nrhs, norms, st);
+  if (partial && norms) launch_row_sum(partial, nb, nout * nrhs, norms, st);
 }
 
 void launch_row_sum(const double* partial, int nblk, int rows, double* out, hipStream_t st) {
@@ -4247,30 +4347,9 @@ __global__ void k_fill_int(int* __restrict__ p, long long n, int v) {
   if (i < n) p[i] = v;
 }
 
-// The scalar state at the start of a solve, in one launch: counters and flags
-// cleared, no iterate update pending, and the used systems active: with up ==
-// nullptr system j R + r for r < nrhs, else as the uploaded slot terms say,
-// which are unpacked to the per-system arrays.
 __global__ __launch_bounds__(256) void k_begin(SysState S, int nsys, int R, int nrhs, SlotUpload up) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nsys) return;
-  S.flags[i] = 0;
-  S.total_iters[i] = 0;
-  S.outer[i] = 0;
-  S.alpha[i] = 0.0;
-  int on = (i % R) < nrhs;
-  if (up.staged) {
-    const double* h = up.staged;
-    up.w[i] = h[i];
-    up.s64[i] = h[nsys + i];
-    up.tol[i] = h[2 * nsys + i];
-    const float* h32 = reinterpret_cast<const float*>(h + 3 * (size_t)nsys);
-    if (up.s32) up.s32[i] = h32[i];
-    if (up.s64b) up.s64b[i] = h[nsys + i];
-    on = reinterpret_cast<const int*>(h32 + nsys)[i];
-  }
-  S.active[i] = on;
-  S.active64[i] = on;
+  if (i < nsys) begin_system(S, i, nsys, R, nrhs, up);
 }
 
 void launch_begin(const SysState& S, int nsys, int R, int nrhs, const SlotUpload& up, hipStream_t st) {

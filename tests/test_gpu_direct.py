@@ -196,3 +196,41 @@ def test_multigrid_counts_agree_where_the_damping_is_set():
         its.append(list(plan.solve(F).report.iters)[:6])
         plan.close()
     assert min(its[0]) >= 3 and all(abs(a - b) <= 1 for a, b in zip(*its))
+
+
+# one workgroup ends the solve (the smallest; 1020 systems), a copy does (more
+# systems; more partial sums), the general kernels start and end it (a pole at a time)
+REPORTS = [(2, 1, 1, "BATCHED"), (2, 15, 170, "BATCHED"), (2, 15, 256, "BATCHED"), (3, 63, 20, "BATCHED"),
+           (2, 255, 1, "BATCHED"), (2, 33, 3, "PER_POLE")]
+
+
+@pytest.mark.parametrize("dim,n,nrhs,schedule", REPORTS)
+def test_state_reaches_the_host_alike_on_every_way(dim, n, nrhs, schedule):
+    """The report of a solve as the device writes it, and as it is copied (what
+    a profiled solve does): the same solution, and sums that differ by the order
+    of at most 32768 terms, 2^-38; with the caller's stream busy and idle."""
+    B = _B()
+    b = oracle_coeffs(0.5, 5)
+    F = _dev(synth.normal_rhs(n, dim, nrhs=nrhs, tag=960 + n))
+    print(f"reports: dim={dim} n={n} nrhs={nrhs} {schedule}", flush=True)
+    plan = B.Plan(dim, n, weights=b.c_f64, shifts=[-x for x in b.d_f64], nrhs_max=nrhs, tol=1e-10,
+                  schedule=getattr(B, "BURA_" + schedule))
+    torch.cuda.synchronize()
+    idle = plan.solve(F)
+    G = torch.zeros_like(F)
+    for _ in range(50):   # work of the caller's that the solve has to wait for
+        G += F / 50
+    torch.cuda.synchronize()
+    G2 = torch.zeros_like(F)
+    for _ in range(50):
+        G2 += F / 50
+    busy, again = plan.solve(G2), plan.solve(G)
+    B.bura_plan_profile(plan.handle, 1)
+    copied = plan.solve(F)
+    assert np.array_equal(_host(idle.u), _host(copied.u))
+    assert np.array_equal(_host(busy.u), _host(again.u))
+    ra, rb = (np.array(list(r.report.relres)[:6]) for r in (idle, copied))
+    assert np.all(np.abs(ra - rb) <= 2.0 ** -38 * rb)
+    assert list(idle.report.iters)[:6] == list(copied.report.iters)[:6]
+    assert abs(idle.report.err_bound - copied.report.err_bound) <= 2.0 ** -37 * copied.report.err_bound
+    plan.close()
