@@ -20,8 +20,9 @@ constexpr int kSlots = 2;              // reduction slots per block
 constexpr int kMaxLdsLevels = 8;
 // the coarse solve: threads of its workgroup, the points a thread may own on
 // its first level (one on the levels below), and the LDS its iterates may take
+// (of 160 KiB: two padded FP64 iterates of 18^3, the largest in 6 points each)
 constexpr int kCoarseThreads = 1024, kCoarsePoints = 6;
-constexpr size_t kCoarseLds = 96 * 1024;
+constexpr size_t kCoarseLds = 128 * 1024;
 // Launch-shape variants of the 2D stencil-product and fused level kernels
 // (tile sizes in bura_kernels.hip); 0 is the default shape.
 constexpr int kTileVariants = BURA_TILE_VARIANTS;
