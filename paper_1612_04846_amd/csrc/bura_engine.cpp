@@ -178,6 +178,7 @@ struct bura_plan_s {
   hipEvent_t join_ev = nullptr;
   unsigned* h_seq = nullptr;           // pinned: the last report the device has written (nullptr: none, copies instead)
   unsigned seq = 0;                    // the last report asked for
+  Progress prog;                       // active systems after each PCG iteration (with h_seq)
   void* h_state = nullptr;             // pinned mirror of the scalar state for reports
   double run_tol = 0.0;                // stopping tolerance of the solve in progress
   // a posteriori error bound (see do_solve): a guaranteed lower bound of the
@@ -869,20 +870,32 @@ bool reports(const bura_plan_t P) { return P->h_seq && !P->prof.on; }
 // the stores to the host (about 20 GB/s) would take longer than it saves.
 constexpr size_t kReportBytes = 128 << 10;
 
-// Wait until report P->seq has arrived.  Spins for a few milliseconds, then
-// waits for the stream (which also returns what went wrong there).
-int wait_report(bura_plan_t P) {
-  volatile unsigned* seq = P->h_seq;
+// Wait until the pinned word(s) that arrived() looks at are there: spins for a
+// few milliseconds, then sleeps between looks.  Fails where the stream ends
+// without them, or with an error.
+template <typename F>
+int wait_host(bura_plan_t P, F arrived) {
   const auto t0 = std::chrono::steady_clock::now();
-  for (int i = 1; *seq != P->seq; ++i) {
-    if ((i & 255) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(4)) {
-      HIPCHK(hipStreamSynchronize(P->stream));
-      if (*seq != P->seq) return BURA_EDEVICE;
-      break;
+  for (unsigned i = 1; !arrived(); ++i) {
+    if ((i & 255) || std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(4)) continue;
+    const hipError_t e = hipStreamQuery(P->stream);
+    if (e == hipSuccess) {
+      if (arrived()) break;
+      return BURA_EDEVICE;
     }
+    if (e != hipErrorNotReady) HIPCHK(e);
+    (void)hipGetLastError();
+    std::this_thread::sleep_for(std::chrono::microseconds(20));
+    i |= 255;   // look at the stream after every sleep
+    i -= 1;
   }
   std::atomic_thread_fence(std::memory_order_acquire);
   return BURA_OK;
+}
+
+int wait_report(bura_plan_t P) {
+  const volatile unsigned* seq = P->h_seq;
+  return wait_host(P, [&]() { return *seq == P->seq; });
 }
 
 int count_active(bura_plan_t P, const int* dev_flags, size_t sys0, int nsys) {
@@ -925,9 +938,14 @@ int run_pcg(bura_plan_t P, Work<T>& W, size_t sys0, int nsys, double tol, int ma
   double* part = P->partial;
   const int nb_flat = flat_blocks(P->N);
   const int check = std::max(1, P->opts.check_every);
+  // The host watches every iteration's residual test and queues the next one
+  // while the rest of the V-cycle runs: no gap between iterations, and after
+  // the last one only that rest runs empty.  Without reports it looks once a
+  // chunk of iterations.
+  const bool watch = reports(P) && !P->fold;
   auto scal = [&](int op, int nblk) {
     ProfScope ps(P, BURA_K_OTHER);
-    launch_scalars(op, part, nblk, nsys, S, tol, max_iter, st);
+    launch_scalars(op, part, nblk, nsys, S, tol, max_iter, st, watch && op == OP_RESID ? P->prog : Progress());
   };
   T* pold = W.p + o;
   T* pnew = W.p2 + o;
@@ -975,11 +993,25 @@ int run_pcg(bura_plan_t P, Work<T>& W, size_t sys0, int nsys, double tol, int ma
   T* rnew = fx ? W.r2 + o : W.r + o;
   precondition<T>(P, W, sys0, nsys, S.active, part, fin(OP_BETA));
   if (!P->fold) scal(OP_BETA, rz_blocks(P));
-  // chunks of an even number of iterations, so p_old is W.p at every chunk start
-  const int chunk = std::max(2, check + (check & 1));
-  const int nchunks = max_iter / chunk + 1;
+  // chunks of an even number of iterations, so p_old is W.p at every chunk
+  // start; watched, an even and an odd iteration in turn, launched one kernel
+  // at a time (2 - 3 us each on the host, 4 us and more on the device: between
+  // graph launches the device stood idle for 8 us)
+  const int chunk = watch ? 1 : std::max(2, check + (check & 1));
+  const int nchunks = watch ? max_iter + 2 : max_iter / chunk + 1;
+  auto run_chunk = [&](int odd) {
+    T* a = odd ? pnew : pold;
+    T* b = odd ? pold : pnew;
+    T* ra = odd ? rnew : rold;
+    T* rb = odd ? rold : rnew;
+    for (int c = 0; c < chunk; ++c) {
+      body(a, b, ra, rb);
+      std::swap(a, b);
+      std::swap(ra, rb);
+    }
+  };
   bura_plan_s::Graph* g = nullptr;
-  if (P->use_graphs) {
+  if (P->use_graphs && !watch) {
     char key[160];
     std::snprintf(key, sizeof(key), "%zu/%zu/%d/%.17g/%d/%d", sizeof(T), sys0, nsys, tol, max_iter, chunk);
     auto it = P->graphs.find(key);
@@ -995,15 +1027,7 @@ int run_pcg(bura_plan_t P, Work<T>& W, size_t sys0, int nsys, double tol, int ma
       hipGraph_t graph = nullptr;
       bool ok = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) == hipSuccess;
       if (ok) {
-        T* a = pold;
-        T* b = pnew;
-        T* ra = rold;
-        T* rb = rnew;
-        for (int c = 0; c < chunk; ++c) {
-          body(a, b, ra, rb);
-          std::swap(a, b);
-          std::swap(ra, rb);
-        }
+        run_chunk(0);
         ok = hipStreamEndCapture(st, &graph) == hipSuccess && graph != nullptr && !P->capture_failed;
       }
       P->capturing = false;
@@ -1022,19 +1046,20 @@ int run_pcg(bura_plan_t P, Work<T>& W, size_t sys0, int nsys, double tol, int ma
       }
     }
   }
+  const volatile unsigned long long* prog = P->prog.host;
+  unsigned want = watch ? (unsigned)(*prog >> 32) : 0;
   for (int ch = 0; ch < nchunks; ++ch) {
-    if (g) {
+    if (g)
       HIPCHK(hipGraphLaunch(g->exec, st));
-    } else {
-      T* a = pold;
-      T* b = pnew;
-      T* ra = rold;
-      T* rb = rnew;
-      for (int c = 0; c < chunk; ++c) {
-        body(a, b, ra, rb);
-        std::swap(a, b);
-        std::swap(ra, rb);
-      }
+    else
+      run_chunk(watch ? ch & 1 : 0);
+    if (watch) {
+      ++want;
+      HIPCHK(hipGetLastError());
+      unsigned long long v = 0;
+      if (const int rc = wait_host(P, [&]() { return (unsigned)((v = *prog) >> 32) == want; })) return rc;
+      if ((unsigned)v == 0) break;
+      continue;
     }
     const int a = count_active(P, P->st.active, sys0, nsys);
     if (a < 0) {
@@ -2112,9 +2137,13 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
   } else {
     if (hipHostMalloc((void**)&P->h_flags, S * sizeof(int), hipHostMallocCoherent) != hipSuccess)
       return fail(BURA_ENOMEM);
-    if (hipHostMalloc(&P->h_state, state_mirror + 8, hipHostMallocCoherent) != hipSuccess) return fail(BURA_ENOMEM);
+    if (hipHostMalloc(&P->h_state, state_mirror + 16, hipHostMallocCoherent) != hipSuccess) return fail(BURA_ENOMEM);
     P->h_seq = (unsigned*)((char*)P->h_state + state_mirror);
     *P->h_seq = 0;
+    P->prog.host = (unsigned long long*)((char*)P->h_state + state_mirror + 8);
+    *P->prog.host = 0;
+    if ((rc = dev_alloc(P, (void**)&P->prog.count, 16))) return fail(rc);
+    if ((rc = dev_zero(P, P->prog.count, 16))) return fail(rc);
   }
   if (o.autotune && !(P->direct && o.tol <= kDirectTol)) {
     if (hipStreamSynchronize(P->stream) != hipSuccess) return fail(BURA_EDEVICE);

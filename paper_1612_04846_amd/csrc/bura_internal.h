@@ -300,8 +300,15 @@ void launch_combine(long long N, const double* x, const double* w, const Combine
                     double* partial = nullptr, double* norms = nullptr);
 void launch_apply64(int dim, bool var, const LevelDev<double>& L, const double* x, double* y, double shift,
                     int nvec, hipStream_t st);
+// Where a k_scalars launch tells the host the active systems left: `host`
+// (pinned) gets the launch's number (high half; one more each time) and the
+// systems (low half).  count: two words on the device, 0 at first.
+struct Progress {
+  unsigned long long* count = nullptr;
+  unsigned long long* host = nullptr;
+};
 void launch_scalars(int op, const double* partial, int nblk, int nsys, SysState st_, double tol,
-                    int max_iter, hipStream_t st);
+                    int max_iter, hipStream_t st, const Progress& pr = Progress());
 void launch_zero(void* p, size_t bytes, hipStream_t st);
 // the terms of one rhs slot of a slot plan, passed by value to a kernel
 struct SlotTermsDev {

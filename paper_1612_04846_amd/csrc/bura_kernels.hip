@@ -3571,17 +3571,28 @@ __device__ void apply_op(int op, double tot, const SysState& S, int sys, double 
   }
 }
 
+// With pr.host set, the last block to end tells the host how many systems are
+// active after the operation: one 64-bit count of the blocks (low half) and of
+// the active systems (high half), left at 0 for the next launch.
 __global__ __launch_bounds__(256) void k_scalars(int op, const double* __restrict__ partial, int nblk, SysState S,
-                                                 double tol, int max_iter) {
+                                                 double tol, int max_iter, Progress pr) {
   const int sys = blockIdx.x;
-  const bool inner = op != OP_OUTER;
-  if (inner && !S.active[sys]) return;
-  if (!inner && !S.active64[sys]) return;
-  double v = 0.0;
-  for (int b = threadIdx.x; b < nblk; b += blockDim.x) v += partial[(size_t)sys * nblk + b];
-  const double tot = block_sum(v);
-  if (threadIdx.x != 0) return;
-  apply_op(op, tot, S, sys, tol, max_iter);
+  const int* act = op != OP_OUTER ? S.active : S.active64;
+  const bool on = act[sys] != 0;
+  if (on) {
+    double v = 0.0;
+    for (int b = threadIdx.x; b < nblk; b += blockDim.x) v += partial[(size_t)sys * nblk + b];
+    const double tot = block_sum(v);
+    if (threadIdx.x == 0) apply_op(op, tot, S, sys, tol, max_iter);
+  }
+  if (!pr.host || threadIdx.x != 0) return;
+  const unsigned long long mine = 1ULL + (on && act[sys] ? 1ULL << 32 : 0ULL);
+  const unsigned long long tot = atomicAdd(pr.count, mine) + mine;
+  if ((unsigned)tot != gridDim.x) return;
+  atomicExch(pr.count, 0ULL);
+  const unsigned long long seq = pr.count[1] + 1;   // only one block gets here in a launch
+  pr.count[1] = seq;
+  __hip_atomic_store(pr.host, seq << 32 | tot >> 32, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The scalar state of system i at the start of a solve: counters and flags
@@ -4295,8 +4306,8 @@ void launch_apply64(int dim, bool var, const LevelDev<double>& L, const double* 
 }
 
 void launch_scalars(int op, const double* partial, int nblk, int nsys, SysState S, double tol, int max_iter,
-                    hipStream_t st) {
-  hipLaunchKernelGGL(k_scalars, dim3(nsys), dim3(256), 0, st, op, partial, nblk, S, tol, max_iter);
+                    hipStream_t st, const Progress& pr) {
+  hipLaunchKernelGGL(k_scalars, dim3(nsys), dim3(256), 0, st, op, partial, nblk, S, tol, max_iter, pr);
 }
 
 // Terms of one right-hand-side slot of a slot plan (systems j R + slot,
