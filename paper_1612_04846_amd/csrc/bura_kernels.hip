@@ -1181,7 +1181,7 @@ constexpr int kRowsSeg = 128, kShortRowsSeg = 32;   // fine rows per workgroup
 // The marching kernels keep the global loads of the next kRowLead rows in
 // flight in a ring of registers: slot s serves steps s, s + kRowLead, ...,
 // is used at the start of its step and is refilled after the step's
-// barriers with the row kRowLead steps ahead (the barriers keep the compiler
+// barrier with the row kRowLead steps ahead (the barrier keeps the compiler
 // from issuing the new load before the old value is used, so the slot stays
 // one register and no register copy has to wait on a load).  The loop over
 // steps is unrolled by kRowLead so that every slot index is a constant.  A
@@ -1199,9 +1199,12 @@ constexpr int kPlaneLead = 2;
 // register, fixed for the whole march) plus a byte offset soff that is the
 // same for the whole workgroup (a scalar register, the row).  Addressing a
 // row then costs no per-lane arithmetic, where a 64-bit pointer costs a
-// 64-bit add per access.  Every access is in range (rows are clamped), so
-// the bounds of the resource never apply.
+// 64-bit add per access.  Rows are clamped; a lane past the grid takes an
+// offset out of the resource's range (kOffGrid), as is the second half of the
+// last pair of a vector: such loads return 0, element by element, and nothing
+// is stored.
 constexpr int kBufWord3 = 0x00020000;   // resource word 3: 32-bit data format
+constexpr unsigned kOffGrid = 0x80000000u;
 template <typename T>
 struct RowBuf {
   __amdgpu_buffer_rsrc_t r;
@@ -1210,6 +1213,44 @@ struct RowBuf {
   __device__ __forceinline__ T ld(unsigned voff, unsigned soff) const {
     if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
     else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+  }
+  // the elements at voff and behind it (element-aligned is enough)
+  __device__ __forceinline__ void ld2(T (&v)[2], unsigned voff, unsigned soff) const {
+    if constexpr (sizeof(T) == 4) {
+      const auto w = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+      v[0] = __uint_as_float(w[0]);
+      v[1] = __uint_as_float(w[1]);
+    } else {
+      const auto w = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
+      v[0] = __hiloint2double((int)w[1], (int)w[0]);
+      v[1] = __hiloint2double((int)w[3], (int)w[2]);
+    }
+  }
+  __device__ __forceinline__ void ld3(T (&v)[3], unsigned voff, unsigned soff) const {
+    if constexpr (sizeof(T) == 4) {
+      const auto w = __builtin_amdgcn_raw_buffer_load_b96(r, voff, soff, 0);
+      v[0] = __uint_as_float(w[0]);
+      v[1] = __uint_as_float(w[1]);
+      v[2] = __uint_as_float(w[2]);
+    } else {
+      T a[2];
+      ld2(a, voff, soff);
+      v[0] = a[0];
+      v[1] = a[1];
+      v[2] = ld(voff + 2 * (unsigned)sizeof(T), soff);
+    }
+  }
+  template <bool NT>
+  __device__ __forceinline__ void st2(const T (&v)[2], unsigned voff, unsigned soff) const {
+    if constexpr (sizeof(T) == 4) {
+      const unsigned __attribute__((ext_vector_type(2))) w = {__float_as_uint(v[0]), __float_as_uint(v[1])};
+      __builtin_amdgcn_raw_buffer_store_b64(w, r, voff, soff, NT ? 2 : 0);
+    } else {
+      const unsigned __attribute__((ext_vector_type(4))) w = {
+          (unsigned)__double2loint(v[0]), (unsigned)__double2hiint(v[0]), (unsigned)__double2loint(v[1]),
+          (unsigned)__double2hiint(v[1])};
+      __builtin_amdgcn_raw_buffer_store_b128(w, r, voff, soff, NT ? 2 : 0);
+    }
   }
   // NT: the nontemporal hint (the value is read again only by a later kernel)
   template <bool NT>
@@ -1237,16 +1278,10 @@ template <int LEAD = kRowLead, typename Step>
 __device__ __forceinline__ void ring_march(int t0, int t1, Step step) {
   ring_march_impl<LEAD>(t0, t1, step, std::make_integer_sequence<int, LEAD>{});
 }
-// the lead of the fused row kernels: in FP64 with variable coefficients
-// three rows of loads do not fit the registers a 1024-thread workgroup
-// leaves (they spilled to scratch memory), so those keep two, and one with
-// three sweeps
-template <typename T, bool VAR, int NU>
-constexpr int row_lead() { return sizeof(T) == 8 && VAR ? (NU >= 3 ? 1 : 2) : kRowLead; }
-// the up kernel holds twice the sweeps' rows (it forms the pre-smoothed
-// iterate again): FP64 with variable coefficients keeps one row of lead
-template <typename T, bool VAR, int NU>
-constexpr int up_row_lead() { return sizeof(T) == 8 && VAR ? 1 : kRowLead; }
+// the lead of the 2D row kernels, in rows of two columns per thread (even, so
+// that a slot has a fixed half of the double-buffered LDS rows)
+template <typename T>
+constexpr int row_lead() { return sizeof(T) == 8 ? 2 : 4; }
 // Before a marching loop starts its ring: every load of the set-up has
 // arrived.  The waits inside the loop must suit both the first step and the
 // steady state; with set-up loads still in flight they are computed for the
@@ -1284,14 +1319,16 @@ __device__ __forceinline__ void count_bytes_row(const RowTile& rt, unsigned long
   atomicAdd(ctr, b);
 }
 // whether the stencil product / down / up kernel of a level of n points per
-// axis runs k_spmv_r2 / k_down2r / k_up2r in variant tv, and their threads
-// per workgroup (one per column and at least one past the grid, in waves)
+// axis runs k_spmv_r2 / k_down2r / k_up2r in variant tv
 static inline bool down_rows(int dim, int n, int tv) {
   const int v = tile_variant(tv);
   return dim == 2 && (v == kRowsVariant || v == kShortRowsVariant) && n <= kRowsMaxN;
 }
 static inline bool up_rows(int dim, int n, int tv) { return down_rows(dim, n, tv); }
 static inline bool spmv_rows(int dim, int n, int tv) { return down_rows(dim, n, tv); }
+// threads per workgroup, in waves: one per pair of columns (those three), one
+// per column and at least one past the grid (the FP64 residual)
+static inline int pair_threads(int n) { return (((n + 1) / 2 + 63) / 64) * 64; }
 static inline int rows_threads(int n) { return ((n + 1 + 63) / 64) * 64; }
 // fine rows per workgroup of a row variant (the down kernel: half as many coarse rows)
 static inline int rows_seg(int tv) { return tile_variant(tv) == kShortRowsVariant ? kShortRowsSeg : kRowsSeg; }
@@ -1661,45 +1698,145 @@ __global__ __launch_bounds__(256) void k_up2(LevelDev<T> Lc, LevelDev<T> Lf, con
 }
 
 // --------------------------------------------------------------------------
-// k_down2r: the down kernel of k_down2 (same inputs and outputs, the same
-// arithmetic per point except the order of the full weighting's sum)
-// marching along y over whole grid rows.  A workgroup has one
-// thread per grid column (blockDim.x >= n + 1, a multiple of 64) and owns the
-// fine rows of ky coarse rows (a launch parameter); it walks up its rows with the stages
-// lagging one row behind each other, as the 3D kernels walk up their planes:
-// at step t row t of b (RUP: b_old - alpha (A + s) p, p of rows t - 1 .. t + 1)
-// enters, the first sweep is formed on it pointwise, sweep m + 1 on row t - m,
-// the residual on row t - NU, and the full weighting of coarse row K once the
-// residual of fine row 2K + 2 is there.  The newest row of every stage goes
-// into LDS for the left/right neighbours; the rows below and above stay in
-// registers.  A workgroup starts NU rows below its first owned row (warm-up),
-// so every row it writes is exact.  There is no halo across columns and none
-// along y beyond the warm-up rows, where the tiles of k_down2 fetch 1.4 - 1.8
-// times their points (halo rows and columns, partial cache lines) and sweep
-// that many.  Columns past the grid and rows outside it carry a zero
-// right-hand side and a zero inverse diagonal, so they stay exactly 0; the
-// LDS rows have a zero pad on each side.  Two barriers per row.  With xout
-// == nullptr the pre-smoothed iterate is not stored (the level's up kernel
-// is k_up2r, which forms it again).
+// The 2D row kernels march along y over whole grid rows with two columns per
+// thread: thread i has columns 2i and 2i + 1 in registers, and what it needs
+// from its neighbours (the odd column of thread i - 1, the even one of thread
+// i + 1) goes through LDS, double-buffered by the parity of the step, so that a
+// row takes one barrier.  Thread i's LDS record is RowRec<T, ...> values wide,
+// an odd number, so that a wave's accesses fall in different banks; the records
+// before the first and behind the last thread stay 0 (columns off the grid).
+// With one column per thread, two barriers and every face weight loaded twice
+// (a face belongs to two columns and two rows) these kernels were bound by
+// instruction issue: the up kernel of 511^2 took 58 vector, 63 scalar and 10
+// memory instructions per row and wave.
+// --------------------------------------------------------------------------
+constexpr int kRowThreads = 512;   // pairs of columns: kRowsMaxN at most
+extern __shared__ double row_lds[];   // (NT + 2) records
+
+// LDS records of a row kernel with `words` values a thread and step
+constexpr int row_rec(int words) { return 2 * words + 1; }
+template <typename T>
+static inline size_t row_lds_bytes(int words, int threads) {
+  return (size_t)(threads + 2) * row_rec(words) * sizeof(T);
+}
+constexpr int down_words(int nu, bool rup) { return 2 * nu + 1 + (rup ? 2 : 0); }
+constexpr int up_words(int nu) { return 2 * (2 * nu - 1); }
+constexpr int spmv_words() { return 2; }
+
+// What the row kernels share: a thread's pair of columns and the loads of the
+// operator's rows.  l: the faces left of the pair, between and right of it;
+// u: the faces above (below a row: u of the row before).
+template <typename T, bool VAR>
+struct RowPair {
+  int n, i;
+  bool on[2];         // the columns are on the grid
+  unsigned cb;        // byte offset of the pair in a row (kOffGrid: none)
+  unsigned rowb;      // bytes per row
+  T m1;               // 1 where the odd column is on the grid, else 0
+  RowBuf<T> w0, w1;
+  struct Faces { T l[3], u[2]; };
+  __device__ __forceinline__ RowPair(const LevelDev<T>& L, const T* any)
+      : n(L.n), i(threadIdx.x), on{2 * (int)threadIdx.x < L.n, 2 * (int)threadIdx.x + 1 < L.n},
+        cb(on[0] ? 2 * threadIdx.x * (unsigned)sizeof(T) : kOffGrid), rowb((unsigned)L.n * (unsigned)sizeof(T)),
+        m1(on[1] ? T(1) : T(0)), w0(VAR ? L.wf0 : any, VAR ? (long long)(L.n + 1) * L.n : 1),
+        w1(VAR ? L.wf1 : any, VAR ? (long long)(L.n + 1) * L.n : 1) {}
+  __device__ __forceinline__ unsigned row(int r) const { return (unsigned)min(max(r, 0), n - 1) * rowb; }
+  __device__ __forceinline__ bool in(int r) const { return r >= 0 && r < n; }
+  // faces of row r (clamped; the faces above row -1 are those below row 0)
+  __device__ __forceinline__ void faces(Faces& f, int r) const {
+    if (VAR) {
+      w0.ld3(f.l, cb, (unsigned)min(max(r, 0), n - 1) * (rowb + (unsigned)sizeof(T)));
+      above(f.u, r);
+    }
+  }
+  __device__ __forceinline__ void above(T (&u)[2], int r) const {
+    if (VAR) w1.ld2(u, cb, (unsigned)min(max(r + 1, 0), n) * rowb);
+  }
+  // stores the columns that are on the grid
+  template <bool NT>
+  __device__ __forceinline__ void store(const RowBuf<T>& b, const T (&v)[2], int r) const {
+    if (on[1]) b.template st2<NT>(v, cb, (unsigned)r * rowb);
+    else if (on[0]) b.template st<NT>(v[0], cb, (unsigned)r * rowb);
+  }
+};
+
+// (A + s) x at the pair from its row x, the values left and right of it, below
+// and above (f: the row's faces, d: those below; the flux form of apply_pt)
+template <typename T, bool VAR>
+__device__ __forceinline__ void pair_apply(T (&y)[2], const typename RowPair<T, VAR>::Faces& f, const T (&d)[2],
+                                           const T (&x)[2], T left, T right, const T (&dn)[2], const T (&up)[2], T wc,
+                                           T sh) {
+  const T e[2][2] = {{left, x[1]}, {x[0], right}};
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if (!VAR)
+      y[c] = wc * ((x[c] - e[c][0]) + (x[c] - e[c][1]) + (x[c] - dn[c]) + (x[c] - up[c])) + sh * x[c];
+    else
+      y[c] = f.l[c] * (x[c] - e[c][0]) + f.l[c + 1] * (x[c] - e[c][1]) + d[c] * (x[c] - dn[c]) +
+             f.u[c] * (x[c] - up[c]) + sh * x[c];
+  }
+}
+
+// One damped Jacobi update x + w (b - (A + s) x) / diag at the pair, written as
+// x + w ((b + the neighbours' face-weighted sum) / diag - x): diag holds every
+// face weight and the shift, so the two agree in exact arithmetic, and this
+// form takes 6 instead of 12 vector operations per point (the residual keeps
+// the difference form).  r: 1 / diag, 0 off the grid, where x stays exactly 0.
+template <typename T, bool VAR>
+__device__ __forceinline__ void pair_relax(T (&y)[2], const typename RowPair<T, VAR>::Faces& f, const T (&d)[2],
+                                           const T (&x)[2], T left, T right, const T (&dn)[2], const T (&up)[2], T wc,
+                                           const T (&b)[2], T w, const T (&r)[2]) {
+  const T e[2][2] = {{left, x[1]}, {x[0], right}};
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const T nb = VAR ? b[c] + f.l[c] * e[c][0] + f.l[c + 1] * e[c][1] + d[c] * dn[c] + f.u[c] * up[c]
+                     : b[c] + wc * ((e[c][0] + e[c][1]) + (dn[c] + up[c]));
+    y[c] = x[c] + w * (r[c] * nb - x[c]);
+  }
+}
+
+template <typename T, bool VAR>
+__device__ __forceinline__ void pair_recip(T (&r)[2], const RowPair<T, VAR>& pr, bool in,
+                                           const typename RowPair<T, VAR>::Faces& f, const T (&d)[2], T sh, T rcon) {
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const T v = VAR ? jacobi_recip(f.l[c] + f.l[c + 1] + d[c] + f.u[c] + sh) : rcon;
+    r[c] = in && pr.on[c] ? v : T(0);
+  }
+}
+
+// --------------------------------------------------------------------------
+// k_down2r: the down kernel of k_down2 (same inputs and outputs) on whole grid
+// rows.  A workgroup owns the fine rows of ky coarse rows (a launch parameter);
+// it walks up its rows with the stages lagging one row behind each other, as
+// the 3D kernels walk up their planes: at step t row t of b (RUP: b_old -
+// alpha (A + s) p, p of rows t - 1 .. t + 1) enters, the first sweep is formed
+// on it pointwise, sweep m + 1 on row t - m, the residual on row t - NU, and
+// the full weighting of coarse row K once the residual of fine row 2K + 2 is
+// there.  The rows below and above stay in registers.  A workgroup starts NU
+// rows below its first owned row (warm-up), so every row it writes is exact.
+// There is no halo across columns and none along y beyond the warm-up rows,
+// where the tiles of k_down2 fetch 1.4 - 1.8 times their points (halo rows and
+// columns, partial cache lines) and sweep that many.  Columns and rows outside
+// the grid have a zero inverse diagonal, so they stay exactly 0.  With xout
+// == nullptr the pre-smoothed iterate is not stored (the level's up kernel is
+// k_up2r, which forms it again).
 // --------------------------------------------------------------------------
 template <typename T, bool VAR, int NU, bool RUP>
-__global__ __launch_bounds__(1024) void k_down2r(LevelDev<T> Lf, LevelDev<T> Lc, const T* __restrict__ b,
+__global__ __launch_bounds__(kRowThreads) void k_down2r(LevelDev<T> Lf, LevelDev<T> Lc, const T* __restrict__ b,
                                                  T* __restrict__ xout, T* __restrict__ bc,
                                                  const T* __restrict__ shift, const int* __restrict__ active,
                                                  Sweeps<T> om, unsigned long long* __restrict__ ctr,
                                                  const T* __restrict__ pv, const double* __restrict__ alpha,
                                                  T* __restrict__ bout, double* __restrict__ partial, Fin fin,
                                                  int ky) {
-  constexpr int LW = 1024 + 2;   // an LDS row: pad, up to 1024 columns, pad
-  __shared__ T sx[NU][LW];       // newest row of each sweep's output
-  __shared__ T sr[LW];           // residual row
-  __shared__ T sp[RUP ? LW : 1]; // p of the row being updated (RUP)
+  // a thread's LDS values per step: sweep m's pair at 2m, the even residual at
+  // RES, p's pair at PV
+  constexpr int WORDS = down_words(NU, RUP), REC = row_rec(WORDS), RES = 2 * NU, PV = RES + 1;
+  constexpr int LEAD = row_lead<T>();
   const RowTile rt = row_tile();
   const int sys = rt.sys;
-  constexpr int LEAD = row_lead<T, VAR, NU>();
   if (!active[sys]) return;
-  // xout == nullptr: the pre-smoothed iterate is not stored (the level's up
-  // kernel is k_up2r, which forms it again)
   const bool keepx = xout != nullptr;
   count_bytes_row(rt, ctr, (unsigned long long)Lf.N * sizeof(T) * ((RUP ? 3 : 1) + (keepx ? 1 : 0)) +
                                    (unsigned long long)Lc.N * sizeof(T) +
@@ -1707,165 +1844,154 @@ __global__ __launch_bounds__(1024) void k_down2r(LevelDev<T> Lf, LevelDev<T> Lc,
   const int nf = Lf.n, nc = Lc.n;
   const int K0 = rt.seg * ky, K1 = min(K0 + ky, nc);
   const int f1 = K1 == nc ? nf : 2 * K1;   // owned fine rows [2 K0, f1) (the last segment: the top one too)
-  const int i = threadIdx.x;               // this thread's column
-  const int NT = blockDim.x;
-  const bool col_on = i < nf;
-  const int ic = min(i, nf - 1);           // clamped column for the loads
-  const unsigned cb = (unsigned)ic * (unsigned)sizeof(T), ib = (unsigned)i * (unsigned)sizeof(T);
-  const unsigned rowb = (unsigned)nf * (unsigned)sizeof(T);   // bytes per grid row
+  const int i = threadIdx.x, NT = blockDim.x;
   const T sh = shift[sys];
   const T rcon = jacobi_recip(Lf.wc * T(4) + sh);
   const T am = RUP ? (T)alpha[sys] : T(0);
   const long long off = (long long)sys * Lf.N;
-  const T* __restrict__ bs = b + off;
-  const T* __restrict__ ps = RUP ? pv + off : nullptr;
-  T* __restrict__ xs = keepx ? xout + off : nullptr;
-  T* __restrict__ bo = RUP ? bout + off : nullptr;
-  const RowBuf<T> bsb(bs, Lf.N), psb(RUP ? ps : bs, Lf.N), xsb(xs, Lf.N), bob(RUP ? bo : xs, Lf.N);
-  const RowBuf<T> w0b(VAR ? Lf.wf0 : bs, VAR ? (long long)(nf + 1) * nf : 1), w1b(VAR ? Lf.wf1 : bs, VAR ? (long long)(nf + 1) * nf : 1);
-  const int q = 1 + i;   // this column in an LDS row
-  // the pads (columns -1 and NT) stay 0; every other entry is written before it is read
-  if (i < 2) {
-    const int pq = i == 0 ? 0 : NT + 1;
-#pragma unroll
-    for (int m = 0; m < NU; ++m) sx[m][pq] = T(0);
-    sr[pq] = T(0);
-    if (RUP) sp[pq] = T(0);
-  }
-  auto row_on = [&](int r) { return col_on && r >= 0 && r < nf; };
-  auto crow = [&](int r) { return min(max(r, 0), nf - 1); };
-  // 1 on the grid, 0 off it, applied to a row's loads when they are used
-  auto on_f = [&](int r) { return row_on(r) ? T(1) : T(0); };
-  // face weights of row r at this column (clamped row: finite off the grid,
-  // where no sweep uses them) and the inverse diagonal of row r
-  struct Faces { T l, r, d, u; };
-  auto load_faces = [&](int r) {
-    Faces f{T(0), T(0), T(0), T(0)};
-    if (VAR) {
-      const unsigned rr = (unsigned)crow(r);
-      const unsigned o0 = rr * (unsigned)(nf + 1) * (unsigned)sizeof(T), o1 = rr * rowb;
-      f.l = w0b.ld(cb, o0);
-      f.r = w0b.ld(cb + (unsigned)sizeof(T), o0);
-      f.d = w1b.ld(cb, o1);
-      f.u = w1b.ld(cb, o1 + rowb);
-    }
-    return f;
-  };
-  auto rdiag = [&](const Faces& f, int r) {
-    if (!VAR) return row_on(r) ? rcon : T(0);
-    return row_on(r) ? jacobi_recip(f.l + f.r + f.d + f.u + sh) : T(0);
-  };
-  // (A + s) x at this column of a row with faces f, centre xc, left/right from
-  // the LDS row X, below xd and above xu (the arithmetic and order of k_down2)
-  auto apply = [&](const Faces& f, const T* X, T xc, T xd, T xu) {
-    const T xl = X[q - 1], xr = X[q + 1];
-    if (!VAR) return Lf.wc * ((xc - xl) + (xc - xr) + (xc - xd) + (xc - xu)) + sh * xc;
-    return f.l * (xc - xl) + f.r * (xc - xr) + f.d * (xc - xd) + f.u * (xc - xu) + sh * xc;
-  };
-  // one damped Jacobi update x + w (b - (A + s) x) / diag written as
-  // x + w ((b + the neighbours' face-weighted sum) / diag - x): diag holds
-  // every face weight and the shift, so the two agree in exact arithmetic, and
-  // this form takes 6 instead of 12 vector operations per point (the residual
-  // keeps the difference form)
-  auto relax = [&](const Faces& f, const T* X, T xc, T xd, T xu, T bb, T w, T r) {
-    const T xl = X[q - 1], xr = X[q + 1];
-    const T nb = VAR ? bb + f.l * xl + f.r * xr + f.d * xd + f.u * xu : bb + Lf.wc * ((xl + xr) + (xd + xu));
-    return xc + w * (r * nb - xc);
-  };
+  const RowPair<T, VAR> pr(Lf, b + off);
+  const RowBuf<T> bsb(b + off, Lf.N), psb((RUP ? pv : b) + off, Lf.N), xsb((keepx ? xout : bc) + (keepx ? off : 0), keepx ? Lf.N : 0),
+      bob((RUP ? bout : bc) + (RUP ? off : 0), RUP ? Lf.N : 0);
+  typedef typename RowPair<T, VAR>::Faces Faces;
+  T* lds = reinterpret_cast<T*>(row_lds);
+  for (int j = i; j < (NT + 2) * REC; j += NT) lds[j] = T(0);
+  T* rec = lds + (i + 1) * REC;
   const int t0 = 2 * K0 - NU, t1 = 2 * K1 + NU;
   // registers: bh[d] = b of row t - d; xh[m][0], xh[m][1] = sweep m+1's output
   // at its newest row of the previous step and the one below; fw[d], rd[d] =
-  // faces and inverse diagonal of row t - d
-  T bh[NU + 1], xh[NU][2], rd[NU + 1];
-  Faces fw[NU + 1];
+  // faces and inverse diagonal of row t - d (fw[d + 1].u: the faces below it)
+  T bh[NU + 1][2], xh[NU][2][2], rd[NU + 1][2];
+  Faces fw[NU + 2];
 #pragma unroll
-  for (int d = 0; d <= NU; ++d) {
-    bh[d] = T(0);
-    rd[d] = T(0);
-    fw[d] = load_faces(t0 - 1 - d);
+  for (int d = 0; d <= NU + 1; ++d) {
+    fw[d] = Faces{};
+    if (d <= NU) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        bh[d][c] = T(0);
+        rd[d][c] = T(0);
+        if (d < NU) xh[d][0][c] = xh[d][1][c] = T(0);
+      }
+    }
   }
+  // the faces of the rows before the first step (valid where a sweep uses them)
 #pragma unroll
-  for (int m = 0; m < NU; ++m) xh[m][0] = xh[m][1] = T(0);
+  for (int d = 0; d <= NU; ++d) pr.faces(fw[d], t0 - 1 - d);
+  __syncthreads();
   // p of rows t - 1, t, t + 1 (RUP; 0 outside the grid) during step t, p(t)
-  // also in sp; before the first step they hold rows t0 - 1 and t0
-  T pm = T(0), pc = T(0), pa = T(0);
+  // also in LDS; before the first step they hold rows t0 - 1 and t0
+  T pm[2] = {T(0), T(0)}, pc[2] = {T(0), T(0)}, pa[2] = {T(0), T(0)};
   if (RUP) {
-    pc = ps[(long long)crow(t0 - 1) * nf + ic] * on_f(t0 - 1);
-    pa = ps[(long long)crow(t0) * nf + ic] * on_f(t0);
-    sp[q] = pa;
+    psb.ld2(pc, pr.cb, pr.row(t0 - 1));
+    psb.ld2(pa, pr.cb, pr.row(t0));
+    const T mc = pr.in(t0 - 1) ? T(1) : T(0), ma = pr.in(t0) ? T(1) : T(0);
+    pc[0] *= mc;
+    pc[1] *= mc * pr.m1;
+    pa[0] *= ma;
+    pa[1] *= ma * pr.m1;
+    rec[WORDS + PV] = pa[0];   // the half that step t0 reads
+    rec[WORDS + PV + 1] = pa[1];
   }
   // the coarse column of this thread (threads I < nc) and its weighted
   // in-row sums of the residual on fine rows 2K and 2K + 1
   const bool restricts = i < nc;
   T s_lo = T(0), s_mid = T(0);
   const RowBuf<T> bcb(bc + (long long)sys * Lc.N, Lc.N);
-  const unsigned cbc = (unsigned)min(i, nc - 1) * (unsigned)sizeof(T);   // this lane's coarse column
+  const unsigned cbc = restricts ? (unsigned)i * (unsigned)sizeof(T) : kOffGrid;   // this lane's coarse column
   double rr = 0.0;
   ring_prologue_wait();
   __syncthreads();
   // the ring of row loads (see kRowLead): slot s of step t holds b and the
   // faces of row t and p of row t + 1, as loaded (clamped rows, unmasked)
-  T rb[LEAD], rp[LEAD];
+  T rb[LEAD][2], rp[LEAD][2];
   Faces rf[LEAD];
+  auto fill = [&](int t, int s) {
+    bsb.ld2(rb[s], pr.cb, pr.row(t));
+    pr.faces(rf[s], t);
+    if (RUP) psb.ld2(rp[s], pr.cb, pr.row(t + 1));
+  };
 #pragma unroll
-  for (int s = 0; s < LEAD; ++s) {
-    rb[s] = bsb.ld(cb, (unsigned)crow(t0 + s) * rowb);
-    rf[s] = load_faces(t0 + s);
-    rp[s] = RUP ? psb.ld(cb, (unsigned)crow(t0 + 1 + s) * rowb) : T(0);
-  }
+  for (int s = 0; s < LEAD; ++s) fill(t0 + s, s);
   ring_march<LEAD>(t0, t1, [&](int t, auto slot) {
     constexpr int s = decltype(slot)::value;
+    constexpr int WR = (s & 1) * WORDS, RD = WORDS - WR;   // the record's halves of this step and the one before
 #pragma unroll
-    for (int d = NU; d > 0; --d) {
-      bh[d] = bh[d - 1];
-      fw[d] = fw[d - 1];
-      rd[d] = rd[d - 1];
+    for (int d = NU + 1; d > 0; --d) fw[d] = fw[d - 1];
+#pragma unroll
+    for (int d = NU; d > 0; --d)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        bh[d][c] = bh[d - 1][c];
+        rd[d][c] = rd[d - 1][c];
+      }
+    if (VAR) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) fw[0].l[c] = ring_take(rf[s].l[c]);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) fw[0].u[c] = ring_take(rf[s].u[c]);
     }
-    if (VAR) fw[0] = Faces{ring_take(rf[s].l), ring_take(rf[s].r), ring_take(rf[s].d), ring_take(rf[s].u)};
-    rd[0] = rdiag(fw[0], t);
+    pair_recip<T, VAR>(rd[0], pr, pr.in(t), fw[0], fw[1].u, sh, rcon);
     if (RUP) {
-      pm = pc;
-      pc = pa;
-      pa = rp[s] * on_f(t + 1);
+      const T m = pr.in(t + 1) ? T(1) : T(0);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        pm[c] = pc[c];
+        pc[c] = pa[c];
+      }
+      pa[0] = rp[s][0] * m;
+      pa[1] = rp[s][1] * (m * pr.m1);
     }
-    T bn = rb[s];
-    if (RUP) bn = bn - am * apply(fw[0], sp, pc, pm, pa);
-    bh[0] = row_on(t) ? bn : T(0);
-    if (RUP && t >= 2 * K0 && t < f1 && col_on) {
-      bob.template st<true>(bh[0], ib, (unsigned)t * rowb);
-      rr += (double)bh[0] * (double)bh[0];
+    bh[0][0] = rb[s][0];
+    bh[0][1] = rb[s][1];
+    if (RUP) {
+      T q[2];
+      pair_apply<T, VAR>(q, fw[0], fw[1].u, pc, rec[RD + PV + 1 - REC], rec[RD + PV + REC], pm, pa, Lf.wc, sh);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) bh[0][c] -= am * q[c];
+      if (t >= 2 * K0 && t < f1) {
+        pr.template store<true>(bob, bh[0], t);
+        const double r0 = (double)bh[0][0], r1 = (double)(bh[0][1] * pr.m1);   // (lanes past the grid: 0)
+        rr += r0 * r0;
+        rr += r1 * r1;
+      }
     }
     // sweep 1 on row t from x = 0; sweep m + 1 on row t - m from sweep m's
-    // output (centre row in sx[m - 1], below in xh, above just formed)
-    T xn[NU];
-    xn[0] = sweep_w(om, 0) * bh[0] * rd[0];
+    // output (centre row in xh and LDS, below in xh, above just formed)
+    T xn[NU][2];
 #pragma unroll
-    for (int m = 1; m < NU; ++m) {
-      xn[m] = relax(fw[m], sx[m - 1], xh[m - 1][0], xh[m - 1][1], xn[m - 1], bh[m], sweep_w(om, m), rd[m]);
-    }
+    for (int c = 0; c < 2; ++c) xn[0][c] = sweep_w(om, 0) * bh[0][c] * rd[0][c];
+#pragma unroll
+    for (int m = 1; m < NU; ++m)
+      pair_relax<T, VAR>(xn[m], fw[m], fw[m + 1].u, xh[m - 1][0], rec[RD + 2 * m - 1 - REC], rec[RD + 2 * m - 2 + REC],
+                         xh[m - 1][1], xn[m - 1], Lf.wc, bh[m], sweep_w(om, m), rd[m]);
     // the residual on row t - NU
-    const T res = bh[NU] - apply(fw[NU], sx[NU - 1], xh[NU - 1][0], xh[NU - 1][1], xn[NU - 1]);
+    T res[2];
+    pair_apply<T, VAR>(res, fw[NU], fw[NU + 1].u, xh[NU - 1][0], rec[RD + 2 * NU - 1 - REC],
+                       rec[RD + 2 * NU - 2 + REC], xh[NU - 1][1], xn[NU - 1], Lf.wc, sh);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) res[c] = bh[NU][c] - res[c];
     // the pre-smoothed iterate: sweep NU's newest row t - NU + 1
     const int gx = t - NU + 1;
-    if (keepx && gx >= 2 * K0 && gx < f1 && col_on) xsb.template st<true>(xn[NU - 1], ib, (unsigned)gx * rowb);
-    __syncthreads();   // every read of this step's LDS rows is done
+    if (keepx && gx >= 2 * K0 && gx < f1) pr.template store<true>(xsb, xn[NU - 1], gx);
 #pragma unroll
-    for (int m = 0; m < NU; ++m) sx[m][q] = xn[m];
-    sr[q] = res;
-    if (RUP) sp[q] = pa;   // p(t + 1), the centre row of the next step
+    for (int m = 0; m < NU; ++m)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) rec[WR + 2 * m + c] = xn[m][c];
+    rec[WR + RES] = res[0];
+    if (RUP) {   // p(t + 1), the centre row of the next step
+      rec[WR + PV] = pa[0];
+      rec[WR + PV + 1] = pa[1];
+    }
     __syncthreads();
-    // refill the slot with the rows LEAD steps ahead
-    rb[s] = bsb.ld(cb, (unsigned)crow(t + LEAD) * rowb);
-    rf[s] = load_faces(t + LEAD);
-    if (RUP) rp[s] = psb.ld(cb, (unsigned)crow(t + 1 + LEAD) * rowb);
-    // full weighting: this coarse column's in-row sum of fine row f = t - NU,
-    // and coarse row K = f/2 - 1 once f = 2K + 2 (weights 1/4, 1/2, 1/4 along y)
+    fill(t + LEAD, s);   // refill the slot with the rows LEAD steps ahead
+    // full weighting: this coarse column's in-row sum of fine row f = t - NU
+    // (fine columns 2I .. 2I + 2), and coarse row K = f/2 - 1 once f = 2K + 2
+    // (weights 1/4, 1/2, 1/4 along y)
     const int f = t - NU;
-    if (restricts && f >= 2 * K0) {
-      const T* R = sr + 1 + 2 * i;   // fine columns 2I .. 2I + 2
-      const T acc = T(0.25) * R[0] + T(0.5) * R[1] + T(0.25) * R[2];
+    if (f >= 2 * K0) {
+      const T acc = T(0.25) * res[0] + T(0.5) * res[1] + T(0.25) * rec[WR + RES + REC];
       const bool odd = f & 1;
-      if (!odd && f != 2 * K0) {
+      if (restricts && !odd && f != 2 * K0) {
         const int K = f / 2 - 1;
         bcb.template st<false>(T(0.25) * s_lo + T(0.5) * s_mid + T(0.25) * acc, cbc, (unsigned)K * (unsigned)nc * (unsigned)sizeof(T));
       }
@@ -1875,10 +2001,12 @@ __global__ __launch_bounds__(1024) void k_down2r(LevelDev<T> Lf, LevelDev<T> Lc,
       s_lo = odd ? s_lo : acc;
     }
 #pragma unroll
-    for (int m = 0; m < NU; ++m) {
-      xh[m][1] = xh[m][0];
-      xh[m][0] = xn[m];
-    }
+    for (int m = 0; m < NU; ++m)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        xh[m][1][c] = xh[m][0][c];
+        xh[m][0][c] = xn[m][c];
+      }
   });
   if (RUP) {
     write_partial(partial, sys, rr, rt.seg, rt.nseg);
@@ -1887,189 +2015,169 @@ __global__ __launch_bounds__(1024) void k_down2r(LevelDev<T> Lf, LevelDev<T> Lc,
 }
 
 // k_up2r: the up kernel of k_up2 (same output; its sweeps in the form of
-// k_down2r's relax, equal in exact arithmetic)
-// marching along y over whole grid rows, as k_down2r, without reading the
-// pre-smoothed iterate: it forms it again from b, as the down kernel did
-// (NU sweeps from zero, the same weights and order), so the down kernel of
-// the level need not store it (8 bytes per point in FP32 less for the pair,
-// 30 -> 22).  2 NU stages lag one row behind each other: at step t row t of
-// b enters, pre-sweep k + 1 runs on row t - k (k < NU; the first one
+// pair_relax, equal in exact arithmetic) on whole grid rows, as k_down2r,
+// without reading the pre-smoothed iterate: it forms it again from b, as the
+// down kernel did (NU sweeps from zero, the same weights and order), so the
+// down kernel of the level need not store it (8 bytes per point in FP32 less
+// for the pair, 30 -> 22).  2 NU stages lag one row behind each other: at step
+// t row t of b enters, pre-sweep k + 1 runs on row t - k (k < NU; the first one
 // pointwise), the last of them adds P x_c, and post-sweep m on row
 // t - NU + 1 - m (the pre-smoothing weights reversed); post-sweep NU's row
 // t - 2 NU + 1 is written on the owned rows [rows s, rows (s + 1)) of
 // segment s (rows: a launch parameter), with b.x when this is the finest
-// level.  Each thread reads the coarse values under its column (the coarse
-// columns left and right of it) from the two coarse rows that bracket the row
-// where P x_c is added.  xin is not read.
-// (FP32, up to two sweeps: at most 80 VGPRs, six waves per SIMD, three
-// 512-thread workgroups per CU)
+// level.  The even column of thread i lies between coarse columns i - 1 and i,
+// the odd one on coarse column i; fine row r takes coarse row r / 2 (rounded
+// down), an even one the mean with the coarse row before it, which is the row
+// that the step before took.
 template <typename T, bool VAR, int NU, bool DOT>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && NU <= 2 ? 6 : 1))) void k_up2r(LevelDev<T> Lc, LevelDev<T> Lf, const T* __restrict__ xc,
+__global__ __launch_bounds__(kRowThreads) void k_up2r(LevelDev<T> Lc, LevelDev<T> Lf, const T* __restrict__ xc,
                                                const T* __restrict__ xin, const T* __restrict__ b,
                                                T* __restrict__ xout, const T* __restrict__ shift,
                                                const int* __restrict__ active, Sweeps<T> om,
                                                double* __restrict__ partial, unsigned long long* __restrict__ ctr,
                                                Fin fin, int rows) {
   (void)xin;
-  constexpr int LW = 1024 + 2;
   constexpr int NS = 2 * NU;   // stages: NU pre-sweeps (the last one adds P x_c), NU post-sweeps
-  __shared__ T sx[NS - 1][LW];   // newest row of stages 0 .. NS - 2 (the next stage's left/right neighbours)
+  constexpr int WORDS = up_words(NU), REC = row_rec(WORDS);   // LDS: the pairs of stages 0 .. NS - 2
+  constexpr int LEAD = row_lead<T>();
   const RowTile rt = row_tile();
   const int sys = rt.sys;
-  constexpr int LEAD = up_row_lead<T, VAR, NU>();
   if (!active[sys]) return;
   count_bytes_row(rt, ctr, (unsigned long long)Lf.N * sizeof(T) * 2 + (unsigned long long)Lc.N * sizeof(T) +
                                    (VAR && sys == 0 ? (unsigned long long)Lf.N * sizeof(T) * 2 : 0ULL));
   const int nf = Lf.n, nc = Lc.n;
   const int y0 = rt.seg * rows, y1 = min(y0 + rows, nf);   // owned fine rows
-  const int i = threadIdx.x;
-  const int NT = blockDim.x;
-  const bool col_on = i < nf;
-  const int ic = min(i, nf - 1);
+  const int i = threadIdx.x, NT = blockDim.x;
   const T sh = shift[sys];
   const T rcon = jacobi_recip(Lf.wc * T(4) + sh);
   const long long off = (long long)sys * Lf.N;
-  const T* __restrict__ xcs = xc + (long long)sys * Lc.N;
-  const T* __restrict__ bs = b + off;
-  T* __restrict__ xs = xout + off;
-  const unsigned cb = (unsigned)ic * (unsigned)sizeof(T), ib = (unsigned)i * (unsigned)sizeof(T);
-  const unsigned rowb = (unsigned)nf * (unsigned)sizeof(T);   // bytes per grid row
-  const RowBuf<T> xcb(xcs, Lc.N), bsb(bs, Lf.N), xsb(xs, Lf.N);
-  const RowBuf<T> w0b(VAR ? Lf.wf0 : bs, VAR ? (long long)(nf + 1) * nf : 1), w1b(VAR ? Lf.wf1 : bs, VAR ? (long long)(nf + 1) * nf : 1);
-  const int q = 1 + i;
-  if (i < 2) {
-    const int pq = i == 0 ? 0 : NT + 1;
-#pragma unroll
-    for (int k = 0; k < NS - 1; ++k) sx[k][pq] = T(0);
-  }
-  auto row_on = [&](int r) { return col_on && r >= 0 && r < nf; };
-  auto crow = [&](int r) { return min(max(r, 0), nf - 1); };
-  struct Faces { T l, r, d, u; };
-  auto load_faces = [&](int r) {
-    Faces f{T(0), T(0), T(0), T(0)};
-    if (VAR) {
-      const int rr = crow(r);
-      const unsigned o0 = (unsigned)rr * (unsigned)(nf + 1) * (unsigned)sizeof(T), o1 = (unsigned)rr * rowb;
-      f.l = w0b.ld(cb, o0);
-      f.r = w0b.ld(cb + (unsigned)sizeof(T), o0);
-      f.d = w1b.ld(cb, o1);
-      f.u = w1b.ld(cb, o1 + rowb);
-    }
-    return f;
+  const RowPair<T, VAR> pr(Lf, b + off);
+  const RowBuf<T> xcb(xc + (long long)sys * Lc.N, Lc.N), bsb(b + off, Lf.N), xsb(xout + off, Lf.N);
+  typedef typename RowPair<T, VAR>::Faces Faces;
+  T* lds = reinterpret_cast<T*>(row_lds);
+  for (int j = i; j < (NT + 2) * REC; j += NT) lds[j] = T(0);
+  T* rec = lds + (i + 1) * REC;
+  // coarse columns i - 1 and i (0 outside the coarse grid)
+  const unsigned ca0 = i >= 1 && i - 1 < nc ? (unsigned)(i - 1) * (unsigned)sizeof(T) : kOffGrid,
+                 ca1 = i < nc ? (unsigned)i * (unsigned)sizeof(T) : kOffGrid;
+  auto load_c = [&](int r, T (&v)[2]) {   // of fine row r
+    const unsigned ko = (unsigned)min(max(r >> 1, 0), nc - 1) * (unsigned)nc * (unsigned)sizeof(T);
+    v[0] = xcb.ld(ca0, ko);
+    v[1] = xcb.ld(ca1, ko);
   };
-  auto rdiag = [&](const Faces& f, int r) {
-    if (!VAR) return row_on(r) ? rcon : T(0);
-    return row_on(r) ? jacobi_recip(f.l + f.r + f.d + f.u + sh) : T(0);
+  // their in-row interpolation at the pair's columns (0 off the coarse rows)
+  auto interp = [&](int r, const T (&v)[2], T (&h)[2]) {
+    const T k = (r >> 1) >= 0 && (r >> 1) < nc ? T(0.5) : T(0);
+    h[0] = k * (v[0] + v[1]);
+    h[1] = (k + k) * v[1];
   };
-  // the damped Jacobi update in the form of k_down2r's relax
-  auto relax = [&](const Faces& f, const T* X, T xc_, T xd, T xu, T bb, T w, T r) {
-    const T xl = X[q - 1], xr = X[q + 1];
-    const T nb = VAR ? bb + f.l * xl + f.r * xr + f.d * xd + f.u * xu : bb + Lf.wc * ((xl + xr) + (xd + xu));
-    return xc_ + w * (r * nb - xc_);
-  };
-  // the coarse columns of this fine column: ia (and ia + 1 for an even column)
-  const int ia = (i & 1) ? (i - 1) / 2 : i / 2 - 1;
-  const bool ia0_on = ia >= 0 && ia < nc, ia1_on = ia + 1 >= 0 && ia + 1 < nc;
-  const unsigned ca0 = (unsigned)min(max(ia, 0), nc - 1) * (unsigned)sizeof(T),
-                 ca1 = (unsigned)min(max(ia + 1, 0), nc - 1) * (unsigned)sizeof(T);
-  // coarse row K at columns ia, ia + 1 as loaded (clamped, unmasked) and the
-  // masks that make them 0 outside the coarse grid
-  auto load_c = [&](int K, T& c0, T& c1) {
-    const int Kc_ = min(max(K, 0), nc - 1);
-    const unsigned ko = (unsigned)Kc_ * (unsigned)nc * (unsigned)sizeof(T);
-    c0 = xcb.ld(ca0, ko);
-    c1 = xcb.ld(ca1, ko);
-  };
-  auto mask_c = [&](int K, T& c0, T& c1) {
-    const bool kin = K >= 0 && K < nc;
-    c0 = kin && ia0_on ? c0 : T(0);
-    c1 = kin && ia1_on ? c1 : T(0);
-  };
-  // lowest coarse row of fine row t (odd t lies on it, even t halfway to the next)
-  auto klo = [](int t) { return (t >> 1) - 1 + (t & 1); };
   const int t0 = y0 - (NS - 1), t1 = y1 + NS - 2;
   // registers: bh[d], fw[d], rd[d] = b, faces and inverse diagonal of row
-  // t - d; xh[k][0], xh[k][1] = stage k's output at its newest row of the
-  // previous step and the one below
-  T bh[NS], xh[NS - 1][2], rd[NS];
-  Faces fw[NS];
+  // t - d (fw[d + 1].u: the faces below it); xh[k][0], xh[k][1] = stage k's
+  // output at its newest row of the previous step and the one below
+  T bh[NS][2], xh[NS - 1][2][2], rd[NS][2], hp[2], hc[2];
+  Faces fw[NS + 1];
+#pragma unroll
+  for (int d = 0; d <= NS; ++d) fw[d] = Faces{};
 #pragma unroll
   for (int d = 0; d < NS; ++d) {
-    bh[d] = T(0);
-    rd[d] = T(0);
-    fw[d] = load_faces(t0 - 1 - d);
-  }
+    pr.faces(fw[d], t0 - 1 - d);
 #pragma unroll
-  for (int k = 0; k < NS - 1; ++k) xh[k][0] = xh[k][1] = T(0);
+    for (int c = 0; c < 2; ++c) {
+      bh[d][c] = T(0);
+      rd[d][c] = T(0);
+      if (d < NS - 1) xh[d][0][c] = xh[d][1][c] = T(0);
+    }
+  }
+  {
+    T v[2];
+    load_c(t0 - NU, v);   // the row before the first one that P x_c is added on
+    interp(t0 - NU, v, hc);
+  }
   double dot = 0.0;
   ring_prologue_wait();
   __syncthreads();
   // the ring of row loads (see kRowLead): slot s of step t holds b and the
-  // faces of row t and the coarse rows klo(r), klo(r) + 1 at columns ia,
-  // ia + 1 for the row r = t - NU + 1 where P x_c is added, as loaded
-  // (clamped, unmasked); a coarse row serves four fine steps and is loaded
-  // for each (the repeats hit the cache)
-  T rb[LEAD], rl0[LEAD], rl1[LEAD], rh0[LEAD], rh1[LEAD];
+  // faces of row t and the coarse values of the row t - NU + 1 where P x_c is
+  // added, as loaded
+  T rb[LEAD][2], rc[LEAD][2];
   Faces rf[LEAD];
   auto fill = [&](int t, int s) {
-    rb[s] = bsb.ld(cb, (unsigned)crow(t) * rowb);
-    rf[s] = load_faces(t);
-    const int r = t - (NU - 1);
-    load_c(klo(r), rl0[s], rl1[s]);
-    load_c(klo(r) + 1, rh0[s], rh1[s]);
+    bsb.ld2(rb[s], pr.cb, pr.row(t));
+    pr.faces(rf[s], t);
+    load_c(t - (NU - 1), rc[s]);
   };
 #pragma unroll
   for (int s = 0; s < LEAD; ++s) fill(t0 + s, s);
   ring_march<LEAD>(t0, t1, [&](int t, auto slot) {
     constexpr int s = decltype(slot)::value;
+    constexpr int WR = (s & 1) * WORDS, RD = WORDS - WR;   // the record's halves of this step and the one before
 #pragma unroll
-    for (int d = NS - 1; d > 0; --d) {
-      bh[d] = bh[d - 1];
-      fw[d] = fw[d - 1];
-      rd[d] = rd[d - 1];
+    for (int d = NS; d > 0; --d) fw[d] = fw[d - 1];
+#pragma unroll
+    for (int d = NS - 1; d > 0; --d)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        bh[d][c] = bh[d - 1][c];
+        rd[d][c] = rd[d - 1][c];
+      }
+    if (VAR) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) fw[0].l[c] = ring_take(rf[s].l[c]);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) fw[0].u[c] = ring_take(rf[s].u[c]);
     }
-    if (VAR) fw[0] = Faces{ring_take(rf[s].l), ring_take(rf[s].r), ring_take(rf[s].d), ring_take(rf[s].u)};
-    rd[0] = rdiag(fw[0], t);
-    bh[0] = row_on(t) ? rb[s] : T(0);
-    // P x_c on row r = t - NU + 1 (multilinear, the expressions of k_up2)
+    pair_recip<T, VAR>(rd[0], pr, pr.in(t), fw[0], fw[1].u, sh, rcon);
+    bh[0][0] = rb[s][0];
+    bh[0][1] = rb[s][1];
+    // P x_c on row r = t - NU + 1
     const int r = t - (NU - 1);
-    T lo0 = rl0[s], lo1 = rl1[s], hi0 = rh0[s], hi1 = rh1[s];
-    mask_c(klo(r), lo0, lo1);
-    mask_c(klo(r) + 1, hi0, hi1);
-    // without a branch on the column's parity (odd and even columns share a
-    // wave): an odd column counts its one coarse column twice, which the
-    // weights 1/2 and 1/4 undo exactly
-    const bool odd_col = i & 1;
-    const T sl = lo0 + (odd_col ? lo0 : lo1), sh_ = hi0 + (odd_col ? hi0 : hi1);
-    const T v = (r & 1) ? T(0.5) * sl : T(0.25) * (sl + sh_);
-    // stage k on row t - k from stage k - 1's output (centre row in
-    // sx[k - 1], below in xh, above just formed); the pre-sweeps are those
-    // of the down kernel (zero start, the first one pointwise)
-    T xn[NS];
-    xn[0] = sweep_w(om, 0) * bh[0] * rd[0];
+    hp[0] = hc[0];
+    hp[1] = hc[1];
+    interp(r, rc[s], hc);
+    const T kp = (r & 1) ? T(0) : T(0.5), kc = T(1) - kp;
+    // stage k on row t - k from stage k - 1's output (centre row in xh and
+    // LDS, below in xh, above just formed); the pre-sweeps are those of the
+    // down kernel (zero start, the first one pointwise)
+    T xn[NS][2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) xn[0][c] = sweep_w(om, 0) * bh[0][c] * rd[0][c];
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
-      if (k > 0) {
-        const T w = k < NU ? sweep_w(om, k) : sweep_w(om, NS - 1 - k);
-        xn[k] = relax(fw[k], sx[k - 1], xh[k - 1][0], xh[k - 1][1], xn[k - 1], bh[k], w, rd[k]);
+      if (k > 0)
+        pair_relax<T, VAR>(xn[k], fw[k], fw[k + 1].u, xh[k - 1][0], rec[RD + 2 * k - 1 - REC],
+                           rec[RD + 2 * k - 2 + REC], xh[k - 1][1], xn[k - 1], Lf.wc, bh[k],
+                           k < NU ? sweep_w(om, k) : sweep_w(om, NS - 1 - k), rd[k]);
+      if (k == NU - 1) {   // x_pre + P x_c
+        const bool in = pr.in(r);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const T v = xn[k][c] + (kp * hp[c] + kc * hc[c]);
+          xn[k][c] = in && pr.on[c] ? v : T(0);
+        }
       }
-      if (k == NU - 1) xn[k] = row_on(r) ? xn[k] + v : T(0);   // x_pre + P x_c
     }
     const int g = t - (NS - 1);
-    if (g >= y0 && g < y1 && col_on) {
-      xsb.template st<true>(xn[NS - 1], ib, (unsigned)g * rowb);
-      if (DOT) dot += (double)bh[NS - 1] * (double)xn[NS - 1];
+    if (g >= y0 && g < y1) {
+      pr.template store<true>(xsb, xn[NS - 1], g);
+      if (DOT) {
+        dot += (double)bh[NS - 1][0] * (double)xn[NS - 1][0];   // (x is 0 off the grid)
+        dot += (double)bh[NS - 1][1] * (double)xn[NS - 1][1];
+      }
     }
-    __syncthreads();   // every read of this step's LDS rows is done
 #pragma unroll
-    for (int k = 0; k < NS - 1; ++k) sx[k][q] = xn[k];
+    for (int k = 0; k < NS - 1; ++k)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) rec[WR + 2 * k + c] = xn[k][c];
     __syncthreads();
     fill(t + LEAD, s);   // refill the slot with row t + LEAD
 #pragma unroll
-    for (int k = 0; k < NS - 1; ++k) {
-      xh[k][1] = xh[k][0];
-      xh[k][0] = xn[k];
-    }
+    for (int k = 0; k < NS - 1; ++k)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        xh[k][1][c] = xh[k][0][c];
+        xh[k][0][c] = xn[k][c];
+      }
   });
   if (DOT) {
     write_partial(partial, sys, dot, rt.seg, rt.nseg);
@@ -2766,22 +2874,21 @@ __global__ __launch_bounds__(kBlock) void k_spmv_p2(LevelDev<T> L, const T* __re
   finish(fin, partial, sys, gridDim.x * gridDim.y);
 }
 
-// Row-marching version of k_spmv_p2 (launch-shape variant 3): one thread per
-// grid column, a workgroup walks `rows` rows (a launch parameter); p_new of the rows below, at
-// and above the current one stays in registers and the current row's p_new
-// is in LDS for the left/right neighbours, so z and p_old are read once per
-// point (plus one row above and below a segment).  Same values per point as
-// k_spmv_p2; two barriers per row.
-
+// Row-marching version of k_spmv_p2 (launch-shape variant 3), two columns per
+// thread: a workgroup walks `rows` rows (a launch parameter); p_new of the rows
+// below, at and above the current one stays in registers and the current row's
+// p_new is in LDS for the left/right neighbours, so z and p_old are read once
+// per point (plus one row above and below a segment).  Same values per point
+// as k_spmv_p2.
 template <typename T, bool VAR, bool XUP, bool WQ>
-__global__ __launch_bounds__(1024) void k_spmv_r2(LevelDev<T> L, const T* __restrict__ z, const T* __restrict__ pold,
+__global__ __launch_bounds__(kRowThreads) void k_spmv_r2(LevelDev<T> L, const T* __restrict__ z, const T* __restrict__ pold,
                                                   T* __restrict__ pnew, T* __restrict__ q,
                                                   const double* __restrict__ beta, const T* __restrict__ shift,
                                                   const int* __restrict__ active, double* __restrict__ partial,
                                                   unsigned long long* __restrict__ ctr, Fin fin,
                                                   T* __restrict__ x, const double* __restrict__ alpha, int rows) {
-  constexpr int LW = 1024 + 2;
-  __shared__ T sp[LW];   // p_new of the current row, zero pads at columns -1 and blockDim.x
+  constexpr int WORDS = spmv_words(), REC = row_rec(WORDS);   // LDS: p_new's pair
+  constexpr int LEAD = row_lead<T>();
   const RowTile rt = row_tile();
   const int sys = rt.sys;
   if (!active[sys]) return;
@@ -2793,33 +2900,40 @@ __global__ __launch_bounds__(1024) void k_spmv_r2(LevelDev<T> L, const T* __rest
   const int n = L.n;
   const int i = threadIdx.x, NT = blockDim.x;
   const int j0 = rt.seg * rows, j1 = min(j0 + rows, n);
-  const bool col_on = i < n;
-  const int ic = min(i, n - 1);
-  const int qi = 1 + i;
   const long long off = (long long)sys * L.N;
   const T* __restrict__ zs = z + off;
   // beta = 0 (first iteration): p_old may hold anything, so read z in its place
   const T* __restrict__ pe = bt == T(0) ? zs : pold + off;
-  const unsigned cb = (unsigned)ic * (unsigned)sizeof(T), ib = (unsigned)i * (unsigned)sizeof(T);
-  const unsigned rowb = (unsigned)n * (unsigned)sizeof(T);   // bytes per grid row
+  const RowPair<T, VAR> pr(L, zs);
   const RowBuf<T> zsb(zs, L.N), peb(pe, L.N), xb(XUP ? x + off : zs, L.N), pnb(pnew + off, L.N), qb(WQ ? q + off : pnew + off, L.N);
-  const RowBuf<T> w0b(VAR ? L.wf0 : zs, VAR ? (long long)(n + 1) * n : 1), w1b(VAR ? L.wf1 : zs, VAR ? (long long)(n + 1) * n : 1);
+  typedef typename RowPair<T, VAR>::Faces Faces;
   const T s_ = shift[sys];
-  if (i < 2) sp[i == 0 ? 0 : NT + 1] = T(0);
-  auto crow = [&](int r) { return min(max(r, 0), n - 1); };
-  // 1 on the grid, 0 off it: a factor rather than a select (a select lets the
-  // compiler move a load into a branch and wait there for every load in flight)
-  auto on_f = [&](int r) { return (col_on && r >= 0 && r < n) ? T(1) : T(0); };
-  // p_new below and at row j0 (dn, c) and p_old at row j0 (pc)
-  T dn, c, pc;
+  T* lds = reinterpret_cast<T*>(row_lds);
+  for (int j = i; j < (NT + 2) * REC; j += NT) lds[j] = T(0);
+  T* rec = lds + (i + 1) * REC;
+  __syncthreads();
+  // p_new of a row off the grid is 0: a factor rather than a select (a select
+  // lets the compiler move a load into a branch and wait there for every load
+  // in flight)
+  auto p_new = [&](const T (&zv)[2], const T (&ev)[2], int r, T (&v)[2]) {
+    const T m = pr.in(r) ? T(1) : T(0);
+    v[0] = (zv[0] + bt * ev[0]) * m;
+    v[1] = (zv[1] + bt * ev[1]) * (m * pr.m1);
+  };
+  // p_new below and at row j0 (dn, c), p_old at row j0 (pc), the faces below it
+  T dn[2], c[2], pc[2], fd[2] = {T(0), T(0)};
   {
-    const int rb = crow(j0 - 1) * n + ic, rc = j0 * n + ic;
-    const T zb = zs[rb], eb = pe[rb], zc = zs[rc], ec = pe[rc];
-    dn = (zb + bt * eb) * on_f(j0 - 1);
-    c = (zc + bt * ec) * on_f(j0);
-    pc = ec;
+    T zb[2], eb[2], zc[2];
+    zsb.ld2(zb, pr.cb, pr.row(j0 - 1));
+    peb.ld2(eb, pr.cb, pr.row(j0 - 1));
+    zsb.ld2(zc, pr.cb, pr.row(j0));
+    peb.ld2(pc, pr.cb, pr.row(j0));
+    pr.above(fd, j0 - 1);
+    p_new(zb, eb, j0 - 1, dn);
+    p_new(zc, pc, j0, c);
   }
-  sp[qi] = c;
+  rec[WORDS] = c[0];   // the half that the first step reads
+  rec[WORDS + 1] = c[1];
   double dot = 0.0;
   ring_prologue_wait();
   __syncthreads();
@@ -2828,46 +2942,44 @@ __global__ __launch_bounds__(1024) void k_spmv_r2(LevelDev<T> L, const T* __rest
     // the ring of row loads (see kRowLead): slot s of step j holds z and
     // p_old of row j + 1 and x and the faces of row j, as loaded (clamped
     // rows, unmasked)
-    T rz[kRowLead], re[kRowLead], rx[kRowLead], rfl[kRowLead], rfr[kRowLead], rfd[kRowLead], rfu[kRowLead];
+    T rz[LEAD][2], re[LEAD][2], rx[LEAD][2];
+    Faces rf[LEAD];
     auto fill = [&](int j, int s) {
-      const unsigned ra = (unsigned)crow(j + 1) * rowb, rw = (unsigned)crow(j) * rowb;
-      rz[s] = zsb.ld(cb, ra);
-      re[s] = peb.ld(cb, ra);
-      rx[s] = UPD ? xb.ld(cb, rw) : T(0);
-      if (VAR) {
-        const unsigned fx = (unsigned)crow(j) * (unsigned)(n + 1) * (unsigned)sizeof(T);
-        rfl[s] = w0b.ld(cb, fx);
-        rfr[s] = w0b.ld(cb + (unsigned)sizeof(T), fx);
-        rfd[s] = w1b.ld(cb, rw);
-        rfu[s] = w1b.ld(cb, rw + rowb);
-      }
+      const unsigned ra = pr.row(j + 1);
+      zsb.ld2(rz[s], pr.cb, ra);
+      peb.ld2(re[s], pr.cb, ra);
+      if (UPD) xb.ld2(rx[s], pr.cb, pr.row(j));
+      pr.faces(rf[s], j);
     };
 #pragma unroll
-    for (int s = 0; s < kRowLead; ++s) fill(j0 + s, s);
-    ring_march(j0, j1 - 1, [&](int j, auto slot) {
+    for (int s = 0; s < LEAD; ++s) fill(j0 + s, s);
+    ring_march<LEAD>(j0, j1 - 1, [&](int j, auto slot) {
       constexpr int s = decltype(slot)::value;
-      const int row = j * n;   // 2D grids: fewer than 2^31 points
-      const T up = (rz[s] + bt * re[s]) * on_f(j + 1);
-      const T lv = sp[qi - 1], rv = sp[qi + 1];
-      T qv;
-      if (!VAR) qv = L.wc * ((c - lv) + (c - rv) + (c - dn) + (c - up)) + s_ * c;
-      else qv = rfl[s] * (c - lv) + rfr[s] * (c - rv) + rfd[s] * (c - dn) + rfu[s] * (c - up) + s_ * c;
-      if (col_on) {
-        const unsigned g = (unsigned)row * (unsigned)sizeof(T);
-        pnb.template st<true>(c, ib, g);
-        if (WQ) qb.template st<true>(qv, ib, g);
-        // the deferred update uses p_old = pc (pe is p_old whenever alpha != 0)
-        if (UPD) xb.template st<true>(rx[s] + ap * pc, ib, g);
-        dot += (double)c * (double)qv;
+      constexpr int WR = (s & 1) * WORDS, RD = WORDS - WR;
+      T up[2], qv[2];
+      p_new(rz[s], re[s], j + 1, up);
+      pair_apply<T, VAR>(qv, rf[s], fd, c, rec[RD + 1 - REC], rec[RD + REC], dn, up, L.wc, s_);
+      pr.template store<true>(pnb, c, j);
+      if (WQ) pr.template store<true>(qb, qv, j);
+      // the deferred update uses p_old = pc (pe is p_old whenever alpha != 0)
+      if (UPD) {
+        const T xv[2] = {rx[s][0] + ap * pc[0], rx[s][1] + ap * pc[1]};
+        pr.template store<true>(xb, xv, j);
       }
-      const T pn = ring_take(re[s]);   // p_old of row j + 1, the next step's pc
-      __syncthreads();   // every read of this row's p_new is done
-      sp[qi] = up;
+      // (off the grid c is 0)
+      dot += (double)c[0] * (double)qv[0];
+      dot += (double)c[1] * (double)qv[1];
+      rec[WR] = up[0];
+      rec[WR + 1] = up[1];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        pc[e] = ring_take(re[s][e]);   // p_old of row j + 1, the next step's pc
+        if (VAR) fd[e] = ring_take(rf[s].u[e]);
+        dn[e] = c[e];
+        c[e] = up[e];
+      }
       __syncthreads();
-      fill(j + kRowLead, s);
-      dn = c;
-      c = up;
-      pc = pn;
+      fill(j + LEAD, s);
     });
   };
   if (XUP && ap != T(0)) walk(std::true_type{});
@@ -3955,9 +4067,9 @@ void Launch<T>::spmv_p(int dim, bool var, const LevelDev<T>& L, const T* z, cons
   const bool xup = x != nullptr;
   if (dim == 2 && spmv_rows(dim, L.n, tv)) {
     const int rows = rows_seg(tv);
-    const dim3 g = rows_grid((L.n + rows - 1) / rows, nsys), blk(rows_threads(L.n));
+    const dim3 g = rows_grid((L.n + rows - 1) / rows, nsys), blk(pair_threads(L.n));
 #define K_SR(V, X_, Q_) \
-  hipLaunchKernelGGL((k_spmv_r2<T, V, X_, Q_>), g, blk, 0, st, L, z, pold, pnew, q, beta, shift, active, partial, \
+  hipLaunchKernelGGL((k_spmv_r2<T, V, X_, Q_>), g, blk, row_lds_bytes<T>(spmv_words(), blk.x), st, L, z, pold, pnew, q, beta, shift, active, partial, \
                      ctr, fin, x, alpha, rows)
     if (var) {
       if (!q) K_SR(true, true, false); else if (xup) K_SR(true, true, true); else K_SR(true, false, true);
@@ -4029,9 +4141,9 @@ bool Launch<T>::fused_down(int dim, bool var, int nu, const LevelDev<T>& Lf, con
   if (down_rows(dim, Lf.n, tv)) {
     if (up_rows(dim, Lf.n, tv_up)) xout = nullptr;   // k_up2r forms the pre-smoothed iterate again
     const int ky = rows_seg(tv) / 2;
-    const dim3 g = rows_grid((Lc.n + ky - 1) / ky, nsys), blk(rows_threads(Lf.n));
+    const dim3 g = rows_grid((Lc.n + ky - 1) / ky, nsys), blk(pair_threads(Lf.n));
 #define K_DR0(V, NU_, R_)                                                                                     \
-  hipLaunchKernelGGL((k_down2r<T, V, NU_, R_>), g, blk, 0, st, Lf, Lc, b, xout, bc, shift, active, om, ctr, p, \
+  hipLaunchKernelGGL((k_down2r<T, V, NU_, R_>), g, blk, row_lds_bytes<T>(down_words(NU_, R_), blk.x), st, Lf, Lc, b, xout, bc, shift, active, om, ctr, p, \
                      alpha, bout, partial, fin, ky)
 #define K_DR(V, NU_) do { if (rup) K_DR0(V, NU_, true); else K_DR0(V, NU_, false); } while (0)
     if (var) {
@@ -4122,9 +4234,9 @@ bool Launch<T>::fused_up(int dim, bool var, int nu, const LevelDev<T>& Lc, const
   if (dim != 2 || nu < 1 || nu > 3) return false;
   if (up_rows(dim, Lf.n, tv)) {
     const int rows = rows_seg(tv);
-    const dim3 g = rows_grid((Lf.n + rows - 1) / rows, nsys), blk(rows_threads(Lf.n));
+    const dim3 g = rows_grid((Lf.n + rows - 1) / rows, nsys), blk(pair_threads(Lf.n));
 #define K_UR0(V, NU_, D_)                                                                                        \
-  hipLaunchKernelGGL((k_up2r<T, V, NU_, D_>), g, blk, 0, st, Lc, Lf, xc, xin, b, xout, shift, active, om, partial, \
+  hipLaunchKernelGGL((k_up2r<T, V, NU_, D_>), g, blk, row_lds_bytes<T>(up_words(NU_), blk.x), st, Lc, Lf, xc, xin, b, xout, shift, active, om, partial, \
                      ctr, fin, rows)
 #define K_UR(V, NU_) do { if (dot) K_UR0(V, NU_, true); else K_UR0(V, NU_, false); } while (0)
     if (var) {
