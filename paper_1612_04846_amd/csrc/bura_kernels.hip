@@ -1949,7 +1949,7 @@ __global__ __launch_bounds__(kRowThreads) void k_down2r(LevelDev<T> Lf, LevelDev
 #pragma unroll
       for (int c = 0; c < 2; ++c) bh[0][c] -= am * q[c];
       if (t >= 2 * K0 && t < f1) {
-        pr.template store<true>(bob, bh[0], t);
+        pr.template store<false>(bob, bh[0], t);
         const double r0 = (double)bh[0][0], r1 = (double)(bh[0][1] * pr.m1);   // (lanes past the grid: 0)
         rr += r0 * r0;
         rr += r1 * r1;
@@ -1972,7 +1972,7 @@ __global__ __launch_bounds__(kRowThreads) void k_down2r(LevelDev<T> Lf, LevelDev
     for (int c = 0; c < 2; ++c) res[c] = bh[NU][c] - res[c];
     // the pre-smoothed iterate: sweep NU's newest row t - NU + 1
     const int gx = t - NU + 1;
-    if (keepx && gx >= 2 * K0 && gx < f1) pr.template store<true>(xsb, xn[NU - 1], gx);
+    if (keepx && gx >= 2 * K0 && gx < f1) pr.template store<false>(xsb, xn[NU - 1], gx);
 #pragma unroll
     for (int m = 0; m < NU; ++m)
 #pragma unroll
@@ -2159,7 +2159,7 @@ __global__ __launch_bounds__(kRowThreads) void k_up2r(LevelDev<T> Lc, LevelDev<T
     }
     const int g = t - (NS - 1);
     if (g >= y0 && g < y1) {
-      pr.template store<true>(xsb, xn[NS - 1], g);
+      pr.template store<false>(xsb, xn[NS - 1], g);
       if (DOT) {
         dot += (double)bh[NS - 1][0] * (double)xn[NS - 1][0];   // (x is 0 off the grid)
         dot += (double)bh[NS - 1][1] * (double)xn[NS - 1][1];
@@ -2959,12 +2959,12 @@ __global__ __launch_bounds__(kRowThreads) void k_spmv_r2(LevelDev<T> L, const T*
       T up[2], qv[2];
       p_new(rz[s], re[s], j + 1, up);
       pair_apply<T, VAR>(qv, rf[s], fd, c, rec[RD + 1 - REC], rec[RD + REC], dn, up, L.wc, s_);
-      pr.template store<true>(pnb, c, j);
-      if (WQ) pr.template store<true>(qb, qv, j);
+      pr.template store<false>(pnb, c, j);
+      if (WQ) pr.template store<false>(qb, qv, j);
       // the deferred update uses p_old = pc (pe is p_old whenever alpha != 0)
       if (UPD) {
         const T xv[2] = {rx[s][0] + ap * pc[0], rx[s][1] + ap * pc[1]};
-        pr.template store<true>(xb, xv, j);
+        pr.template store<false>(xb, xv, j);
       }
       // (off the grid c is 0)
       dot += (double)c[0] * (double)qv[0];
