@@ -307,6 +307,14 @@ void run_pass(SinePass a, long long batches, hipStream_t st) {
 // 16 for L = 128), in the self-sorting order, the values exchanged through LDS
 // between steps, real parts first and then imaginary parts (half the LDS of
 // complex values, so two workgroups of 512 threads fit a CU).
+//
+// What bounds it is the latency of those steps: at 1023^2 and 30 systems the
+// arithmetic alone is about 50 us a pass and the traffic 50 (the scaled pass,
+// which only writes) or 100.  With every value loaded and scaled at both of its
+// places and 130 - 177 registers (2 - 3 waves per SIMD) the passes took 245 and
+// 140 us; one load per value, LDS positions that are constants away from one
+// register and twiddle powers formed in pairs leave 98 - 116 registers, 4 waves,
+// and 121 and 110 us (255^3, 9 systems: 1030, 717 and 660 -> 803, 527 and 467).
 // --------------------------------------------------------------------------
 struct FftPass {
   const double* in;
@@ -327,6 +335,9 @@ struct FftPass {
   double* partial;
   unsigned long long* ctr;
 };
+
+// two neighbouring values of an odd row length: 8-byte aligned
+typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
 
 struct cplx {
   double x, y;
@@ -402,23 +413,40 @@ __device__ __forceinline__ void dft(cplx* v, int s, int d) {
   }
 }
 
-// v[s + i d] *= w^i, i < R, from w, w^2, w^4, w^8 (at most three roundings)
+// w^1, w^2, w^4, w^8 (as far as R needs them) for the twiddles w^i, i < R, of
+// table step m
 template <int R>
-__device__ __forceinline__ void twiddle(cplx* v, int s, int d, const double2* __restrict__ tw, int m, int mask) {
-  cplx w[R > 8 ? 16 : (R > 4 ? 8 : 4)];
+struct Twiddle {
+  cplx w[4];
+  __device__ __forceinline__ void load(const double2* __restrict__ tw, int m, int mask) {
 #pragma unroll
-  for (int i = 1; i < R; i <<= 1) {
-    const double2 a = tw[(m * i) & mask];
-    w[i] = {a.x, a.y};
+    for (int b = 0; (1 << b) < R; ++b) {
+      const double2 a = tw[(m << b) & mask];
+      w[b] = {a.x, a.y};
+    }
   }
-#pragma unroll
-  for (int i = 3; i < R; ++i) {
-    const int top = i >= 8 ? 8 : (i >= 4 ? 4 : 2);
-    if (i != top) w[i] = w[top] * w[i - top];
+  // v[s + i d] *= w^i (at most three roundings; w^i and w^{i + 8} together, so
+  // that few powers are held at a time)
+  __device__ __forceinline__ void apply(cplx* v, int s, int d) const {
+    auto at = [&](int i, cplx p) {
+      if (i < R) v[s + i * d] = v[s + i * d] * p;
+      if (i + 8 < R) v[s + (i + 8) * d] = v[s + (i + 8) * d] * (w[3] * p);
+    };
+    at(1, w[0]);
+    if constexpr (R > 2) {
+      at(2, w[1]);
+      const cplx w3 = w[1] * w[0];
+      at(3, w3);
+      if constexpr (R > 4) {
+        at(4, w[2]);
+        at(5, w[2] * w[0]);
+        at(6, w[2] * w[1]);
+        at(7, w[2] * w3);
+      }
+      if constexpr (R > 8) v[s + 8 * d] = v[s + 8 * d] * w[3];
+    }
   }
-#pragma unroll
-  for (int i = 1; i < R; ++i) v[s + i * d] = v[s + i * d] * w[i];
-}
+};
 
 // Workgroup shape: T = L/16 threads per pair of lines.  Rows: 256 threads (at
 // least one pair).  Columns: pairs side by side so that a row of the tile is
@@ -430,10 +458,12 @@ constexpr int fft_pairs(bool row) {
 }
 
 template <int LOG, bool ROW, bool SCALE>
-__global__ __launch_bounds__((1 << LOG) / 16 * fft_pairs<LOG>(ROW)) void k_sine_fft(FftPass a) {
+__global__ __launch_bounds__((1 << LOG) / 16 * fft_pairs<LOG>(ROW)) __attribute__((amdgpu_waves_per_eu(4))) void
+k_sine_fft(FftPass a) {
   constexpr int L = 1 << LOG, N = L / 2, T = L / 16, P = fft_pairs<LOG>(ROW);
   constexpr int RL = LOG == 7 ? 8 : (L / 256);   // the last step's radix (1: there is none)
-  __shared__ double sh[L * P];
+  constexpr int LP = L + L / 16;   // a line of padded positions (see below)
+  __shared__ double sh[LP * P];
   const long long id = blockIdx.x;
   // neighbouring tiles on one XCD: a tile row of columns may be half a line
   const long long grp = (id & 7) * a.per + (id >> 3);
@@ -465,9 +495,9 @@ __global__ __launch_bounds__((1 << LOG) / 16 * fft_pairs<LOG>(ROW)) void k_sine_
     return;
   }
   double mu0 = 0.0, mu1 = 0.0;
-  // the split order of the eigenvalue table: odd numbers first
-  auto mu_at = [&](long long k) { return a.mu[(k & 1) ? (k - 1) / 2 : N / 2 + k / 2 - 1]; };
   if (SCALE) {
+    // the split order of the eigenvalue table: odd numbers first
+    auto mu_at = [&](long long k) { return a.mu[(k & 1) ? (k - 1) / 2 : N / 2 + k / 2 - 1]; };
     auto across = [&](long long l) {
       l = min(l, a.lines - 1);
       return a.axes == 1 ? mu_at(l + 1) : mu_at(l / n + 1) + mu_at(l % n + 1);
@@ -475,94 +505,150 @@ __global__ __launch_bounds__((1 << LOG) / 16 * fft_pairs<LOG>(ROW)) void k_sine_
     mu0 = fma(a.wc, across(l0), a.shift[sys]);
     mu1 = fma(a.wc, across(l0 + 1), a.shift[sys]);
   }
+  // The odd extension z_j = x_j, z_{L-j} = -x_j, 0 at 0 and N: this thread's
+  // values t + i T.  The first half (i < 8) is loaded; the second half is the
+  // first half of other threads, mirrored, and comes through LDS (loaded and
+  // scaled twice, a scaled pass took 1.7 times as long).  Loads are clamped to
+  // a line and a value that exist (a last line without a partner takes the one
+  // before it along): what is not on the grid is 0 at value 0, and is not
+  // stored otherwise.
   cplx v[16];
-  double ssq = 0.0;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    // odd extension: z_j = x_j, z_{L-j} = -x_j, 0 at 0 and N
-    const int e = t + i * T;
-    const int j = i < 8 ? e : L - e;
-    const bool in_grid = j >= 1 && j < N;
-    v[i] = {0.0, 0.0};
-    if (in_grid && on0) v[i].x = in[addr(j, l0)];
-    if (in_grid && on1) v[i].y = in[addr(j, l0 + 1)];
+  const long long step = ROW ? 1 : a.ld;
+  const double* __restrict__ p0;
+  const double* __restrict__ p1;
+  {
+    const long long c0 = min(l0, a.lines - 1), c1 = min(l0 + 1, a.lines - 1);
+    const long long q = (long long)(t - 1) * step;   // value t (value 0: see below)
+    p0 = in + (ROW ? c0 * n : (on1 ? c0 : c1 - 1)) + q;
+    p1 = in + (ROW ? c1 * n : 0) + q;
   }
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    if (ROW && !SCALE && i < 8) ssq += v[i].x * v[i].x + v[i].y * v[i].y;
-    if (SCALE) {
-      const int e = t + i * T;
-      const int j = min(max(i < 8 ? e : L - e, 1), N - 1);
-      const double m = mu_at(j);
+  for (int i = 0; i < 8; ++i) {
+    const long long o = i == 0 && t == 0 ? step : (long long)i * T * step;
+    if (ROW) {
+      v[i] = {p0[o], p1[o]};
+    } else {
+      const f64x2u w = *reinterpret_cast<const f64x2u*>(p0 + o);
+      v[i] = {on1 ? w[0] : w[1], w[1]};
+    }
+    if (i == 0 && t == 0) v[i] = {0.0, 0.0};
+  }
+  // the workgroup's sum of squares, in fixed order (before the transform, so
+  // that nothing of it stays in registers)
+  constexpr int NW = (T * P + 63) / 64;
+  __shared__ double sw[NW];
+  if (ROW && !SCALE) {
+    double ssq = 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ssq += (on0 ? v[i].x * v[i].x : 0.0) + (on1 ? v[i].y * v[i].y : 0.0);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ssq += __shfl_xor(ssq, o, 64);
+    if ((tid & 63) == 0) sw[tid >> 6] = ssq;
+  }
+  if (SCALE) {
+    // value j = t + i T has the parity of t (T is even)
+    const double* __restrict__ pm = a.mu + ((t & 1) ? (t - 1) / 2 : N / 2 + t / 2 - 1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const double m = pm[i * (T / 2)];
       v[i].x *= recip(fma(a.wc, m, mu0));
       v[i].y *= recip(fma(a.wc, m, mu1));
+      // (all the reciprocals at once do not fit the registers of 4 waves)
+      if (i & 1) __builtin_amdgcn_sched_barrier(0);
     }
-    if (i >= 8) v[i] = {-v[i].x, -v[i].y};
   }
-  // LDS position of value q of this thread's pair: the low four bits of q are
-  // mixed with the next four, so the strided writes of a step spread over the banks
-  auto at = [&](int q) {
-    const int z = q ^ ((q >> 4) & 15);
-    return ROW ? pair * L + z : z * P + pair;
-  };
-  // hand the values over: put(i) is where value i goes, get(i) what comes back
-  auto exchange = [&](auto put, auto get) {
+  // Value q of a pair is at position q + q / 16 of its line in LDS: the strided
+  // accesses of a step fall in different banks, and every access of a thread
+  // is a constant away from one position (all the constants here are
+  // multiples of 16 or below the next one), so that few registers hold
+  // addresses.  C: what a position of a line is worth in LDS.
+  constexpr int C = ROW ? 1 : P;
+  auto pos = [](int q) constexpr { return q + q / 16; };
+  double* const line = sh + (ROW ? pair * LP : pair);
+  {
+    double* w = line + pos(t) * C;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      w[pos(i * T) * C] = v[i].x;
+      w[pos(N + i * T) * C] = v[i].y;
+    }
+    __syncthreads();
+    // value L - (t + i T), which is value 0 for t = 0, i = 8
+    const double* r = line - (t + (t + 15) / 16) * C;
+#pragma unroll
+    for (int i = 8; i < 16; ++i) {
+      // (T = 8: L - i T is an odd multiple of 8 for odd i, and t < 8)
+      const double* ri = i == 8 && t == 0 ? line - pos(N) * C : (L - i * T) % 16 ? line - t * C : r;
+      v[i] = {-ri[pos(L - i * T) * C], -ri[pos(N + L - i * T) * C]};
+    }
+  }
+  // hand the values over: value i goes to put + its constant, what comes back
+  // is at get + its constant
+  auto exchange = [&](int put, auto put_c, int get, auto get_c) {
+    double* w = line + put * C;
+    const double* r = line + get * C;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sh[at(put(i))] = v[i].x;
+    for (int i = 0; i < 16; ++i) w[put_c(i) * C] = v[i].x;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) v[i].x = sh[at(get(i))];
+    for (int i = 0; i < 16; ++i) v[i].x = r[get_c(i) * C];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) sh[at(put(i))] = v[i].y;
+    for (int i = 0; i < 16; ++i) w[put_c(i) * C] = v[i].y;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 16; ++i) v[i].y = sh[at(get(i))];
+    for (int i = 0; i < 16; ++i) v[i].y = r[get_c(i) * C];
   };
   dft<16>(v, 0, 1);
   constexpr int M = 16 / RL;   // the last step's transforms per thread
   if constexpr (LOG >= 8) {
-    exchange([&](int i) { return t * 16 + i; }, [&](int i) { return t + i * T; });
     const int k = t & 15;
-    twiddle<16>(v, 0, 1, a.tw, k * (L / 256), L - 1);
+    Twiddle<16> w;
+    w.load(a.tw, k * (L / 256), L - 1);
+    exchange(t * 17, [](int i) { return i; }, pos(t), [&](int i) { return pos(i * T); });
+    w.apply(v, 0, 1);
     dft<16>(v, 0, 1);
     if constexpr (RL > 1)
-      exchange([&](int i) { return (t >> 4) * 256 + k + i * 16; },
-               [&](int i) { return t + (i / RL) * T + (i % RL) * 256; });
+      exchange((t >> 4) * pos(256) + k, [&](int i) { return pos(i * 16); }, pos(t),
+               [&](int i) { return pos((i / RL) * T + (i % RL) * 256); });
   } else {
-    exchange([&](int i) { return t * 16 + i; }, [&](int i) { return t + (i / RL) * T + (i % RL) * 16; });
+    // (T = 8: value t + 8 c + 16 i, of position t + 8 c + 17 i)
+    exchange(t * 17, [](int i) { return i; }, t, [&](int i) { return (i / RL) * T + (i % RL) * 17; });
   }
   if constexpr (RL > 1) {
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-      twiddle<RL>(v, m * RL, 1, a.tw, t + m * T, L - 1);
+      Twiddle<RL> w;
+      w.load(a.tw, t + m * T, L - 1);
+      w.apply(v, m * RL, 1);
       dft<RL>(v, m * RL, 1);
     }
   }
-  // coefficient k of value i; those past N repeat the first half
+  // coefficient k of value i; those past N repeat the first half (known when
+  // compiling, so the last step does not form them)
   const double sc = 0.5 * sqrt(2.0 / N);
+  const int k0 = RL > 1 ? t : (t >> 4) * 256 + (t & 15);
+  auto put = [&](auto store) {
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    constexpr int NS = L / RL;
-    const int k = RL > 1 ? t + (i / RL) * T + (i % RL) * NS : (t >> 4) * 256 + (t & 15) + i * 16;
-    if (k < 1 || k >= N) continue;
-    if (on0) out[addr(k, l0)] = -sc * v[i].y;
-    if (on1) out[addr(k, l0 + 1)] = sc * v[i].x;
-  }
-  if (ROW && !SCALE && a.partial) {
-    // fixed-order block sum of the squares
-    constexpr int NW = (T * P + 63) / 64;
-    __shared__ double sw[NW];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ssq += __shfl_xor(ssq, o, 64);
-    if ((tid & 63) == 0) sw[tid >> 6] = ssq;
-    __syncthreads();
-    if (tid == 0) {
-      double tot = 0.0;
-      for (int w = 0; w < NW; ++w) tot += sw[w];
-      a.partial[grp] = tot;
+    for (int i = 0; i < 16; ++i) {
+      constexpr int NS = L / RL;
+      if (RL > 1 ? (i % RL) >= RL / 2 : i >= 8) continue;
+      if (i == 0 && k0 == 0) continue;
+      store((RL > 1 ? (i / RL) * T + (i % RL) * NS : i * 16) * step, -sc * v[i].y, sc * v[i].x);
     }
+  };
+  double* const o0 = out + (k0 - 1) * step + l0 * (ROW ? n : 1);
+  if (!ROW && on1) {
+    put([&](long long o, double x, double y) { *reinterpret_cast<f64x2u*>(o0 + o) = f64x2u{x, y}; });
+  } else {
+    if (on0) put([&](long long o, double x, double) { o0[o] = x; });
+    if (ROW && on1) put([&](long long o, double, double y) { o0[n + o] = y; });
+  }
+  if (ROW && !SCALE && a.partial && tid == 0) {
+    double tot = 0.0;
+    for (int w = 0; w < NW; ++w) tot += sw[w];
+    a.partial[grp] = tot;
   }
 }
 
