@@ -326,6 +326,7 @@ struct FftPass {
   long long per;         // groups per XCD
   long long in_stride, out_stride, ld, lines;
   int planes, rhs_of;
+  int by_tile;           // scaled passes: the systems of a tile side by side
   const int* gate;
   int zero;
   const double* mu;      // 1D eigenvalues in the split order of the products
@@ -468,8 +469,9 @@ k_sine_fft(FftPass a) {
   // neighbouring tiles on one XCD: a tile row of columns may be half a line
   const long long grp = (id & 7) * a.per + (id >> 3);
   if (grp >= a.groups) return;
-  const long long batch = grp / a.tiles;
-  const int tile = (int)(grp - batch * a.tiles);
+  const long long nb = a.groups / a.tiles;
+  const long long batch = SCALE && a.by_tile ? grp % nb : grp / a.tiles;
+  const int tile = (int)(SCALE && a.by_tile ? grp / nb : grp - batch * a.tiles);
   const int sys = (int)(batch / a.planes);
   const int g = a.gate ? a.gate[sys] : 1;
   if (g == 0 || (g == 2 && !a.zero)) return;
@@ -682,6 +684,13 @@ void run_fft(const SinePass& p, const double2* tw, long long batches, hipStream_
   a.lines = p.lines;
   a.planes = p.planes;
   a.rhs_of = p.rhs_of;
+  // A scaled pass reads the same coefficients for every system of a right-hand
+  // side.  In 3D, where they are more than the L2s hold (32 MB), the systems of
+  // a tile go side by side and read them once: 255^3, 9 systems 803 -> 566 us.
+  // In 2D they stay in the caches and a system's neighbouring tiles, which
+  // share lines of memory, have to be close: 1023^2, 30 systems by tiles 149 us
+  // against 121.
+  a.by_tile = p.axes == 2 && p.in_stride * 8 > (32LL << 20);
   a.gate = p.gate;
   a.zero = p.zero;
   a.mu = p.mu;

@@ -3779,7 +3779,15 @@ __global__ __launch_bounds__(1024) void k_conclude(int op, const double* __restr
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   auto wave_sum = [&](const double* p, int n) {
     double v = 0.0;
-    for (int b = lane; b < n; b += 64) v += p[b];
+    int b = lane;
+    for (; b + 7 * 64 < n; b += 8 * 64) {   // eight loads in flight
+      double w[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) w[k] = p[b + k * 64];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v += w[k];
+    }
+    for (; b < n; b += 64) v += p[b];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
