@@ -42,6 +42,26 @@ __device__ __forceinline__ Tile block_tile() {
   return r;
 }
 
+// The tile of a launch whose systems share more than the L2s hold (the face
+// weights of a 3D variable-coefficient level, the FP64 right-hand side): the
+// systems of a tile run side by side on one XCD (workgroups are dealt to the 8
+// XCDs round-robin), which reads the shared values once, and an XCD has a
+// contiguous range of tiles.  127^3, 9 systems, whose weights (25 MB in FP32)
+// were read from memory once per system: a solve of 7513 us takes 7377.  (FP64
+// sweeps, whose vectors are twice as long, take the launch order: 127^3, 8
+// systems 11.1 ms, by tiles 11.7.)
+__device__ __forceinline__ Tile block_tile_shared() {
+  const unsigned lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+  const unsigned total = gridDim.x * gridDim.y * gridDim.z, x = lin & 7;
+  const unsigned idx = x * (total >> 3) + min(x, total & 7) + (lin >> 3);
+  const unsigned tile = idx / gridDim.z;
+  Tile r;
+  r.x = tile % gridDim.x;
+  r.y = tile / gridDim.x;
+  r.z = idx - tile * gridDim.z;
+  return r;
+}
+
 template <int DIM>
 __device__ __forceinline__ void tile_ijk(const Tile& tl, int n, int& i, int& j, int& k) {
   i = tl.x * kTileX + threadIdx.x;
@@ -260,28 +280,79 @@ __device__ __forceinline__ T diag_pt(const LevelDev<T>& L, int i, int j, int k, 
   return d + s;
 }
 
-// apply_pt for DIM = 3 from values already loaded: the centre, its in-plane
-// neighbours l, r, d, u and the points below (b) and above (f), each 0 outside
-// the grid.  Same arithmetic and order as apply_pt.
-template <typename T, bool VAR>
-__device__ __forceinline__ T apply_col3(const LevelDev<T>& L, int i, int j, int k, long long p, T xc, T xl, T xr,
-                                        T xd, T xu, T xb, T xf, T s, T* dg) {
+// value o of a plane whose address is the same for the workgroup: a scalar base
+// and a 32-bit offset, not a 64-bit address per lane
+template <typename T>
+__device__ __forceinline__ T plane_at(const T* __restrict__ plane, unsigned o) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(plane) + o * (unsigned)sizeof(T));
+}
+
+// The face weights of a marching thread's R rows at one plane: left, right,
+// below in y (d[R]: above the last row), below and above in z.  All of them
+// are loaded with the plane's other values, before any is used (loaded where
+// each row used them, behind the row's bounds test, every row waited for
+// memory again); the face between two rows or planes is loaded once.  127^3
+// mixed, 9 systems: 7377 -> 6524 us a solve.  FP64 sweeps would hold 160 - 280
+// registers that way and ran 5 - 8 % slower (47^3 - 127^3): they load a row's
+// weights at the row (EARLY false), the FP64 residual all at once (155 -> 151 us).
+template <typename T, bool VAR, int R, bool EARLY = sizeof(T) == 4>
+struct ColFaces {
+  T l[R], r[R], d[R + 1], b[R], f[R];
+  __device__ __forceinline__ void start(const LevelDev<T>& L, const Rows<R>& w, int k0) {
+    if (!VAR || !EARLY) return;
+#pragma unroll
+    for (int q = 0; q < R; ++q) f[q] = L.wf2[(long long)k0 * L.n * L.n + w.col[q]];
+  }
+  // the weights of row q of the grid (EARLY false)
+  __device__ __forceinline__ void row(const LevelDev<T>& L, const Rows<R>& w, int i, int j0, int k, int q) {
+    if (!VAR || EARLY) return;
+    const int n = L.n;
+    const long long fx = ((long long)k * n + j0 + q) * (n + 1) + i, fy = ((long long)k * (n + 1) + j0 + q) * n + i;
+    const long long p = (long long)k * n * n + w.col[q];
+    l[q] = L.wf0[fx];
+    r[q] = L.wf0[fx + 1];
+    d[q] = L.wf1[fy];
+    d[q + 1] = L.wf1[fy + n];
+    b[q] = L.wf2[p];
+    f[q] = L.wf2[p + (long long)n * n];
+  }
+  // the weights of every row (EARLY)
+  __device__ __forceinline__ void load(const LevelDev<T>& L, const Rows<R>& w, int i, int j0, int k) {
+    if (!VAR || !EARLY) return;
+    const int n = L.n;
+    const T* w0 = L.wf0 + (long long)k * n * (n + 1);
+    const T* w1 = L.wf1 + (long long)k * (n + 1) * n;
+    const T* w2 = L.wf2 + (long long)(k + 1) * n * n;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const unsigned o = (unsigned)(min(j0 + q, n - 1) * (n + 1) + i);
+      b[q] = f[q];
+      l[q] = plane_at(w0, o);
+      r[q] = plane_at(w0, o + 1);
+      f[q] = plane_at(w2, (unsigned)w.col[q]);
+    }
+#pragma unroll
+    for (int q = 0; q <= R; ++q) d[q] = plane_at(w1, (unsigned)(min(j0 + q, n) * n + i));
+  }
+  __device__ __forceinline__ T diag(const LevelDev<T>& L, int q, T s) const {
+    if (!VAR) return L.wc * T(6) + s;
+    return l[q] + r[q] + d[q] + d[q + 1] + (b[q] + f[q]) + s;
+  }
+};
+
+// apply_pt for DIM = 3 from values already loaded: the face weights of row q,
+// the centre, its in-plane neighbours l, r, d, u and the points below (b) and
+// above (f), each 0 outside the grid.  Same arithmetic and order as apply_pt.
+template <typename T, bool VAR, int R, bool EARLY>
+__device__ __forceinline__ T apply_col3(const LevelDev<T>& L, const ColFaces<T, VAR, R, EARLY>& w, int q, T xc, T xl, T xr,
+                                        T xd, T xu, T xb, T xf, T s) {
   if (!VAR) {
     T sum = (xc - xl) + (xc - xr) + (xc - xd) + (xc - xu);
     sum += (xc - xb) + (xc - xf);
-    if (dg) *dg = L.wc * T(6) + s;
     return L.wc * sum + s * xc;
   }
-  const int n = L.n;
-  const long long fx = ((long long)k * n + j) * (n + 1) + i;
-  const long long fy = ((long long)k * (n + 1) + j) * n + i;
-  const T wl = L.wf0[fx], wr = L.wf0[fx + 1], wd = L.wf1[fy], wu = L.wf1[fy + n];
-  const T wb = L.wf2[p], wf = L.wf2[p + (long long)n * n];
-  T acc = wl * (xc - xl) + wr * (xc - xr) + wd * (xc - xd) + wu * (xc - xu);
-  T d = wl + wr + wd + wu;
-  acc += wb * (xc - xb) + wf * (xc - xf);
-  d += wb + wf;
-  if (dg) *dg = d + s;
+  T acc = w.l[q] * (xc - xl) + w.r[q] * (xc - xr) + w.d[q] * (xc - xd) + w.d[q + 1] * (xc - xu);
+  acc += w.b[q] * (xc - xb) + w.f[q] * (xc - xf);
   return acc + s * xc;
 }
 
@@ -350,7 +421,7 @@ __global__ __launch_bounds__(kBlock) void k_jacobi3(LevelDev<T> L, const T* __re
                                                     T omega, double* __restrict__ partial,
                                                     unsigned long long* __restrict__ ctr, Fin fin, int planes) {
   constexpr int R = kMarchRows;
-  const Tile tl = block_tile();
+  const Tile tl = VAR && sizeof(T) == 4 ? block_tile_shared() : block_tile();
   const int sys = tl.z;
   if (!active[sys]) return;
   count_bytes_tile(tl, ctr, (unsigned long long)L.N * sizeof(T) * ((ZERO ? 2 : 3) + (VAR && sys == 0 ? 3 : 0)));
@@ -363,16 +434,21 @@ __global__ __launch_bounds__(kBlock) void k_jacobi3(LevelDev<T> L, const T* __re
     const T s = shift[sys];
     const T* bs = b + off;
     T* xo = xout + off;
+    ColFaces<T, VAR, R> fw;
+    fw.start(L, w, c.k0);
     if (ZERO) {
       for (int k = c.k0; k < c.k1; ++k) {
+        T bv[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) bv[r] = bs[k * nn + w.col[r]];
+        fw.load(L, w, c.i, c.j, k);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           if (!w.valid[r]) continue;
-          const long long p = k * nn + w.col[r];
-          const T bv = bs[p];
-          const T xn = omega * bv / diag_pt<T, 3, VAR>(L, c.i, c.j + r, k, s);
-          xo[p] = xn;
-          if (DOT) dot += (double)bv * (double)xn;
+          fw.row(L, w, c.i, c.j, k, r);
+          const T xn = omega * bv[r] / fw.diag(L, r, s);
+          xo[k * nn + w.col[r]] = xn;
+          if (DOT) dot += (double)bv[r] * (double)xn;
         }
       }
     } else {
@@ -399,19 +475,18 @@ __global__ __launch_bounds__(kBlock) void k_jacobi3(LevelDev<T> L, const T* __re
           bv[r] = bs[p];
         }
         const T hd = xs[pk + w.col_d], hu = xs[pk + w.col_u];
+        fw.load(L, w, c.i, c.j, k);
         T above[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) above[r] = k + 1 < n ? xa[r] : T(0);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           if (!w.valid[r]) continue;
-          const long long p = pk + w.col[r];
-          T dg;
-          const T ax = apply_col3<T, VAR>(L, c.i, c.j + r, k, p, centre[r], w.il ? xl[r] : T(0),
-                                          w.ir ? xr[r] : T(0), w.down(r, centre, hd), w.up(r, centre, hu),
-                                          below[r], above[r], s, &dg);
-          const T xn = centre[r] + omega * (bv[r] - ax) / dg;
-          xo[p] = xn;
+          fw.row(L, w, c.i, c.j, k, r);
+          const T ax = apply_col3(L, fw, r, centre[r], w.il ? xl[r] : T(0), w.ir ? xr[r] : T(0),
+                                             w.down(r, centre, hd), w.up(r, centre, hu), below[r], above[r], s);
+          const T xn = centre[r] + omega * (bv[r] - ax) / fw.diag(L, r, s);
+          xo[pk + w.col[r]] = xn;
           if (DOT) dot += (double)bv[r] * (double)xn;
         }
 #pragma unroll
@@ -491,7 +566,7 @@ __global__ __launch_bounds__(kBlock) void k_jacobi0_rup3p(LevelDev<T> L, const T
                                                           T omega, double* __restrict__ partial,
                                                           unsigned long long* __restrict__ ctr, Fin fin) {
   constexpr int R = kMarchRows;
-  const Tile tl = block_tile();
+  const Tile tl = VAR && sizeof(T) == 4 ? block_tile_shared() : block_tile();
   const int sys = tl.z;
   if (!active[sys]) return;
   // b_old and p read, b and x_out written; faces once per launch
@@ -514,6 +589,8 @@ __global__ __launch_bounds__(kBlock) void k_jacobi0_rup3p(LevelDev<T> L, const T
       below[r] = c.k0 > 0 ? pb0 : T(0);
       centre[r] = ps[p0];
     }
+    ColFaces<T, VAR, R> fw;
+    fw.start(L, w, c.k0);
     for (int k = c.k0; k < c.k1; ++k) {
       const long long pk = k * nn;
       T pa[R], pl[R], pr[R], bv[R];
@@ -526,6 +603,7 @@ __global__ __launch_bounds__(kBlock) void k_jacobi0_rup3p(LevelDev<T> L, const T
         bv[r] = bs[p];
       }
       const T hd = ps[pk + w.col_d], hu = ps[pk + w.col_u];
+      fw.load(L, w, c.i, c.j, k);
       T above[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) above[r] = k + 1 < n ? pa[r] : T(0);
@@ -533,12 +611,12 @@ __global__ __launch_bounds__(kBlock) void k_jacobi0_rup3p(LevelDev<T> L, const T
       for (int r = 0; r < R; ++r) {
         if (!w.valid[r]) continue;
         const long long p = pk + w.col[r];
-        T dg;
-        const T ap = apply_col3<T, VAR>(L, c.i, c.j + r, k, p, centre[r], w.il ? pl[r] : T(0), w.ir ? pr[r] : T(0),
-                                        w.down(r, centre, hd), w.up(r, centre, hu), below[r], above[r], s, &dg);
+        fw.row(L, w, c.i, c.j, k, r);
+        const T ap = apply_col3(L, fw, r, centre[r], w.il ? pl[r] : T(0), w.ir ? pr[r] : T(0),
+                                           w.down(r, centre, hd), w.up(r, centre, hu), below[r], above[r], s);
         const T bn = bv[r] - a * ap;
         bout[off + p] = bn;
-        xout[off + p] = omega * bn / dg;
+        xout[off + p] = omega * bn / fw.diag(L, r, s);
         rr += (double)bn * (double)bn;
       }
 #pragma unroll
@@ -739,9 +817,10 @@ __global__ __launch_bounds__(256) void k_restrict3(LevelDev<T> Lf, LevelDev<T> L
                                                    const T* __restrict__ shift, const int* __restrict__ active,
                                                    unsigned long long* __restrict__ ctr, int planes) {
   constexpr int PER = (kRfn + 255) / 256;
+  constexpr bool EARLY = sizeof(T) == 4;   // the face weights with the plane's other loads (see ColFaces)
   __shared__ T rb[kRfn];
   __shared__ T xt[kRhn];
-  const Tile tl = block_tile();
+  const Tile tl = VAR && sizeof(T) == 4 ? block_tile_shared() : block_tile();
   const int sys = tl.z;
   if (!active[sys]) return;
   count_bytes_tile(tl, ctr, (unsigned long long)Lc.N * sizeof(T) * (2 * 8 + 1 + (VAR && sys == 0 ? 3 * 8 : 0)));
@@ -757,6 +836,7 @@ __global__ __launch_bounds__(256) void k_restrict3(LevelDev<T> Lf, LevelDev<T> L
   const long long nnf = (long long)nf * nf;
   int fk = 2 * K0;
   T xm[PER], xc0[PER];   // x at the fine plane below and at the current one, per owned fine point
+  T wf[PER];             // the weight of the face below the current plane
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
     const int q = tid + 256 * u;
@@ -764,8 +844,10 @@ __global__ __launch_bounds__(256) void k_restrict3(LevelDev<T> Lf, LevelDev<T> L
     const int fi = 2 * I0 + fx, fj = 2 * J0 + fy;
     xm[u] = T(0);
     xc0[u] = T(0);
+    wf[u] = T(0);
     if (q < kRfn && fi < nf && fj < nf) {
       const long long p = fk * nnf + (long long)fj * nf + fi;
+      if (VAR && EARLY) wf[u] = Lf.wf2[p];
       const T xb = xs[fk > 0 ? p - nnf : p];
       xm[u] = fk > 0 ? xb : T(0);
       xc0[u] = xs[p];
@@ -797,16 +879,35 @@ __global__ __launch_bounds__(256) void k_restrict3(LevelDev<T> Lf, LevelDev<T> L
   // weighted in-plane sum of it; advances fk and the registers
   auto rplane = [&]() -> T {
     // x of plane fk into the tile (0 off the grid), x above and b loaded
+    // (and the faces: see ColFaces)
     T xa[PER], bv[PER];
+    ColFaces<T, VAR, 1> fw[PER];
+    // faces of the point at offset o1 of the plane (o0: in a plane of wf0); the
+    // one below in z is the one above of the plane before (planes of wf0 and
+    // wf1 have as many faces)
+    auto load_faces = [&](ColFaces<T, VAR, 1>& w, unsigned o1, unsigned o0) {
+      const long long f0 = (long long)fk * nf * (nf + 1);
+      w.l[0] = plane_at(Lf.wf0 + f0, o0);
+      w.r[0] = plane_at(Lf.wf0 + f0, o0 + 1);
+      w.d[0] = plane_at(Lf.wf1 + f0, o1);
+      w.d[1] = plane_at(Lf.wf1 + f0, o1 + (unsigned)nf);
+      w.f[0] = plane_at(Lf.wf2 + (fk + 1) * nnf, o1);
+      if (!EARLY) w.b[0] = plane_at(Lf.wf2 + fk * nnf, o1);
+    };
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       const int q = tid + 256 * u;
       const int fy = q / kRfx, fx = q - fy * kRfx;
       const int fi = 2 * I0 + fx, fj = 2 * J0 + fy;
       const bool in = q < kRfn && fi < nf && fj < nf;
-      const long long p = fk * nnf + (in ? (long long)fj * nf + fi : 0LL);
-      xa[u] = xs[fk + 1 < nf ? p + nnf : p];
-      bv[u] = bs[p];
+      const unsigned o = in ? (unsigned)(fj * nf + fi) : 0u;
+      xa[u] = plane_at(xs + (fk + 1 < nf ? fk + 1 : fk) * nnf, o);
+      bv[u] = plane_at(bs + fk * nnf, o);
+      if (VAR && EARLY) {
+        load_faces(fw[u], o, in ? o + (unsigned)fj : 0u);
+        fw[u].b[0] = wf[u];
+        wf[u] = fw[u].f[0];
+      }
       if (q < kRfn) xt[(fy + 1) * kRhx + fx + 1] = xc0[u];
     }
     if (ring_h >= 0) xt[ring_h] = ring_off >= 0 ? xs[fk * nnf + ring_off] : T(0);
@@ -819,11 +920,11 @@ __global__ __launch_bounds__(256) void k_restrict3(LevelDev<T> Lf, LevelDev<T> L
       if (q < kRfn) {
         T r = T(0);
         if (fi < nf && fj < nf) {
-          const long long p = fk * nnf + (long long)fj * nf + fi;
           const int h = (fy + 1) * kRhx + fx + 1;
           const T above = fk + 1 < nf ? xa[u] : T(0);
-          r = bv[u] - apply_col3<T, VAR>(Lf, fi, fj, fk, p, xc0[u], xt[h - 1], xt[h + 1], xt[h - kRhx], xt[h + kRhx],
-                                         xm[u], above, s, nullptr);
+          if (VAR && !EARLY) load_faces(fw[u], (unsigned)(fj * nf + fi), (unsigned)(fj * (nf + 1) + fi));
+          r = bv[u] - apply_col3(Lf, fw[u], 0, xc0[u], xt[h - 1], xt[h + 1], xt[h - kRhx], xt[h + kRhx],
+                                            xm[u], above, s);
           xm[u] = xc0[u];
           xc0[u] = above;
         }
@@ -2718,7 +2819,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_p3(LevelDev<T> L, const T* __re
                                                     unsigned long long* __restrict__ ctr, Fin fin,
                                                     T* __restrict__ x, const double* __restrict__ alpha) {
   constexpr int R = kMarchRows;
-  const Tile tl = block_tile();
+  const Tile tl = VAR && sizeof(T) == 4 ? block_tile_shared() : block_tile();
   const int sys = tl.z;
   if (!active[sys]) return;
   const T bt = (T)beta[sys];
@@ -2746,6 +2847,8 @@ __global__ __launch_bounds__(kBlock) void k_spmv_p3(LevelDev<T> L, const T* __re
       centre[r] = zc + bt * ec;
       pold_c[r] = ec;
     }
+    ColFaces<T, VAR, R> fw;
+    fw.start(L, w, c.k0);
     for (int k = c.k0; k < c.k1; ++k) {
       const long long pk = k * nn;
       // every load of the plane first, then the arithmetic
@@ -2763,6 +2866,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_p3(LevelDev<T> L, const T* __re
         xv[r] = XUP ? x[off + p] : T(0);
       }
       const T zd = zs[pk + w.col_d], ed = pe[pk + w.col_d], zu = zs[pk + w.col_u], eu = pe[pk + w.col_u];
+      fw.load(L, w, c.i, c.j, k);
       const T hd = zd + bt * ed, hu = zu + bt * eu;
       T above[R];
 #pragma unroll
@@ -2772,8 +2876,9 @@ __global__ __launch_bounds__(kBlock) void k_spmv_p3(LevelDev<T> L, const T* __re
         if (!w.valid[r]) continue;
         const long long p = pk + w.col[r];
         const T lv = w.il ? zl[r] + bt * el[r] : T(0), rv = w.ir ? zr[r] + bt * er[r] : T(0);
-        const T qv = apply_col3<T, VAR>(L, c.i, c.j + r, k, p, centre[r], lv, rv, w.down(r, centre, hd),
-                                        w.up(r, centre, hu), below[r], above[r], s, nullptr);
+        fw.row(L, w, c.i, c.j, k, r);
+        const T qv = apply_col3(L, fw, r, centre[r], lv, rv, w.down(r, centre, hd), w.up(r, centre, hu),
+                                           below[r], above[r], s);
         pnew[off + p] = centre[r];
         if (WQ) q[off + p] = qv;
         if (XUP && ap != T(0)) x[off + p] = xv[r] + ap * pold_c[r];
@@ -3349,7 +3454,7 @@ __global__ __launch_bounds__(kBlock) void k_residual64_3(LevelDev<double> L, con
                                                          double* __restrict__ partial,
                                                          unsigned long long* __restrict__ ctr) {
   constexpr int R = kMarchRows;
-  const Tile tl = block_tile();
+  const Tile tl = VAR ? block_tile_shared() : block_tile();
   const int sys = tl.z;
   if (!active64[sys]) return;
   count_bytes_tile(tl, ctr, (unsigned long long)L.N * (8 + 8 + 4 + 4 + (VAR && sys == 0 ? 8 * 3 : 0)));
@@ -3370,6 +3475,8 @@ __global__ __launch_bounds__(kBlock) void k_residual64_3(LevelDev<double> L, con
       below[r] = c.k0 > 0 ? xb0 : 0.0;
       centre[r] = xs[p0];
     }
+    ColFaces<double, VAR, R, true> fw;
+    fw.start(L, w, c.k0);
     for (int k = c.k0; k < c.k1; ++k) {
       const long long pk = k * nn;
       double xa[R], xl[R], xr[R], fv[R];
@@ -3382,6 +3489,7 @@ __global__ __launch_bounds__(kBlock) void k_residual64_3(LevelDev<double> L, con
         fv[r] = fs[p];
       }
       const double hd = xs[pk + w.col_d], hu = xs[pk + w.col_u];
+      fw.load(L, w, c.i, c.j, k);
       double above[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) above[r] = k + 1 < n ? xa[r] : 0.0;
@@ -3389,9 +3497,8 @@ __global__ __launch_bounds__(kBlock) void k_residual64_3(LevelDev<double> L, con
       for (int r = 0; r < R; ++r) {
         if (!w.valid[r]) continue;
         const long long p = pk + w.col[r];
-        const double ax = apply_col3<double, VAR>(L, c.i, c.j + r, k, p, centre[r], w.il ? xl[r] : 0.0,
-                                                  w.ir ? xr[r] : 0.0, w.down(r, centre, hd), w.up(r, centre, hu),
-                                                  below[r], above[r], s, nullptr);
+        const double ax = apply_col3(L, fw, r, centre[r], w.il ? xl[r] : 0.0, w.ir ? xr[r] : 0.0,
+                                                     w.down(r, centre, hd), w.up(r, centre, hu), below[r], above[r], s);
         const double rv = fv[r] - ax;
         r32[off + p] = (RT)rv;
         if constexpr (sizeof(RT) == 4) e[off + p] = 0.0f;
