@@ -128,7 +128,9 @@ typedef struct {
                           (200 with a multigrid hierarchy, 40 n + 200 without)           */
   int max_outer;       /* MIXED: refinement-step cap                                     */
   int nrhs_max;        /* largest nrhs any solve on this plan will use (sizes buffers)   */
-  int check_every;     /* PCG iterations between host convergence checks (>= 1)          */
+  int check_every;     /* PCG iterations between host convergence checks (>= 1) of a
+                          static-workspace, profiled or BURA_VARIANT_FOLD_SCALARS solve;
+                          others are watched at every iteration                          */
   int nu_pre, nu_post; /* Jacobi sweeps before / after coarse-grid correction             */
   double omega;        /* Jacobi damping of every sweep; 0 = library default: 4/5 (2D)
                           or 6/7 (3D), and for the FP32 inner solves of BURA_MIXED
@@ -168,8 +170,9 @@ enum bura_variant {
   BURA_VARIANT_FOLD_SCALARS = 4, /* the per-system scalar updates by the last block of the
                                     producing kernel (device-scope fence) instead of a small
                                     kernel of their own                                      */
-  BURA_VARIANT_NO_GRAPH = 8      /* launch every PCG iteration eagerly instead of replaying a
-                                    captured graph per chunk of iterations                   */
+  BURA_VARIANT_NO_GRAPH = 8      /* launch every PCG iteration eagerly where a solve would
+                                    replay a captured graph per chunk of iterations
+                                    (profiled and BURA_VARIANT_FOLD_SCALARS solves)          */
 };
 
 /* Per-solve report (host struct filled by solve/poll). */
