@@ -415,7 +415,8 @@ __global__ __launch_bounds__(kBlock) void k_jacobi(LevelDev<T> L, const T* __res
 // k_jacobi in 3D, marching along z (one workgroup per `planes` planes,
 // kMarchRows rows per thread).
 template <typename T, bool VAR, bool ZERO, bool DOT>
-__global__ __launch_bounds__(kBlock) void k_jacobi3(LevelDev<T> L, const T* __restrict__ b,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && VAR && !DOT ? 4 : 1))) void
+k_jacobi3(LevelDev<T> L, const T* __restrict__ b,
                                                     const T* __restrict__ xin, T* __restrict__ xout,
                                                     const T* __restrict__ shift, const int* __restrict__ active,
                                                     T omega, double* __restrict__ partial,
