@@ -1817,9 +1817,13 @@ extern __shared__ double row_lds[];   // (NT + 2) records
 
 // LDS records of a row kernel with `words` values a thread and step
 constexpr int row_rec(int words) { return 2 * words + 1; }
-template <typename T>
-static inline size_t row_lds_bytes(int words, int threads) {
-  return (size_t)(threads + 2) * row_rec(words) * sizeof(T);
+// (more than 64 KiB, which FP64 with three sweeps takes at 1023 columns, has to be asked for)
+template <typename T, typename Kernel>
+static inline size_t row_lds_bytes(Kernel* kern, int words, int threads) {
+  const size_t bytes = (size_t)(threads + 2) * row_rec(words) * sizeof(T);
+  if (bytes > 64 * 1024)
+    (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  return bytes;
 }
 constexpr int down_words(int nu, bool rup) { return 2 * nu + 1 + (rup ? 2 : 0); }
 constexpr int up_words(int nu) { return 2 * (2 * nu - 1); }
@@ -4185,7 +4189,8 @@ void Launch<T>::spmv_p(int dim, bool var, const LevelDev<T>& L, const T* z, cons
     const int rows = rows_seg(tv);
     const dim3 g = rows_grid((L.n + rows - 1) / rows, nsys), blk(pair_threads(L.n));
 #define K_SR(V, X_, Q_) \
-  hipLaunchKernelGGL((k_spmv_r2<T, V, X_, Q_>), g, blk, row_lds_bytes<T>(spmv_words(), blk.x), st, L, z, pold, pnew, q, beta, shift, active, partial, \
+  hipLaunchKernelGGL((k_spmv_r2<T, V, X_, Q_>), g, blk, row_lds_bytes<T>(k_spmv_r2<T, V, X_, Q_>, spmv_words(), blk.x), \
+                     st, L, z, pold, pnew, q, beta, shift, active, partial, \
                      ctr, fin, x, alpha, rows)
     if (var) {
       if (!q) K_SR(true, true, false); else if (xup) K_SR(true, true, true); else K_SR(true, false, true);
@@ -4259,7 +4264,8 @@ bool Launch<T>::fused_down(int dim, bool var, int nu, const LevelDev<T>& Lf, con
     const int ky = rows_seg(tv) / 2;
     const dim3 g = rows_grid((Lc.n + ky - 1) / ky, nsys), blk(pair_threads(Lf.n));
 #define K_DR0(V, NU_, R_)                                                                                     \
-  hipLaunchKernelGGL((k_down2r<T, V, NU_, R_>), g, blk, row_lds_bytes<T>(down_words(NU_, R_), blk.x), st, Lf, Lc, b, xout, bc, shift, active, om, ctr, p, \
+  hipLaunchKernelGGL((k_down2r<T, V, NU_, R_>), g, blk,                                              \
+                     row_lds_bytes<T>(k_down2r<T, V, NU_, R_>, down_words(NU_, R_), blk.x), st, Lf, Lc, b, xout, bc, shift, active, om, ctr, p, \
                      alpha, bout, partial, fin, ky)
 #define K_DR(V, NU_) do { if (rup) K_DR0(V, NU_, true); else K_DR0(V, NU_, false); } while (0)
     if (var) {
@@ -4352,7 +4358,8 @@ bool Launch<T>::fused_up(int dim, bool var, int nu, const LevelDev<T>& Lc, const
     const int rows = rows_seg(tv);
     const dim3 g = rows_grid((Lf.n + rows - 1) / rows, nsys), blk(pair_threads(Lf.n));
 #define K_UR0(V, NU_, D_)                                                                                        \
-  hipLaunchKernelGGL((k_up2r<T, V, NU_, D_>), g, blk, row_lds_bytes<T>(up_words(NU_), blk.x), st, Lc, Lf, xc, xin, b, xout, shift, active, om, partial, \
+  hipLaunchKernelGGL((k_up2r<T, V, NU_, D_>), g, blk,                                                    \
+                     row_lds_bytes<T>(k_up2r<T, V, NU_, D_>, up_words(NU_), blk.x), st, Lc, Lf, xc, xin, b, xout, shift, active, om, partial, \
                      ctr, fin, rows)
 #define K_UR(V, NU_) do { if (dot) K_UR0(V, NU_, true); else K_UR0(V, NU_, false); } while (0)
     if (var) {

@@ -59,3 +59,28 @@ def test_first_coarse_level_sizes(dim, n, coeff, prec):
     assert max(its) <= 20 and its[0] >= 2
     assert err <= bound
     plan.close()
+
+
+@pytest.mark.parametrize("n,nu,prec", [(1023, 3, "FP64"), (1023, 2, "FP64"), (1023, 3, "MIXED"), (767, 3, "FP64"),
+                                       (511, 2, "MIXED")])
+def test_row_kernels_at_their_widest(n, nu, prec):
+    """The row-marching 2D kernels with as many columns as they take (three FP64
+    sweeps need more than 64 KiB of LDS there); the bound of the test above,
+    with constant coefficients: launch shapes that are set make a plan iterate."""
+    import paper_1612_04846_amd as B
+    from oracle import spectral
+    tol, w, s = 1e-11, [0.5, 0.5], [0.02, 1.5]
+    F = synth.normal_rhs(n, 2, nrhs=1, tag=980 + n)
+    ref = spectral.bura_spectral(F, 2, w, [-v for v in s])
+    bound = 1.1 * tol * sum(c / v for c, v in zip(w, s)) * np.linalg.norm(F)
+    plan = B.Plan(2, n, weights=w, shifts=s, precision=getattr(B, "BURA_" + prec), tol=tol, nu_pre=nu, nu_post=nu)
+    f = torch.from_numpy(np.ascontiguousarray(F)).cuda()
+    for v in (3, 4):
+        print(f"rows: n={n} nu={nu} {prec} variant {v}", flush=True)
+        plan.tiles = [v] * len(plan.tiles)
+        res = plan.solve(f)
+        torch.cuda.synchronize()
+        its = list(res.report.iters)[:2]
+        assert 1 <= max(its) <= 20
+        assert float(np.linalg.norm(res.u.cpu().numpy() - ref)) <= bound
+    plan.close()
