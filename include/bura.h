@@ -337,7 +337,10 @@ int bura_plan_outputs(bura_plan_t plan, int* nout, int* term_begin);
 
 /* u_dev[r] = sum_j c_j (A - d_j I)^{-1} f_dev[r], r < nrhs <= nrhs_max.
  * Synchronous: returns after the result is in u_dev.  rep may be NULL.
- * BURA_ENOCONV leaves the last iterate combined in u_dev. */
+ * BURA_ENOCONV leaves the last iterate combined in u_dev.  u_dev may share
+ * memory with f_dev (solved in place), in every kind of solve, unless
+ * opts.err_tol > 0, whose extra rounds read f_dev again behind the first
+ * result. */
 int bura_solve(bura_plan_t plan, const double* f_dev, double* u_dev, int nrhs, bura_report_t* rep);
 
 /* Asynchronous variant of bura_solve: queue the solve and return at once with

@@ -1376,6 +1376,11 @@ void combine_batch(bura_plan_t P, size_t sys0, int R, const Combine& c, bool sum
                  c.norms ? P->d_upart : nullptr, sum ? P->d_unorm : nullptr);
 }
 
+bool ranges_overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
+  return p < q + nb && q < p + na;
+}
+
 int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t* rep,
              const SlotTerms* slot = nullptr, double tol = 0.0) {
   const auto t0 = std::chrono::steady_clock::now();
@@ -1412,8 +1417,11 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
   // of a sequential form read earlier ones, so there the whole solve runs
   // again with a wait per stage: it is queued in one go only where the direct
   // solution is sure to pass, its residual being rounding, at most about
-  // 3e-16 / (lambda_min + s) of |f|.
-  bool spec = starts_direct(P);   // (the solve is queued to its end)
+  // 3e-16 / (lambda_min + s) of |f|.  Not where u shares memory with f: the
+  // systems that iterate on read f again, so u is written behind the test.
+  const size_t rhs_bytes = (size_t)nrhs * P->N * sizeof(double);
+  const bool overlap = ranges_overlap(f, rhs_bytes, u, rhs_bytes * P->nout);
+  bool spec = starts_direct(P) && !overlap;   // (the solve is queued to its end)
   if (spec && !P->stages.empty()) {
     double smin = HUGE_VAL;
     for (double v : P->s) smin = std::min(smin, v);

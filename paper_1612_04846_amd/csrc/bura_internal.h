@@ -231,7 +231,8 @@ void launch_report_flags(const int* flags, int n, int* host, unsigned* host_seq,
 // s (check_blocks per system), and with u != nullptr the outputs and their norm
 // partials (upartial, check_blocks per output row), as launch_combine forms
 // them.  u == nullptr: the residuals of the systems [0, nsys) only.  f may be
-// the buffer u.
+// the buffer u where there is one output (a point of f is used by the thread
+// that writes the same point of u) and no continuation reads f afterwards.
 struct CheckArgs {
   int n;
   long long N;
