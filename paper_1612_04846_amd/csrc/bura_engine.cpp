@@ -998,7 +998,7 @@ int run_pcg(bura_plan_t P, Work<T>& W, size_t sys0, int nsys, double tol, int ma
   // at a time (2 - 3 us each on the host, 4 us and more on the device: between
   // graph launches the device stood idle for 8 us)
   const int chunk = watch ? 1 : std::max(2, check + (check & 1));
-  const int nchunks = watch ? max_iter + 2 : max_iter / chunk + 1;
+  const long long nchunks = watch ? max_iter + 2LL : max_iter / chunk + 1;   // (max_iter: up to INT_MAX)
   auto run_chunk = [&](int odd) {
     T* a = odd ? pnew : pold;
     T* b = odd ? pold : pnew;
@@ -1048,11 +1048,11 @@ int run_pcg(bura_plan_t P, Work<T>& W, size_t sys0, int nsys, double tol, int ma
   }
   const volatile unsigned long long* prog = P->prog.host;
   unsigned want = watch ? (unsigned)(*prog >> 32) : 0;
-  for (int ch = 0; ch < nchunks; ++ch) {
+  for (long long ch = 0; ch < nchunks; ++ch) {
     if (g)
       HIPCHK(hipGraphLaunch(g->exec, st));
     else
-      run_chunk(watch ? ch & 1 : 0);
+      run_chunk(watch ? (int)(ch & 1) : 0);
     if (watch) {
       ++want;
       HIPCHK(hipGetLastError());
