@@ -139,7 +139,9 @@ typedef struct {
                           constant-coefficient plan to the multigrid iteration         */
   void* stream;        /* hipStream_t used for every launch and copy; NULL = null stream */
   size_t hbm_budget;   /* 0 = unlimited; else plan creation fails with BURA_ENOMEM if its
-                          device footprint would exceed this many bytes                 */
+                          device footprint would exceed this many bytes.  A grid whose
+                          coarsest level is too large for 64 KiB of LDS (three vectors)
+                          then runs without a hierarchy where that fits                 */
   int autotune;        /* 2D multigrid plans: 0 = default tile shapes; 1 = plan creation
                           times every tile-shape variant of the stencil product and of
                           each level's fused kernels on the plan's buffers (whole solves

@@ -190,12 +190,15 @@ struct bura_plan_s {
   double* d_unorm = nullptr;   // rows = nout x nrhs_max
   double* d_tol_err = nullptr; // MIXED: per-system refinement tolerances set by opts.err_tol
   // direct solution in the sine basis (constant coefficients, bura_direct.hip):
-  // its tables, the partials of |f|^2 and the systems' gates; off for a plan
+  // its tables, the partials of |f|^2, the systems' gates and the partials of
+  // its test; off for a plan
   // whose launch shapes or damping the caller has chosen (direct_allowed)
   bool direct = false;
   double* d_sine = nullptr;
   double* d_fpart = nullptr;
   int* d_gate = nullptr;
+  double* d_cpart = nullptr;   // launch_check's partials: partial and d_upart where those hold them (see check_extra)
+  double* d_cupart = nullptr;
   int run_nrhs = 0;            // right-hand sides of the solve in progress
   // continuous batching (bura::serve_*): the slots' right-hand sides, the
   // systems being initialised, and the host copy of each slot's terms
@@ -613,9 +616,22 @@ bool direct_allowed(const bura_plan_t P) {
   return !P->var && !(P->opts.omega > 0.0) && P->n <= (P->dim == 2 ? kDirectMaxN2 : kDirectMaxN3);
 }
 
+// The partials of launch_check, in doubles, where they outnumber those of the
+// other kernels (small 3D grids, one plane per workgroup there), else 0: sums
+// over the systems, and over the output rows.  Memory of the direct solution's
+// own, so that a plan without it takes no more than the iteration needs.
+size_t check_extra_systems(const bura_plan_t P) {
+  const int nb = check_blocks(P->dim, P->n);
+  return nb > max_partial_blocks(P->dim, P->n, P->N) ? (size_t)P->S * nb : 0;
+}
+size_t check_extra_rows(const bura_plan_t P) {
+  const int nb = check_blocks(P->dim, P->n);
+  return nb > combine_blocks(P->N) ? (size_t)P->nout * P->opts.nrhs_max * nb : 0;
+}
+
 size_t direct_bytes(const bura_plan_t P) {
   return sine_table_doubles(P->n) * 8 + (size_t)P->opts.nrhs_max * sine_norm_max_blocks(P->dim, P->n) * 8 +
-         (size_t)P->S * 4;
+         (size_t)P->S * 4 + (check_extra_systems(P) + check_extra_rows(P)) * 8;
 }
 
 // q = (A + s) p needs a buffer unless the kernel that takes the PCG residual
@@ -1175,7 +1191,7 @@ void direct_batch(bura_plan_t P, const double* f, int R, size_t sys0, int nsys, 
     c.shift = s.shift;
     c.active = mixed ? S.active64 : S.active;
     c.stride = R;
-    c.partial = P->partial;
+    c.partial = P->d_cpart;
     c.ctr = ps.ctr;
     if (comb) {
       c.w = comb->w;
@@ -1183,7 +1199,7 @@ void direct_batch(bura_plan_t P, const double* f, int R, size_t sys0, int nsys, 
       c.u = comb->u;
       c.base = comb->base;
       c.base_w = comb->base_w;
-      c.upartial = comb->norms ? P->d_upart : nullptr;
+      c.upartial = comb->norms ? P->d_cupart : nullptr;
       c.nrhs = comb->nrhs;
     }
     launch_check(P->dim, c, comb ? comb->t : CombineTerms{}, comb ? comb->nout : 1, nsys, st);
@@ -1192,9 +1208,9 @@ void direct_batch(bura_plan_t P, const double* f, int R, size_t sys0, int nsys, 
   ProfScope ps(P, BURA_K_OTHER);
   const int nb = check_blocks(P->dim, P->n);
   S.started = 1;
-  launch_scalars(mixed ? OP_OUTER : OP_RESTART, P->partial, nb, nsys, S, P->run_tol,
+  launch_scalars(mixed ? OP_OUTER : OP_RESTART, P->d_cpart, nb, nsys, S, P->run_tol,
                  mixed ? P->opts.max_outer : P->opts.max_iter, st);
-  if (comb && comb->norms) launch_row_sum(P->d_upart, nb, comb->nout * comb->nrhs, P->d_unorm, st);
+  if (comb && comb->norms) launch_row_sum(P->d_cupart, nb, comb->nout * comb->nrhs, P->d_unorm, st);
 }
 
 // Both batch solvers find the state as launch_begin leaves it: the used
@@ -1438,7 +1454,8 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
   const bool whole = direct && P->stages.empty() && P->opts.schedule != BURA_PER_POLE;
   const bool conclude = whole && spec && reports(P) && (long long)S_used * check_blocks(P->dim, P->n) <= 32768 &&
                         S_used <= kReportBytes / 128;
-  int unblk = 0;   // conclude: partials per output row
+  int unblk = 0;   // conclude: partials per output row, and where they are
+  const double* upart = nullptr;
   if (!whole) begin();
   // a batch that starts from the direct solution: with its combine in the pass
   // of the residual test where nothing waits for that test
@@ -1451,6 +1468,7 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
     }
     if (c && !fuse) combine_batch(P, sys0, R, *c, !conclude);
     unblk = fuse ? check_blocks(P->dim, P->n) : combine_blocks(P->N);
+    upart = fuse ? P->d_cupart : P->d_upart;
     return BURA_OK;
   };
   const double* xsol = mixed ? P->x64 : P->w64.x;
@@ -1525,8 +1543,8 @@ int do_solve(bura_plan_t P, const double* f, double* u, int nrhs, bura_report_t*
       Ss.started = 1;
       const bool sums = conclude && !fetched;
       fetched = true;
-      launch_conclude(!sums ? -1 : mixed ? OP_OUTER : OP_RESTART, P->partial, check_blocks(P->dim, P->n), (int)S_used,
-                      Ss, P->run_tol, mixed ? P->opts.max_outer : P->opts.max_iter, P->d_upart, unblk, sums ? rows : 0,
+      launch_conclude(!sums ? -1 : mixed ? OP_OUTER : OP_RESTART, P->d_cpart, check_blocks(P->dim, P->n), (int)S_used,
+                      Ss, P->run_tol, mixed ? P->opts.max_outer : P->opts.max_iter, upart, unblk, sums ? rows : 0,
                       P->d_unorm, P->state_block, bytes, P->h_state, P->h_seq, ++P->seq, P->stream);
       HIPCHK(hipGetLastError());
       return wait_report(P);
@@ -1959,8 +1977,11 @@ int tune_tiles(bura_plan_t P) {
   return BURA_OK;
 }
 
-int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_plan_t* out,
-           const LateTerms& late = LateTerms(), void* ws = nullptr, size_t ws_cap = 0) {
+// wide_coarse false: a plan whose coarse solve needs more than 64 KiB of LDS
+// runs without a hierarchy.  *wide tells whether this is such a plan.
+int create_plan(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_plan_t* out, const LateTerms& late,
+                void* ws, size_t ws_cap, bool wide_coarse, bool* wide) {
+  *wide = false;
   if (out) *out = nullptr;
   if (!g || !out) return BURA_EINVAL;
   if (!late && check_terms(terms)) return BURA_EINVAL;
@@ -2042,6 +2063,11 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
   set_default_tiles(P);
   const bool mixed = o.precision == BURA_MIXED;
   choose_lds(P, mixed ? 4 : 8);
+  *wide = P->lc > 0 && 3 * (size_t)P->lev.back().N * (mixed ? 4 : 8) > 64 * 1024;
+  if (*wide && !wide_coarse) {
+    P->lc = -1;
+    P->lds_bytes = 0;
+  }
   // the folded vector updates need a multigrid level with a pre-smoothing
   // sweep (the fused down kernel in 2D, the first Jacobi sweep otherwise)
   P->foldxr = P->lc > 0 && !(o.variant & BURA_VARIANT_NO_FOLDXR);
@@ -2082,8 +2108,6 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
       return fail(BURA_EDEVICE);
   }
   P->partial_len = (size_t)P->S * (size_t)max_partial_blocks(P->dim, P->n, P->N);
-  if (direct_allowed(P))
-    P->partial_len = std::max(P->partial_len, (size_t)P->S * (size_t)check_blocks(P->dim, P->n));
   if ((rc = dev_alloc(P, (void**)&P->partial, P->partial_len * 8))) return fail(rc);
   if ((rc = dev_alloc(P, (void**)&P->d_w, nterms * 8))) return fail(rc);
   if (!P->stages.empty() && (rc = dev_alloc(P, (void**)&P->d_buf, (size_t)o.nrhs_max * P->N * 8))) return fail(rc);
@@ -2111,8 +2135,7 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
   if ((rc = dev_alloc(P, (void**)&P->prof.d_ctr, BURA_K_COUNT * sizeof(unsigned long long)))) return fail(rc);
   if ((rc = dev_zero(P, P->prof.d_ctr, BURA_K_COUNT * sizeof(unsigned long long)))) return fail(rc);
   {
-    size_t nb = (size_t)combine_blocks(P->N);
-    if (direct_allowed(P)) nb = std::max(nb, (size_t)check_blocks(P->dim, P->n));
+    const size_t nb = (size_t)combine_blocks(P->N);
     if ((rc = dev_alloc(P, (void**)&P->d_upart, unorm_rows * nb * 8))) return fail(rc);
     if (mixed && (rc = dev_alloc(P, (void**)&P->d_tol_err, S * 8))) return fail(rc);
   }
@@ -2125,13 +2148,18 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
   if (direct_allowed(P)) {
     // the direct solution's tables; a plan that they would take over its
     // budget or its static workspace runs without them
-    const bool fits = ws ? P->ws_used + direct_bytes(P) + 1024 <= ws_cap
+    const bool fits = ws ? P->ws_used + direct_bytes(P) + 6 * 256 <= ws_cap
                          : o.hbm_budget == 0 || footprint(P, mixed ? 4 : 8, mixed) + direct_bytes(P) <= o.hbm_budget;
     if (fits) {
       const size_t fpart = (size_t)o.nrhs_max * sine_norm_max_blocks(P->dim, P->n) * 8;
       P->direct = !dev_alloc(P, (void**)&P->d_sine, sine_table_doubles(P->n) * 8) &&
                   !dev_alloc(P, (void**)&P->d_fpart, fpart) &&
                   !dev_alloc(P, (void**)&P->d_gate, S * sizeof(int));
+      P->d_cpart = P->partial;
+      P->d_cupart = P->d_upart;
+      if (P->direct && check_extra_systems(P))
+        P->direct = !dev_alloc(P, (void**)&P->d_cpart, check_extra_systems(P) * 8);
+      if (P->direct && check_extra_rows(P)) P->direct = !dev_alloc(P, (void**)&P->d_cupart, check_extra_rows(P) * 8);
       if (P->direct) launch_sine_tables(P->n, P->d_sine, P->stream);
       (void)hipGetLastError();   // no memory for them: the plan iterates from zero
     }
@@ -2162,6 +2190,20 @@ int create(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, bura_p
   if (hipStreamSynchronize(P->stream) != hipSuccess) return fail(BURA_EDEVICE);
   *out = P;
   return BURA_OK;
+}
+
+// A hierarchy takes one vector per system and the coarse levels' more than the
+// Jacobi-preconditioned iteration.  Grids whose coarsest level has an exact
+// solve only with more than 64 KiB of LDS give it up where that is what does
+// not fit the memory (budget, static workspace, device): the solve is then as
+// long as on an even grid, and not refused.
+int create(const bura_grid_t* g, const Terms& terms, const bura_opts_t* opts, bura_plan_t* out,
+           const LateTerms& late = LateTerms(), void* ws = nullptr, size_t ws_cap = 0) {
+  bool wide = false;
+  const int rc = create_plan(g, terms, opts, out, late, ws, ws_cap, true, &wide);
+  if (!wide || (rc != BURA_ENOMEM && rc != BURA_ETOOBIG)) return rc;
+  (void)hipGetLastError();
+  return create_plan(g, terms, opts, out, late, ws, ws_cap, false, &wide);
 }
 
 }  // namespace

@@ -37,3 +37,74 @@ def test_largest_iteration_cap(cap, prec):
         assert got.report.iters[0] == want.report.iters[0]
         assert torch.equal(got.u, want.u)
     plan.close()
+
+
+# The systems of one grid that the 64 MiB workspace has always taken: grids
+# whose coarsest level had no exact solve before the coarse solve took more
+# LDS (121^2, 145^2, 149^2; 29^3, 37^3: with the hierarchy they would need one
+# vector a system more) and small 3D grids (where the direct solution's partial
+# sums outnumber the other kernels').
+STATIC = [(2, 121, "FP64", 81), (2, 145, "FP64", 56), (2, 149, "MIXED", 83), (3, 7, "FP64", 3392),
+          (3, 7, "MIXED", 5277), (3, 13, "MIXED", 828), (3, 19, "MIXED", 265), (3, 29, "FP64", 49),
+          (3, 37, "FP64", 23), (3, 37, "MIXED", 36)]
+
+
+@pytest.mark.parametrize("dim,n,prec,nsys", STATIC)
+def test_static_workspace_takes_as_many_systems(dim, n, prec, nsys):
+    from oracle import spectral
+    B = _B()
+    tol, shift = 1e-8, 0.5
+    F = synth.normal_rhs(n, dim, nrhs=nsys, tag=1012)
+    f = torch.from_numpy(F.reshape(nsys, -1)).cuda()
+    u = torch.empty_like(f)
+    print(f"static: {dim}D {n} {prec} {nsys} systems", flush=True)
+    o = B.bura_opts_default(precision=getattr(B, "BURA_" + prec), nrhs_max=nsys, tol=tol)
+    B.bura_solve_static(dim, n, [1.0], [shift], f, u, o)
+    ref = spectral.bura_spectral(F[-2:], dim, [1.0], [-shift]).reshape(2, -1)
+    # |(A + s)^-1 r| <= tol |f| / s
+    d = np.linalg.norm(u[-2:].cpu().numpy() - ref, axis=1)
+    assert np.all(d <= 1.1 * tol / shift * np.linalg.norm(F[-2:].reshape(2, -1), axis=1))
+    over = B.bura_opts_default(nrhs_max=2 * nsys, tol=tol)
+    f2 = torch.zeros((2 * nsys, n ** dim), dtype=torch.float64, device="cuda")
+    rep = B.bura_solve_static(dim, n, [1.0], [shift], f2, torch.empty_like(f2), over, ok=(B.BURA_ETOOBIG,))
+    assert rep.status == B.BURA_ETOOBIG
+
+
+def _smallest_budget(B, dim, n, var, prec):
+    lo, hi = 0, 1 << 30
+    while hi - lo > 4096:
+        m = (lo + hi) // 2
+        try:
+            B.Plan(dim, n, weights=[1.0] * 2, shifts=[0.1, 0.5], coeff=_coeff(n, dim) if var else None,
+                   precision=getattr(B, "BURA_" + prec), hbm_budget=m).close()
+            hi = m
+        except B.BuraError as e:
+            assert e.code == B.BURA_ENOMEM
+            lo = m
+    return hi
+
+
+@pytest.mark.parametrize("dim,n,prec", [(2, 121, "FP64"), (2, 149, "MIXED"), (3, 29, "FP64"), (3, 37, "MIXED")])
+@pytest.mark.parametrize("var", [False, True])
+def test_budget_that_was_enough_without_a_hierarchy(dim, n, prec, var):
+    """The hierarchy of a grid whose coarse solve needs the larger LDS is given
+    up where it does not fit the budget: such a grid asks for no more than the
+    next one, which is even and has none, and the same vectors per point.  (The
+    coarser levels' face weights are counted all the same: 1/3 of the finest
+    level's in 2D, 1/7 in 3D; 64 KiB for partial sums, which go by blocks.)"""
+    B = _B()
+    print(f"budget: {dim}D {n} {prec} var={var}", flush=True)
+    a, b = (_smallest_budget(B, dim, m, var, prec) for m in (n, n + 1))
+    faces = dim * (n + 2) ** dim * 12 / (2 ** dim - 1) if var else 0
+    assert a <= b * (n / (n + 1)) ** dim + faces + 65536
+    # and such a plan solves
+    kw = dict(weights=[1.0] * 2, shifts=[0.1, 0.5], coeff=_coeff(n, dim) if var else None,
+              precision=getattr(B, "BURA_" + prec), tol=1e-9, omega=0.8)
+    f = torch.from_numpy(synth.normal_rhs(n, dim, nrhs=1, tag=1013)).cuda()
+    small, full = B.Plan(dim, n, hbm_budget=a, **kw), B.Plan(dim, n, **kw)
+    us, uf = small.solve(f), full.solve(f)
+    assert max(us.report.iters) > 2 * max(uf.report.iters)
+    d = float((us.u - uf.u).norm())
+    assert d <= 2.2e-9 * (1 / 0.1 + 1 / 0.5) * float(f.norm())
+    small.close()
+    full.close()
