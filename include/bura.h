@@ -146,8 +146,9 @@ typedef struct {
                           times every tile-shape variant of the stencil product and of
                           each level's fused kernels on the plan's buffers (whole solves
                           in the plan's schedule) and keeps the fastest (cached per shape
-                          in the process; see bura_plan_tiles).  Plans whose solves the
-                          direct solution starts (tol <= 1e-6) have nothing to time      */
+                          in the process; see bura_plan_tiles).  With constant coefficients
+                          too: solves at a loose tolerance, and systems that the direct
+                          solution leaves over theirs, run these kernels               */
   double err_tol;      /* 0: stop on the residual test (tol) alone.  > 0 (BURA_MIXED, plans
                           without stages; else BURA_EUNSUPPORTED): also require the certified
                           bound of the report (err_bound) to be <= err_tol; the refinement

@@ -2181,7 +2181,9 @@ int create_plan(const bura_grid_t* g, Terms terms, const bura_opts_t* opts_in, b
     if ((rc = dev_alloc(P, (void**)&P->prog.count, 16))) return fail(rc);
     if ((rc = dev_zero(P, P->prog.count, 16))) return fail(rc);
   }
-  if (o.autotune && !(P->direct && o.tol <= kDirectTol)) {
+  // (also where the direct solution starts the plan's solves: those that are
+  // asked for a loose tolerance iterate from zero, others may go on from there)
+  if (o.autotune) {
     if (hipStreamSynchronize(P->stream) != hipSuccess) return fail(BURA_EDEVICE);
     if ((rc = tune_tiles(P))) return fail(rc);
   }

@@ -1,4 +1,6 @@
-"""Calls at the limits of their options: iteration caps, the static workspace, the memory budget."""
+"""Calls at the limits of their options: iteration caps, the static workspace, the memory budget, tuning."""
+
+import time
 
 import numpy as np
 import pytest
@@ -108,3 +110,32 @@ def test_budget_that_was_enough_without_a_hierarchy(dim, n, prec, var):
     assert d <= 2.2e-9 * (1 / 0.1 + 1 / 0.5) * float(f.norm())
     small.close()
     full.close()
+
+
+def test_autotune_times_constant_coefficient_plans():
+    """A plan that the direct solution starts iterates all the same where a
+    tolerance is loose, or a residual over it: autotune = 1 times its kernels.
+    Creation then holds a warm-up and three timings of at least four variants
+    of three kernels, more than 30 solves by iteration; counted as ten."""
+    B = _B()
+    n = 223
+    f = torch.from_numpy(synth.normal_rhs(n, 2, nrhs=3, tag=1014)).cuda()
+    kw = dict(alpha=0.5, k=7, nrhs_max=3, tol=1e-10)
+    it = B.Plan(2, n, omega=0.8, **kw)
+    solve = []
+    for _ in range(5):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        it.solve(f)
+        solve.append(time.perf_counter() - t)
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    tuned = B.Plan(2, n, autotune=1, **kw)
+    t = time.perf_counter() - t
+    print(f"iterated solve {min(solve) * 1e3:.2f} ms, creation {t * 1e3:.1f} ms, tiles {tuned.tiles}")
+    assert t >= 10 * min(solve)
+    assert all(0 <= v < B.BURA_TILE_VARIANTS for v in tuned.tiles)
+    res = tuned.solve(f)
+    assert max(res.report.iters) == 0   # and its own solves still start from the direct solution
+    for p in (it, tuned):
+        p.close()
