@@ -128,7 +128,8 @@ typedef struct {
                           (200 with a multigrid hierarchy, 40 n + 200 without)           */
   int max_outer;       /* MIXED: refinement-step cap                                     */
   int nrhs_max;        /* largest nrhs any solve on this plan will use (sizes buffers)   */
-  int check_every;     /* PCG iterations between host convergence checks (>= 1) of a
+  int check_every;     /* PCG iterations between host convergence checks (>= 1) of a solve
+                          without a multigrid hierarchy on fewer than 2^21 points, and of a
                           static-workspace, profiled or BURA_VARIANT_FOLD_SCALARS solve;
                           others are watched at every iteration                          */
   int nu_pre, nu_post; /* Jacobi sweeps before / after coarse-grid correction             */
@@ -174,8 +175,8 @@ enum bura_variant {
                                     producing kernel (device-scope fence) instead of a small
                                     kernel of their own                                      */
   BURA_VARIANT_NO_GRAPH = 8      /* launch every PCG iteration eagerly where a solve would
-                                    replay a captured graph per chunk of iterations
-                                    (profiled and BURA_VARIANT_FOLD_SCALARS solves)          */
+                                    replay a captured graph per chunk of iterations (those that
+                                    check_every applies to, but for the static workspace)    */
 };
 
 /* Per-solve report (host struct filled by solve/poll). */

@@ -957,8 +957,12 @@ int run_pcg(bura_plan_t P, Work<T>& W, size_t sys0, int nsys, double tol, int ma
   // The host watches every iteration's residual test and queues the next one
   // while the rest of the V-cycle runs: no gap between iterations, and after
   // the last one only that rest runs empty.  Without reports it looks once a
-  // chunk of iterations.
-  const bool watch = reports(P) && !P->fold;
+  // chunk of iterations.  So it does without a hierarchy, where the rest is one
+  // launch that is too short to hide the host's unless the batch is large, and
+  // a solve has hundreds of iterations (8 systems with variable coefficients,
+  // in captured chunks of 4 and watched: 64^2 FP64 5.6 and 6.4 ms, 300^2 mixed
+  // 34.7 and 39.1 ms; 102^3, 8.5e6 points, 40.5 and 39.3 ms).
+  const bool watch = reports(P) && !P->fold && (P->lc >= 0 || nsys * P->N >= (2LL << 20));
   auto scal = [&](int op, int nblk) {
     ProfScope ps(P, BURA_K_OTHER);
     launch_scalars(op, part, nblk, nsys, S, tol, max_iter, st, watch && op == OP_RESID ? P->prog : Progress());
