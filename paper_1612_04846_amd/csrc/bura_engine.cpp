@@ -931,7 +931,10 @@ int count_active(bura_plan_t P, const int* dev_flags, size_t sys0, int nsys) {
 }
 
 // Order the plan's stream after the caller's pending work; nothing to do where
-// there is none (the event and the wait for it are 12 - 20 us of a solve).
+// there is none (the event and the wait for it are 12 - 20 us of a solve).  The
+// null stream's query, like an event on it, counts work on every blocking
+// stream: it returns hipErrorNotReady while one of them is busy, which
+// test_solve_waits_for_pending_work holds it to.
 int join_caller(bura_plan_t P) {
   if (!P->join_ev) return BURA_OK;
   if (hipStreamQuery(P->user_stream) == hipSuccess) return BURA_OK;
