@@ -998,28 +998,39 @@ __device__ __forceinline__ void ijk_of(int p, int n, float rn, int& i, int& j, i
   }
 }
 
-__device__ __forceinline__ float coarse_recip(float d) { return __builtin_amdgcn_rcpf(d); }
-__device__ __forceinline__ double coarse_recip(double d) { return 1.0 / d; }
+// x + r d, the product rounded first: fused, the error of a rounded damping or
+// diagonal goes into every sweep in the same direction, where x + r d is a tie
+// of the rounding (the FP32 preconditioner of 155^2 with constant coefficients,
+// whose bottom level takes 312 sweeps, was off by 1.7e-7; so it is by 7.6e-8)
+template <typename T>
+__device__ __forceinline__ T add_step(T x, T r, T d) {
+#pragma clang fp contract(off)
+  const T t = r * d;
+  return x + t;
+}
 
 // The P points of this thread on one LDS level: padded position (a position
 // inside the grid for a lane without a point, which computes but does not
-// write), face weights and inverse diagonal.
+// write), face weights and inverse diagonal (an IEEE division, once a level).
+// The operator is in its difference form: its rounding goes with the
+// differences of neighbours, where (weights x neighbours) - diagonal x rounds
+// with x.  Gathered, with the hardware reciprocal, the FP32 preconditioner of
+// 155^2 with variable coefficients was off by 5.7e-7; in this form, and with
+// the division rounded as IEEE does, by 7.5e-8 (2^-24 is 6.0e-8).
 template <typename T, int DIM, bool VAR, int P>
 struct LdsPoints {
   int S1, S2;
   int q[P];
   bool on[P];
-  T wc, w[VAR ? 2 * DIM : 1][P], dg[VAR ? P : 1], di[VAR ? P : 1];
-  __device__ __forceinline__ LdsPoints(const LevelDev<T>& L, T s) {
+  T wc, s, w[VAR ? 2 * DIM : 1][P], di[VAR ? P : 1];
+  __device__ __forceinline__ LdsPoints(const LevelDev<T>& L, T shift) {
     const int n = L.n, N = (int)L.N;
     const float rn = 1.0f / (float)n;
     S1 = n + 2;
     S2 = S1 * S1;
     wc = L.wc;
-    if (!VAR) {
-      dg[0] = wc * T(2 * DIM) + s;
-      di[0] = coarse_recip(dg[0]);
-    }
+    s = shift;
+    if (!VAR) di[0] = T(1) / (wc * T(2 * DIM) + s);
 #pragma unroll
     for (int u = 0; u < P; ++u) {
       const int p = threadIdx.x + kCoarseThreads * u;
@@ -1041,31 +1052,31 @@ struct LdsPoints {
         T d = w[0][u];
 #pragma unroll
         for (int f = 1; f < 2 * DIM; ++f) d += w[VAR ? f : 0][u];
-        dg[VAR ? u : 0] = d + s;
-        di[VAR ? u : 0] = coarse_recip(d + s);
+        di[VAR ? u : 0] = T(1) / (d + s);
       }
     }
   }
-  __device__ __forceinline__ T diag(int u) const { return dg[VAR ? u : 0]; }
   __device__ __forceinline__ T inv(int u) const { return di[VAR ? u : 0]; }
-  // face weights times the neighbours
-  __device__ __forceinline__ T around(const T* A, int u) const {
+  // (A + s) at the point, the arithmetic of apply_pt
+  __device__ __forceinline__ T apply(const T* A, int u) const {
     const T* c = A + q[u];
+    const T x = c[0];
     if (!VAR) {
-      T sum = (c[-1] + c[1]) + (c[-S1] + c[S1]);
-      if (DIM == 3) sum += c[-S2] + c[S2];
-      return wc * sum;
+      T sum = (x - c[-1]) + (x - c[1]) + (x - c[-S1]) + (x - c[S1]);
+      if (DIM == 3) sum += (x - c[-S2]) + (x - c[S2]);
+      return wc * sum + s * x;
     }
-    T sum = w[0][u] * c[-1] + w[VAR ? 1 : 0][u] * c[1] + w[VAR ? 2 : 0][u] * c[-S1] + w[VAR ? 3 : 0][u] * c[S1];
-    if (DIM == 3) sum += w[VAR && DIM == 3 ? 4 : 0][u] * c[-S2] + w[VAR && DIM == 3 ? 5 : 0][u] * c[S2];
-    return sum;
+    T sum = w[0][u] * (x - c[-1]) + w[VAR ? 1 : 0][u] * (x - c[1]) + w[VAR ? 2 : 0][u] * (x - c[-S1]) +
+            w[VAR ? 3 : 0][u] * (x - c[S1]);
+    if (DIM == 3)
+      sum += w[VAR && DIM == 3 ? 4 : 0][u] * (x - c[-S2]) + w[VAR && DIM == 3 ? 5 : 0][u] * (x - c[S2]);
+    return sum + s * x;
   }
   // one sweep X -> Y, then they change places
   __device__ __forceinline__ void sweep(T*& X, T*& Y, const T* b, T om) const {
 #pragma unroll
     for (int u = 0; u < P; ++u) {
-      const T xc = X[q[u]];
-      const T xn = xc + om * ((b[u] + around(X, u)) * inv(u) - xc);
+      const T xn = add_step(X[q[u]], om * (b[u] - apply(X, u)), inv(u));
       if (on[u]) Y[q[u]] = xn;
     }
     __syncthreads();
@@ -1103,7 +1114,7 @@ __device__ __forceinline__ T* lds_cycle(const LdsHierarchy<T>& H, T* sm, T s, co
     // the residual into Y
 #pragma unroll
     for (int u = 0; u < P; ++u)
-      if (pt.on[u]) Y[pt.q[u]] = b[u] - (pt.diag(u) * X[pt.q[u]] - pt.around(X, u));
+      if (pt.on[u]) Y[pt.q[u]] = b[u] - pt.apply(X, u);
     __syncthreads();
   }
   if constexpr (LV + 1 < kMaxLdsLevels) {
