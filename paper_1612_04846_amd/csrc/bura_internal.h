@@ -194,18 +194,9 @@ void launch_sine_back(const SineSolve& s, hipStream_t st, unsigned long long* ct
 // MIXED solve leave the error its caller asked for, not more work.
 constexpr double kDirectTol = 1e-6;
 
-// Start the systems of [0, nsys) (arrays indexed from the same first system):
-// sum the partials of |f|^2 of each system's right-hand side s % R, apply op
-// (OP_INIT or OP_START) and set its gate (see SineSolve): 1 where the direct
-// solution is wanted, 2 where x = 0 is (a zero or non-finite right-hand side,
-// or a tolerance over kDirectTol), 0 for a system that is not active.  With
-// begin != nullptr this is also the solve's launch_begin (of nrhs right-hand
-// sides; all its systems in one batch).
-// The state at the start of a solve: flags and counters 0, no deferred update
-// pending, the used systems active (system j R + r for r < nrhs).  A slot
-// solve's terms come in one upload, staged = [S] weights, shifts, tolerances
-// (double), shifts (float), used flags (int), and go to
-// their arrays here.
+// A slot solve's terms in one upload, staged = [S] weights, shifts, tolerances
+// (double), shifts (float), used flags (int), which the solve's first launch
+// takes to their arrays.  staged == nullptr: none.
 struct SlotUpload {
   const double* staged = nullptr;
   double* w = nullptr;
@@ -214,6 +205,13 @@ struct SlotUpload {
   float* s32 = nullptr;     // MIXED
   double* tol = nullptr;
 };
+// Start the systems of [0, nsys) (arrays indexed from the same first system):
+// sum the partials of |f|^2 of each system's right-hand side s % R, apply op
+// (OP_INIT or OP_START) and set its gate (see SineSolve): 1 where the direct
+// solution is wanted, 2 where x = 0 is (a zero or non-finite right-hand side,
+// or a tolerance over kDirectTol), 0 for a system that is not active.  With
+// begin != nullptr this is also the solve's launch_begin (of nrhs right-hand
+// sides; all its systems in one batch).
 void launch_start(int op, const double* partial, int nblk, int R, int nsys, const SysState& S, int* gate, double tol,
                   hipStream_t st, const SlotUpload* begin = nullptr, int nrhs = 0);
 
@@ -323,6 +321,9 @@ void launch_merge_init(int* init, int* active64, int n, hipStream_t st);
 // dst = src, 16-byte aligned, non-overlapping (counter calibration)
 void launch_stream_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
 void launch_fill_int(int* p, long long n, int v, hipStream_t st);
+// The state at the start of a solve: flags and counters 0, no deferred update
+// pending, the used systems active (system j R + r for r < nrhs, or as a slot
+// solve's terms say).
 void launch_begin(const SysState& S, int nsys, int R, int nrhs, const SlotUpload& up, hipStream_t st);
 
 int stencil_blocks(int dim, int n);   // blocks per system of a stencil launch (tile grid)

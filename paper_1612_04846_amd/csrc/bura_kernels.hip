@@ -1353,26 +1353,23 @@ struct RowBuf {
       v[2] = ld(voff + 2 * (unsigned)sizeof(T), soff);
     }
   }
-  template <bool NT>
   __device__ __forceinline__ void st2(const T (&v)[2], unsigned voff, unsigned soff) const {
     if constexpr (sizeof(T) == 4) {
       const unsigned __attribute__((ext_vector_type(2))) w = {__float_as_uint(v[0]), __float_as_uint(v[1])};
-      __builtin_amdgcn_raw_buffer_store_b64(w, r, voff, soff, NT ? 2 : 0);
+      __builtin_amdgcn_raw_buffer_store_b64(w, r, voff, soff, 0);
     } else {
       const unsigned __attribute__((ext_vector_type(4))) w = {
           (unsigned)__double2loint(v[0]), (unsigned)__double2hiint(v[0]), (unsigned)__double2loint(v[1]),
           (unsigned)__double2hiint(v[1])};
-      __builtin_amdgcn_raw_buffer_store_b128(w, r, voff, soff, NT ? 2 : 0);
+      __builtin_amdgcn_raw_buffer_store_b128(w, r, voff, soff, 0);
     }
   }
-  // NT: the nontemporal hint (the value is read again only by a later kernel)
-  template <bool NT>
   __device__ __forceinline__ void st(T v, unsigned voff, unsigned soff) const {
     if constexpr (sizeof(T) == 4)
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, NT ? 2 : 0);
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, 0);
     else
       __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(unsigned __attribute__((ext_vector_type(2))), v), r,
-                                            voff, soff, NT ? 2 : 0);
+                                            voff, soff, 0);
   }
 };
 
@@ -1870,10 +1867,9 @@ struct RowPair {
     if (VAR) w1.ld2(u, cb, (unsigned)min(max(r + 1, 0), n) * rowb);
   }
   // stores the columns that are on the grid
-  template <bool NT>
   __device__ __forceinline__ void store(const RowBuf<T>& b, const T (&v)[2], int r) const {
-    if (on[1]) b.template st2<NT>(v, cb, (unsigned)r * rowb);
-    else if (on[0]) b.template st<NT>(v[0], cb, (unsigned)r * rowb);
+    if (on[1]) b.st2(v, cb, (unsigned)r * rowb);
+    else if (on[0]) b.st(v[0], cb, (unsigned)r * rowb);
   }
 };
 
@@ -2066,7 +2062,7 @@ __global__ __launch_bounds__(kRowThreads) void k_down2r(LevelDev<T> Lf, LevelDev
 #pragma unroll
       for (int c = 0; c < 2; ++c) bh[0][c] -= am * q[c];
       if (t >= 2 * K0 && t < f1) {
-        pr.template store<false>(bob, bh[0], t);
+        pr.store(bob, bh[0], t);
         const double r0 = (double)bh[0][0], r1 = (double)(bh[0][1] * pr.m1);   // (lanes past the grid: 0)
         rr += r0 * r0;
         rr += r1 * r1;
@@ -2089,7 +2085,7 @@ __global__ __launch_bounds__(kRowThreads) void k_down2r(LevelDev<T> Lf, LevelDev
     for (int c = 0; c < 2; ++c) res[c] = bh[NU][c] - res[c];
     // the pre-smoothed iterate: sweep NU's newest row t - NU + 1
     const int gx = t - NU + 1;
-    if (keepx && gx >= 2 * K0 && gx < f1) pr.template store<false>(xsb, xn[NU - 1], gx);
+    if (keepx && gx >= 2 * K0 && gx < f1) pr.store(xsb, xn[NU - 1], gx);
 #pragma unroll
     for (int m = 0; m < NU; ++m)
 #pragma unroll
@@ -2110,7 +2106,7 @@ __global__ __launch_bounds__(kRowThreads) void k_down2r(LevelDev<T> Lf, LevelDev
       const bool odd = f & 1;
       if (restricts && !odd && f != 2 * K0) {
         const int K = f / 2 - 1;
-        bcb.template st<false>(T(0.25) * s_lo + T(0.5) * s_mid + T(0.25) * acc, cbc, (unsigned)K * (unsigned)nc * (unsigned)sizeof(T));
+        bcb.st(T(0.25) * s_lo + T(0.5) * s_mid + T(0.25) * acc, cbc, (unsigned)K * (unsigned)nc * (unsigned)sizeof(T));
       }
       // selects, not stores in two branches: the compiler would merge those
       // into one store through a pointer and keep both sums in scratch memory
@@ -2276,7 +2272,7 @@ __global__ __launch_bounds__(kRowThreads) void k_up2r(LevelDev<T> Lc, LevelDev<T
     }
     const int g = t - (NS - 1);
     if (g >= y0 && g < y1) {
-      pr.template store<false>(xsb, xn[NS - 1], g);
+      pr.store(xsb, xn[NS - 1], g);
       if (DOT) {
         dot += (double)bh[NS - 1][0] * (double)xn[NS - 1][0];   // (x is 0 off the grid)
         dot += (double)bh[NS - 1][1] * (double)xn[NS - 1][1];
@@ -3080,12 +3076,12 @@ __global__ __launch_bounds__(kRowThreads) void k_spmv_r2(LevelDev<T> L, const T*
       T up[2], qv[2];
       p_new(rz[s], re[s], j + 1, up);
       pair_apply<T, VAR>(qv, rf[s], fd, c, rec[RD + 1 - REC], rec[RD + REC], dn, up, L.wc, s_);
-      pr.template store<false>(pnb, c, j);
-      if (WQ) pr.template store<false>(qb, qv, j);
+      pr.store(pnb, c, j);
+      if (WQ) pr.store(qb, qv, j);
       // the deferred update uses p_old = pc (pe is p_old whenever alpha != 0)
       if (UPD) {
         const T xv[2] = {rx[s][0] + ap * pc[0], rx[s][1] + ap * pc[1]};
-        pr.template store<false>(xb, xv, j);
+        pr.store(xb, xv, j);
       }
       // (off the grid c is 0)
       dot += (double)c[0] * (double)qv[0];
@@ -3413,11 +3409,11 @@ __global__ __launch_bounds__(1024) void k_residual64_2r(LevelDev<double> L, cons
     const double rv64 = rf[s] - ax;
     if (col_on) {
       const unsigned g = (unsigned)row * 4u, ib = (unsigned)i * 4u;
-      rb32.template st<false>((RT)rv64, ib * (unsigned)(sizeof(RT) / 4), g * (unsigned)(sizeof(RT) / 4));
+      rb32.st((RT)rv64, ib * (unsigned)(sizeof(RT) / 4), g * (unsigned)(sizeof(RT) / 4));
       // UPD: the segment's first and last rows are left to k_update_seg_rows
       if (sizeof(RT) == 4 && (!UPD || (j != j0 && j != j1 - 1))) {
-        eb.template st<false>(0.0f, ib, g);
-        if (UPD) xsb.template st<false>(c, 2u * ib, 2u * g);
+        eb.st(0.0f, ib, g);
+        if (UPD) xsb.st(c, 2u * ib, 2u * g);
       }
       rr += rv64 * rv64;
     }
