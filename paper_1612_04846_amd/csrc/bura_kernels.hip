@@ -1017,7 +1017,7 @@ __device__ __forceinline__ T add_step(T x, T r, T d) {
 // with x.  Gathered, with the hardware reciprocal, the FP32 preconditioner of
 // 155^2 with variable coefficients was off by 5.7e-7; in this form, and with
 // the division rounded as IEEE does, by 7.5e-8 (2^-24 is 6.0e-8).
-template <typename T, int DIM, bool VAR, int P>
+template <typename T, int DIM, bool VAR, int P, int NT>
 struct LdsPoints {
   int S1, S2;
   int q[P];
@@ -1033,7 +1033,7 @@ struct LdsPoints {
     if (!VAR) di[0] = T(1) / (wc * T(2 * DIM) + s);
 #pragma unroll
     for (int u = 0; u < P; ++u) {
-      const int p = threadIdx.x + kCoarseThreads * u;
+      const int p = threadIdx.x + NT * u;
       on[u] = p < N;
       int i, j, k;
       ijk_of<DIM>(on[u] ? p : 0, n, rn, i, j, k);
@@ -1090,14 +1090,14 @@ struct LdsPoints {
 // thread's points; returns the buffer that holds the level's iterate (every
 // write of it behind a barrier).  The points are set up again after the coarser
 // levels: held across them, the face weights of all levels together spill.
-template <typename T, int DIM, bool VAR, int P, int LV>
+template <typename T, int DIM, bool VAR, int P, int NT, int LV>
 __device__ __forceinline__ T* lds_cycle(const LdsHierarchy<T>& H, T* sm, T s, const T* b) {
   const LevelDev<T>& L = H.lev[LV];
   const int n = L.n, S1 = n + 2, S2 = S1 * S1;
   T* X = sm + H.off[LV];
   T* Y = X + (DIM == 3 ? S2 * S1 : S2);
   {
-    const LdsPoints<T, DIM, VAR, P> pt(L, s);
+    const LdsPoints<T, DIM, VAR, P, NT> pt(L, s);
     // the first sweep, from zero
     const bool bottom = LV + 1 >= H.nlev;
     const T om0 = bottom ? (L.N == 1 ? T(1) : H.omega) : sweep_w(H.pre, 0);
@@ -1137,8 +1137,8 @@ __device__ __forceinline__ T* lds_cycle(const LdsHierarchy<T>& H, T* sm, T s, co
             acc += (DIM == 3 ? wt[dk + 1] : T(1)) * wt[dj + 1] * wt[dx + 1] * c[dk * S2 + dj * S1 + dx];
       bc[0] = acc;
     }
-    const T* C = lds_cycle<T, DIM, VAR, 1, LV + 1>(H, sm, s, bc);
-    const LdsPoints<T, DIM, VAR, P> pt(L, s);
+    const T* C = lds_cycle<T, DIM, VAR, 1, NT, LV + 1>(H, sm, s, bc);
+    const LdsPoints<T, DIM, VAR, P, NT> pt(L, s);
     // x += P x_c: an odd index lies on a coarse point, an even one halfway
     // between two (the padding is the boundary); only this thread's points of X
     // change before the barrier
@@ -1147,7 +1147,7 @@ __device__ __forceinline__ T* lds_cycle(const LdsHierarchy<T>& H, T* sm, T s, co
 #pragma unroll
     for (int u = 0; u < P; ++u) {
       int i, j, k;
-      ijk_of<DIM>(pt.on[u] ? threadIdx.x + kCoarseThreads * u : 0, n, rn, i, j, k);
+      ijk_of<DIM>(pt.on[u] ? threadIdx.x + NT * u : 0, n, rn, i, j, k);
       const int oi = (i & 1) ? 0 : 1, oj = (j & 1) ? 0 : T1, ok = (DIM == 2 || (k & 1)) ? 0 : T2;
       const T* c = C + ((DIM == 3 ? (k + 1) / 2 : 0) * T1 + (j + 1) / 2) * T1 + (i + 1) / 2;
       // an index on a coarse point takes it twice, halved: exact
@@ -1161,8 +1161,8 @@ __device__ __forceinline__ T* lds_cycle(const LdsHierarchy<T>& H, T* sm, T s, co
   return X;
 }
 
-template <typename T, int DIM, bool VAR, int PER>
-__global__ __launch_bounds__(kCoarseThreads) void k_coarse(LdsHierarchy<T> H, const T* __restrict__ b,
+template <typename T, int DIM, bool VAR, int PER, int NT>
+__global__ __launch_bounds__(NT) void k_coarse(LdsHierarchy<T> H, const T* __restrict__ b,
                                                            T* __restrict__ x, const T* __restrict__ shift,
                                                            const int* __restrict__ active,
                                                            unsigned long long* __restrict__ ctr, int elems) {
@@ -1175,16 +1175,16 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse(LdsHierarchy<T> H, co
   const long long off = (long long)sys * N;
   T bv[PER];
 #pragma unroll
-  for (int u = 0; u < PER; ++u) bv[u] = b[off + min((int)threadIdx.x + kCoarseThreads * u, N - 1)];
-  for (int i = threadIdx.x; i < elems; i += kCoarseThreads) sm[i] = T(0);
+  for (int u = 0; u < PER; ++u) bv[u] = b[off + min((int)threadIdx.x + NT * u, N - 1)];
+  for (int i = threadIdx.x; i < elems; i += NT) sm[i] = T(0);
   const T s = shift[sys];
   __syncthreads();
-  const T* X = lds_cycle<T, DIM, VAR, PER, 0>(H, sm, s, bv);
+  const T* X = lds_cycle<T, DIM, VAR, PER, NT, 0>(H, sm, s, bv);
   const float rn = 1.0f / (float)n;
   const int S1 = n + 2;
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
-    const int p = threadIdx.x + kCoarseThreads * u;
+    const int p = threadIdx.x + NT * u;
     if (p < N) {
       int i, j, k;
       ijk_of<DIM>(p, n, rn, i, j, k);
@@ -4142,21 +4142,30 @@ template <typename T>
 void Launch<T>::coarse_solve(int dim, bool var, const LdsHierarchy<T>& H, const T* b, T* x, const T* shift,
                              const int* active, int nsys, size_t lds_bytes, hipStream_t st,
                              unsigned long long* ctr) {
-  const int per = (int)((H.lev[0].N + kCoarseThreads - 1) / kCoarseThreads);
+  // As many threads as the first level has points, in steps of 256, 512 and
+  // 1024.  Where there are enough systems to fill the chip either way, the
+  // threads that the levels below leave idle count: 31^2 then takes two points
+  // per thread of 512.  FP64, 2048 systems: 31^2 64 -> 40 us, 15^2 42 -> 32,
+  // 7^3 38 -> 28.
+  const int N0 = (int)H.lev[0].N, N1 = H.nlev > 1 ? (int)H.lev[1].N : 0;
+  const int per = (N0 + kCoarseThreads - 1) / kCoarseThreads;
   const int elems = (int)(lds_bytes / sizeof(T));
-#define K_CO(D, V, P)                                                                                            \
+#define K_CO(D, V, P, NT_)                                                                                       \
   do {                                                                                                           \
-    auto* kern = k_coarse<T, D, V, P>;                                                                           \
+    auto* kern = k_coarse<T, D, V, P, NT_>;                                                                      \
     if (lds_bytes > 64 * 1024)                                                                                   \
       (void)hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);  \
-    hipLaunchKernelGGL(kern, dim3(nsys), dim3(kCoarseThreads), lds_bytes, st, H, b, x, shift, active, ctr, elems); \
+    hipLaunchKernelGGL(kern, dim3(nsys), dim3(NT_), lds_bytes, st, H, b, x, shift, active, ctr, elems);          \
   } while (0)
-#define K_COP(D, V, dummy)     \
-  do {                         \
-    if (per <= 1) K_CO(D, V, 1); \
-    else if (per == 2) K_CO(D, V, 2); \
-    else if (per <= 4) K_CO(D, V, 4); \
-    else K_CO(D, V, 6);        \
+#define K_COP(D, V, dummy)                                                \
+  do {                                                                    \
+    if (N0 <= 256) K_CO(D, V, 1, 256);                                    \
+    else if (N0 <= 512) K_CO(D, V, 1, 512);                               \
+    else if (N0 <= 1024 && N1 <= 512 && nsys >= 1024) K_CO(D, V, 2, 512); \
+    else if (per <= 1) K_CO(D, V, 1, kCoarseThreads);                     \
+    else if (per == 2) K_CO(D, V, 2, kCoarseThreads);                     \
+    else if (per <= 4) K_CO(D, V, 4, kCoarseThreads);                     \
+    else K_CO(D, V, 6, kCoarseThreads);                                   \
   } while (0)
   BURA_DISPATCH_DV(dim, var, K_COP, 0);
 #undef K_COP
