@@ -3965,9 +3965,12 @@ static inline dim3 march_block(int n) { return dim3(march_x(n), kBlock / march_x
 // -> under 8, restrictions 23 and 24 -> 15 and 8); shorter walks read their
 // first and last plane again.  Only for kernels that write no partials: those
 // are grouped by kMarchZ, whatever else shares the launch.
-static inline int march_planes(int n, long long tiles, int least) {
+// Below `few` planes only while there are fewer than 4 workgroups per CU: a
+// restriction reads 2 mz + 1 fine planes for mz coarse ones (15^3 FP32, 512 systems: 2 planes 33
+// us, 4 planes 28, 8 planes 26; 63^3, 18 systems: 1 plane 15.8, 2 planes 13.9).
+static inline int march_planes(int n, long long tiles, int least, int few = 0) {
   int mz = kMarchZ;
-  while (mz > least && tiles * ((n + mz - 1) / mz) < 2048) mz /= 2;
+  while (mz > least && tiles * ((n + mz - 1) / mz) < (mz > few ? 2048 : 1024)) mz /= 2;
   return mz;
 }
 
@@ -4113,7 +4116,7 @@ void Launch<T>::restrict_residual(int dim, bool var, const LevelDev<T>& Lf, cons
   if (dim == 3) {
     const int nc = Lc.n;
     const int xt = (nc + kRcx - 1) / kRcx, yt = (nc + kRcy - 1) / kRcy;
-    const int mz = march_planes(nc, (long long)xt * yt * nsys, 1);
+    const int mz = march_planes(nc, (long long)xt * yt * nsys, 1, 4);
     const dim3 g3(xt, yt * ((nc + mz - 1) / mz), nsys);
     if (var) hipLaunchKernelGGL((k_restrict3<T, true>), g3, dim3(256), 0, st, Lf, Lc, b, x, bc, shift, active, ctr, mz);
     else hipLaunchKernelGGL((k_restrict3<T, false>), g3, dim3(256), 0, st, Lf, Lc, b, x, bc, shift, active, ctr, mz);
