@@ -1353,23 +1353,30 @@ struct RowBuf {
       v[2] = ld(voff + 2 * (unsigned)sizeof(T), soff);
     }
   }
+  // NT: the nontemporal hint.  The row kernels run 1 - 2 % faster without it (two
+  // rows of odd length share a line); the stencil product of a plan without a
+  // fused hierarchy carries it, whose passes after it read other vectors first
+  // (256^2 FP64, 512 systems: the vector update 199 -> 188 us, the product 150
+  // -> 159).
+  template <bool NT = false>
   __device__ __forceinline__ void st2(const T (&v)[2], unsigned voff, unsigned soff) const {
     if constexpr (sizeof(T) == 4) {
       const unsigned __attribute__((ext_vector_type(2))) w = {__float_as_uint(v[0]), __float_as_uint(v[1])};
-      __builtin_amdgcn_raw_buffer_store_b64(w, r, voff, soff, 0);
+      __builtin_amdgcn_raw_buffer_store_b64(w, r, voff, soff, NT ? 2 : 0);
     } else {
       const unsigned __attribute__((ext_vector_type(4))) w = {
           (unsigned)__double2loint(v[0]), (unsigned)__double2hiint(v[0]), (unsigned)__double2loint(v[1]),
           (unsigned)__double2hiint(v[1])};
-      __builtin_amdgcn_raw_buffer_store_b128(w, r, voff, soff, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(w, r, voff, soff, NT ? 2 : 0);
     }
   }
+  template <bool NT = false>
   __device__ __forceinline__ void st(T v, unsigned voff, unsigned soff) const {
     if constexpr (sizeof(T) == 4)
-      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, 0);
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, NT ? 2 : 0);
     else
       __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(unsigned __attribute__((ext_vector_type(2))), v), r,
-                                            voff, soff, 0);
+                                            voff, soff, NT ? 2 : 0);
   }
 };
 
@@ -1867,9 +1874,10 @@ struct RowPair {
     if (VAR) w1.ld2(u, cb, (unsigned)min(max(r + 1, 0), n) * rowb);
   }
   // stores the columns that are on the grid
+  template <bool NT = false>
   __device__ __forceinline__ void store(const RowBuf<T>& b, const T (&v)[2], int r) const {
-    if (on[1]) b.st2(v, cb, (unsigned)r * rowb);
-    else if (on[0]) b.st(v[0], cb, (unsigned)r * rowb);
+    if (on[1]) b.template st2<NT>(v, cb, (unsigned)r * rowb);
+    else if (on[0]) b.template st<NT>(v[0], cb, (unsigned)r * rowb);
   }
 };
 
@@ -3005,7 +3013,9 @@ __global__ __launch_bounds__(kRowThreads) void k_spmv_r2(LevelDev<T> L, const T*
                                                   unsigned long long* __restrict__ ctr, Fin fin,
                                                   T* __restrict__ x, const double* __restrict__ alpha, int rows) {
   constexpr int WORDS = spmv_words(), REC = row_rec(WORDS);   // LDS: p_new's pair
-  constexpr int LEAD = row_lead<T>();
+  // (without face weights FP64 has registers for four rows of lead too: 255^2,
+  // 512 systems 185 -> 175 us)
+  constexpr int LEAD = VAR ? row_lead<T>() : 4;
   const RowTile rt = row_tile();
   const int sys = rt.sys;
   if (!active[sys]) return;
@@ -3076,12 +3086,12 @@ __global__ __launch_bounds__(kRowThreads) void k_spmv_r2(LevelDev<T> L, const T*
       T up[2], qv[2];
       p_new(rz[s], re[s], j + 1, up);
       pair_apply<T, VAR>(qv, rf[s], fd, c, rec[RD + 1 - REC], rec[RD + REC], dn, up, L.wc, s_);
-      pr.store(pnb, c, j);
-      if (WQ) pr.store(qb, qv, j);
+      pr.template store<WQ>(pnb, c, j);
+      if (WQ) pr.template store<WQ>(qb, qv, j);
       // the deferred update uses p_old = pc (pe is p_old whenever alpha != 0)
       if (UPD) {
         const T xv[2] = {rx[s][0] + ap * pc[0], rx[s][1] + ap * pc[1]};
-        pr.store(xb, xv, j);
+        pr.template store<WQ>(xb, xv, j);
       }
       // (off the grid c is 0)
       dot += (double)c[0] * (double)qv[0];
