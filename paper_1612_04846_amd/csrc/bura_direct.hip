@@ -314,7 +314,8 @@ void run_pass(SinePass a, long long batches, hipStream_t st) {
 // places and 130 - 177 registers (2 - 3 waves per SIMD) the passes took 245 and
 // 140 us; one load per value, LDS positions that are constants away from one
 // register and twiddle powers formed in pairs leave 98 - 116 registers, 4 waves,
-// and 121 and 110 us (255^3, 9 systems: 1030, 717 and 660 -> 803, 527 and 467).
+// and 121 - 142, by the card, and 110 us (255^3, 9 systems: 1030, 717 and 660
+// -> 803, 527 and 467).
 // --------------------------------------------------------------------------
 struct FftPass {
   const double* in;

@@ -970,9 +970,10 @@ __global__ __launch_bounds__(256) void k_restrict3(LevelDev<T> Lf, LevelDev<T> L
 // step and no boundary tests; and a coarse point's right-hand side goes
 // straight into its owner's registers.  Against the version that walked the
 // points of every step in a loop, read the face weights in each sweep and
-// copied the iterate back: 63^2 FP32, 2048 systems 83 -> 46 us; 15^3 FP32 with
-// variable coefficients 25 -> 13 us; FP64 takes 47^2 here (15 us) where 23^2
-// (20 us) and the two level kernels of 47^2 (10 us) had run.
+// copied the iterate back, with variable coefficients: 63^2 FP32, 2048 systems
+// 101 -> 87 us a launch, the mean over a solve; 63^2, 8 systems 30 -> 13; 15^3,
+// 8 systems 30 -> 15; FP64, 64 systems, 47^2 here (17 us) where 23^2 (21 us)
+// and the two level kernels of 47^2 (9 us each) had run.
 // --------------------------------------------------------------------------
 // weight i of a half-cycle (selected without indexing the array, which would
 // put the by-value argument in scratch memory)
